@@ -1,146 +1,17 @@
-// Vocabulary-head products of Pruned CTC on matrix cores (gfx950).
+// Vocabulary head of Pruned CTC: what the bf16 and fp32 products share (gfx950).
 //
-//  * lse_partial: logits tile Z^T = W_tile H_tile^T with a fused online log-sum-exp
-//    epilogue over the vocabulary (Eq. lognorm; Algorithm 1 "online log-sum-exp over
-//    vocabulary chunks").  The M x V logits are never written; each workgroup keeps a
-//    running (max, sum) per frame over its vocabulary partition.
-//  * lse_finalize: combines the partitions per frame in double.
-//  * gather_s: S = Z[:, U] - lambda for the selected classes, subtraction in double and
-//    one rounding to float (Algorithm 1; App. B.1 "Forward computation").
-//  * recompute_dz: one vocabulary chunk of dZ = scatter_U(G) - g p, p = exp(Z - lambda),
-//    with Z recomputed (Eq. vjp; Algorithm 1 backward loop); stored in the input dtype.
-//  * dh_gemm / dw_gemm: dH += dZ W_c and dW_c = dZ^T H (App. A, Step 3).
-//
-// Every product C[i][j] = sum_k A[i][k] B[j][k] goes through tile_gemm (pctc_device.h).
+//  * lse_finalize: lambda from the normaliser's per-partition (max, sum) pairs, in double, and
+//    S = Z[:, U] - lambda where the selected logits wait for it;
+//  * greedy emission head: the best of the partitions and the CTC collapse;
+//  * plan and chunk loop of the recomputed backward (Eq. vjp; Algorithm 1 backward loop; App. A,
+//    Step 3), with the second stream's gates in the bf16 schedule.
+// The products themselves are in head_gemm_bf16.hip and head_gemm_f32.hip.
 #include <algorithm>
 
+#include "head_tiles.h"
 #include "pctc_internal.h"
 
 namespace pctc {
-
-// Frames (columns) per forward tile, vocabulary rows per forward tile.
-constexpr int kFwdBR = 256;
-constexpr int kFwdBC = 128;
-constexpr int kBwdB = 128;
-
-template <typename T>
-struct Cfg;
-template <>
-struct Cfg<uint16_t> {
-  static constexpr int BK = 64;
-};
-template <>
-struct Cfg<float> {
-  static constexpr int BK = 32;
-};
-
-// blockIdx -> logical work id such that consecutive logical ids land on the same XCD
-// (the dispatcher places workgroup b on XCD b % 8).
-__device__ __forceinline__ int xcd_swizzle(int bid, int nblocks) {
-  const int full = (nblocks / 8) * 8;
-  if (bid >= full) return bid;
-  return (bid % 8) * (full / 8) + bid / 8;
-}
-
-// ---------------------------------------------------------------------------------------
-// Forward: online log-sum-exp partials
-// ---------------------------------------------------------------------------------------
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-lse_partial_kernel(const T* __restrict__ H, int M, int D, const T* __restrict__ W, const float* __restrict__ bias,
-                   int V, int P, int vper, float2* __restrict__ partials) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kFwdBR, kFwdBC, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  const int work = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int mt = work % nMt;
-  const int p = work / nMt;
-  const int m0 = mt * kFwdBC;
-  const int vbeg = p * vper;
-  const int vend = min(V, vbeg + vper);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-  Operand<T> A{W, D, V, D, nullptr, nullptr};
-  Operand<T> B{H, D, M, D, nullptr, nullptr};
-  float run_max[FC], run_sum[FC];
-#pragma unroll
-  for (int j = 0; j < FC; ++j) {
-    run_max[j] = -INFINITY;
-    run_sum[j] = 0.f;
-  }
-  f32x16 acc[FR][FC];
-  for (int v0 = vbeg; v0 < vend; v0 += kFwdBR) {
-    tile_gemm<T, kFwdBR, kFwdBC, BK, Lay::KMajor, Lay::KMajor>(A, B, v0, m0, 0, D, lds, acc);
-    if (bias) {
-#pragma unroll
-      for (int i = 0; i < FR; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int v = v0 + acc_row<kFwdBR>(wave, lane, i, r);
-          const float b = (v < vend) ? bias[v] : 0.f;
-#pragma unroll
-          for (int j = 0; j < FC; ++j) acc[i][j][r] += b;
-        }
-    }
-    // rows past the partition end take no part in the sums
-    if (v0 + kFwdBR > vend) {
-#pragma unroll
-      for (int i = 0; i < FR; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool ok = v0 + acc_row<kFwdBR>(wave, lane, i, r) < vend;
-#pragma unroll
-          for (int j = 0; j < FC; ++j) acc[i][j][r] = ok ? acc[i][j][r] : -INFINITY;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < FC; ++j) {
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < FR; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
-      tmax = fmaxf(tmax, swap_halves(tmax));
-      const float nmax = fmaxf(run_max[j], tmax);
-      // a column with no finite logit yet (rows masked by a -inf bias) adds nothing
-      const float ms = (nmax == -INFINITY) ? 0.f : nmax * kLog2e;
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < FR; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s += fast_exp2(fmaf(acc[i][j][r], kLog2e, -ms));
-      s += swap_halves(s);
-      const float scale = (run_max[j] == -INFINITY) ? 0.f : fast_exp2((run_max[j] - nmax) * kLog2e);
-      run_sum[j] = fmaf(run_sum[j], scale, s);
-      run_max[j] = nmax;
-    }
-  }
-  // Combine the two wavefronts that share frames (row halves), then write the partial.
-  __syncthreads();
-  float2* xch = reinterpret_cast<float2*>(lds);  // [2 col halves][FC*32]
-  const int rowhalf = wave >> 1, colhalf = wave & 1;
-  if (rowhalf == 1 && lane < 32) {
-#pragma unroll
-    for (int j = 0; j < FC; ++j) xch[colhalf * (FC * 32) + j * 32 + lane] = make_float2(run_max[j], run_sum[j]);
-  }
-  __syncthreads();
-  if (rowhalf == 0 && lane < 32) {
-#pragma unroll
-    for (int j = 0; j < FC; ++j) {
-      const float2 o = xch[colhalf * (FC * 32) + j * 32 + lane];
-      const float nmax = fmaxf(run_max[j], o.x);
-      float s = 0.f;
-      if (run_max[j] != -INFINITY) s += run_sum[j] * fast_exp2((run_max[j] - nmax) * kLog2e);
-      if (o.x != -INFINITY) s += o.y * fast_exp2((o.x - nmax) * kLog2e);
-      if (nmax != nmax) s = nmax;  // NaN logits propagate
-      const int m = m0 + acc_col<kFwdBC>(wave, lane, j);
-      if (m < M) partials[static_cast<int64_t>(p) * M + m] = make_float2(nmax, s);
-    }
-  }
-}
 
 // lambda_m from the per-partition (max, sum) pairs: 16 frames per block, 16 lanes per frame
 // splitting the partitions; the maximum is exact, the rescaled sum is accumulated in double
@@ -213,18 +84,6 @@ __global__ void lam2_kernel(const double* __restrict__ lam, int M, float2* __res
   lam2[m] = make_float2(hi, static_cast<float>(l2 - static_cast<double>(hi)));
 }
 
-int lse_partitions(int M, int V) {
-  // Enough workgroups to fill 256 compute units a few times over; the partition count
-  // (not V) sets the size of the partial buffer.
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  int P = (2048 + nMt - 1) / nMt;
-  const int vtiles = (V + kFwdBR - 1) / kFwdBR;
-  if (P > vtiles) P = vtiles;
-  if (P > 256) P = 256;
-  if (P < 1) P = 1;
-  return P;
-}
-
 size_t lse_partial_bytes(int M, int D) {
   return align_up(static_cast<size_t>(lse_max_parts(D)) * M * sizeof(float2), 256);
 }
@@ -239,24 +98,10 @@ hipError_t launch_lam2(const double* lam, int M, float2* lam2, hipStream_t strea
 hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
                       float2* partials, double* lam, float2* lam2, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  const int P = lse_partitions(M, V);
-  const int vtiles = (V + kFwdBR - 1) / kFwdBR;
-  const int vper = ((vtiles + P - 1) / P) * kFwdBR;
-  const int Peff = (V + vper - 1) / vper;
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  int Pfin = Peff;
-  if (dtype == 1) {
-    hipError_t e1 = launch_lse_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias,
-                                            V, partials, &Pfin, stream);
-    if (e1 != hipSuccess) return e1;
-  } else {
-    Prof pr("lse_partial", stream);
-    hipLaunchKernelGGL(lse_partial_kernel<float>, dim3(nMt * Peff), dim3(256), 0, stream,
-                       static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, Peff, vper, partials);
-  }
-  hipError_t e = hipGetLastError();
+  int P = 0;
+  hipError_t e = launch_lse_partials(dtype, H, M, D, W, bias, V, partials, &P, stream);
   if (e != hipSuccess) return e;
-  return launch_lse_finalize(partials, M, Pfin, lam, lam2, nullptr, nullptr, nullptr, 0, stream);
+  return launch_lse_finalize(partials, M, P, lam, lam2, nullptr, nullptr, nullptr, 0, stream);
 }
 
 hipError_t launch_lse_partials(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
@@ -266,16 +111,8 @@ hipError_t launch_lse_partials(int dtype, const void* H, int M, int D, const voi
   if (dtype == 1)
     return launch_lse_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, V,
                                    partials, P_out, stream);
-  const int P = lse_partitions(M, V);
-  const int vtiles = (V + kFwdBR - 1) / kFwdBR;
-  const int vper = ((vtiles + P - 1) / P) * kFwdBR;
-  const int Peff = (V + vper - 1) / vper;
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  *P_out = Peff;
-  Prof pr("lse_partial", stream);
-  hipLaunchKernelGGL(lse_partial_kernel<float>, dim3(nMt * Peff), dim3(256), 0, stream, static_cast<const float*>(H), M,
-                     D, static_cast<const float*>(W), bias, V, Peff, vper, partials);
-  return hipGetLastError();
+  return launch_lse_partial_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, partials,
+                                P_out, stream);
 }
 
 hipError_t launch_lse_finalize(const float2* partials, int M, int P, double* lam, float2* lam2, const double* Zd,
@@ -299,77 +136,6 @@ hipError_t launch_lse_finalize(const float2* partials, int M, int P, double* lam
 // collapse of each utterance's argmax sequence (Sec. 3.1: merge repeats, drop blanks)
 // ---------------------------------------------------------------------------------------
 
-__device__ __forceinline__ void amax_merge_g(float& bv, int& bi, float ov, int oi) {
-  if (ov > bv || (ov == bv && oi < bi)) {
-    bv = ov;
-    bi = oi;
-  }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-amax_partial_kernel(const T* __restrict__ H, int M, int D, const T* __restrict__ W, const float* __restrict__ bias,
-                    int V, int P, int vper, float2* __restrict__ partials) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kFwdBR, kFwdBC, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  const int work = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int mt = work % nMt;
-  const int p = work / nMt;
-  const int m0 = mt * kFwdBC;
-  const int vbeg = p * vper;
-  const int vend = min(V, vbeg + vper);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  Operand<T> A{W, D, V, D, nullptr, nullptr};
-  Operand<T> B{H, D, M, D, nullptr, nullptr};
-  float bv[FC];
-  int bi[FC];
-#pragma unroll
-  for (int j = 0; j < FC; ++j) {
-    bv[j] = -INFINITY;
-    bi[j] = 0x7fffffff;
-  }
-  f32x16 acc[FR][FC];
-  for (int v0 = vbeg; v0 < vend; v0 += kFwdBR) {
-    tile_gemm<T, kFwdBR, kFwdBC, BK, Lay::KMajor, Lay::KMajor>(A, B, v0, m0, 0, D, lds, acc);
-#pragma unroll
-    for (int j = 0; j < FC; ++j)
-#pragma unroll
-      for (int i = 0; i < FR; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int v = v0 + acc_row<kFwdBR>(wave, lane, i, r);
-          if (v >= vend) continue;
-          const float x = acc[i][j][r] + (bias ? bias[v] : 0.f);
-          if (x > bv[j]) {
-            bv[j] = x;
-            bi[j] = v;
-          }
-        }
-  }
-#pragma unroll
-  for (int j = 0; j < FC; ++j) amax_merge_g(bv[j], bi[j], swap_halves(bv[j]), __shfl_xor(bi[j], 32, 64));
-  __syncthreads();
-  float2* xch = reinterpret_cast<float2*>(lds);
-  const int rowhalf = wave >> 1, colhalf = wave & 1;
-  if (rowhalf == 1 && lane < 32) {
-#pragma unroll
-    for (int j = 0; j < FC; ++j) xch[colhalf * (FC * 32) + j * 32 + lane] = make_float2(bv[j], __int_as_float(bi[j]));
-  }
-  __syncthreads();
-  if (rowhalf == 0 && lane < 32) {
-#pragma unroll
-    for (int j = 0; j < FC; ++j) {
-      const float2 o = xch[colhalf * (FC * 32) + j * 32 + lane];
-      amax_merge_g(bv[j], bi[j], o.x, __float_as_int(o.y));
-      const int m = m0 + acc_col<kFwdBC>(wave, lane, j);
-      if (m < M) partials[static_cast<int64_t>(p) * M + m] = make_float2(bv[j], __int_as_float(bi[j]));
-    }
-  }
-}
-
 // ids[m]: the best of the partitions' (value, id) pairs, in partition order.
 // 16 frames per block, 16 lanes per frame splitting the partitions; the merge (larger value,
 // then smaller id) is order-independent, so the result does not depend on the split.
@@ -384,14 +150,14 @@ amax_finalize_kernel(const float2* __restrict__ partials, int M, int P, int32_t*
 #pragma unroll 4
     for (int p = ph; p < P; p += 16) {
       const float2 q = partials[static_cast<int64_t>(p) * M + m];
-      amax_merge_g(bv, bi, q.x, __float_as_int(q.y));
+      amax_merge(bv, bi, q.x, __float_as_int(q.y));
     }
   }
 #pragma unroll
   for (int o = 8; o >= 1; o >>= 1) {
     const float ov = __shfl_xor(bv, o, 16);
     const int oi = __shfl_xor(bi, o, 16);
-    amax_merge_g(bv, bi, ov, oi);
+    amax_merge(bv, bi, ov, oi);
   }
   if (live && ph == 0) ids[m] = (bi == 0x7fffffff) ? 0 : bi;
 }
@@ -424,21 +190,12 @@ hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, 
                          int32_t* lengths, hipStream_t stream) {
   if (M > 0) {
     int Pfin;
-    if (dtype == 1) {
-      hipError_t e = launch_amax_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W),
-                                              bias, V, partials, &Pfin, stream);
-      if (e != hipSuccess) return e;
-    } else {
-      const int P = lse_partitions(M, V);
-      const int vtiles = (V + kFwdBR - 1) / kFwdBR;
-      const int vper = ((vtiles + P - 1) / P) * kFwdBR;
-      Pfin = (V + vper - 1) / vper;
-      const int nMt = (M + kFwdBC - 1) / kFwdBC;
-      Prof pr("amax_partial", stream);
-      hipLaunchKernelGGL(amax_partial_kernel<float>, dim3(nMt * Pfin), dim3(256), 0, stream,
-                         static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, Pfin, vper,
-                         partials);
-    }
+    hipError_t e =
+        dtype == 1 ? launch_amax_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W),
+                                              bias, V, partials, &Pfin, stream)
+                   : launch_amax_partial_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V,
+                                             partials, &Pfin, stream);
+    if (e != hipSuccess) return e;
     Prof pr("amax_finalize", stream);
     hipLaunchKernelGGL(amax_finalize_kernel, dim3((M + kFinFrames - 1) / kFinFrames), dim3(256), 0, stream, partials,
                        M, Pfin, ids);
@@ -455,46 +212,6 @@ hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, 
 // Selected-class log-probabilities S
 // ---------------------------------------------------------------------------------------
 
-template <typename T>
-__global__ void __launch_bounds__(256, 2)
-gather_s_kernel(const T* __restrict__ H, int M, int D, const T* __restrict__ W, const float* __restrict__ bias,
-                const int32_t* __restrict__ u_ids, const int32_t* __restrict__ Kdev, int K_max,
-                const double* __restrict__ lam, float* __restrict__ S, int ldS) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kFwdBR, kFwdBC, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  const int mt = blockIdx.x % nMt;
-  const int jt = blockIdx.x / nMt;
-  const int K = *Kdev;
-  const int j0 = jt * kFwdBR;
-  if (j0 >= K) return;
-  const int m0 = mt * kFwdBC;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  Operand<T> A{W, D, K_max, D, u_ids, Kdev};
-  Operand<T> B{H, D, M, D, nullptr, nullptr};
-  f32x16 acc[FR][FC];
-  tile_gemm<T, kFwdBR, kFwdBC, BK, Lay::Gathered, Lay::KMajor>(A, B, j0, m0, 0, D, lds, acc);
-#pragma unroll
-  for (int j = 0; j < FC; ++j) {
-    const int m = m0 + acc_col<kFwdBC>(wave, lane, j);
-    if (m >= M) continue;
-    const double l = lam[m];
-#pragma unroll
-    for (int i = 0; i < FR; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int jj = j0 + acc_row<kFwdBR>(wave, lane, i, r);
-        if (jj < K) {
-          double z = static_cast<double>(acc[i][j][r]);
-          if (bias) z += static_cast<double>(bias[u_ids[jj]]);
-          S[static_cast<int64_t>(m) * ldS + jj] = static_cast<float>(z - l);
-        }
-      }
-  }
-}
-
 hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W, const float* bias,
                            const int32_t* u_ids, const int32_t* K, int K_max, const double* lam, float* S, int ldS,
                            hipStream_t stream) {
@@ -502,196 +219,14 @@ hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W
   if (dtype == 1)
     return launch_gather_s_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, u_ids, K,
                                 K_max, lam, S, ldS, stream);
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  const int nJt = (K_max + kFwdBR - 1) / kFwdBR;
-  Prof pr("gather_s", stream);
-  hipLaunchKernelGGL(gather_s_kernel<float>, dim3(nMt * nJt), dim3(256), 0, stream, static_cast<const float*>(H), M, D,
-                     static_cast<const float*>(W), bias, u_ids, K, K_max, lam, S, ldS);
-  return hipGetLastError();
+  return launch_gather_s_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, u_ids, K, K_max,
+                             lam, S, ldS, stream);
 }
 
 // ---------------------------------------------------------------------------------------
 // Backward
 // ---------------------------------------------------------------------------------------
 
-template <typename T>
-__device__ __forceinline__ T to_elem(float x);
-template <>
-__device__ __forceinline__ uint16_t to_elem<uint16_t>(float x) {
-  return f32_to_bf16(x);
-}
-template <>
-__device__ __forceinline__ float to_elem<float>(float x) {
-  return x;
-}
-
-// dZ chunk [M][chunk] (row pitch `chunk`): columns v_local in [0, cw) hold
-// scatter_U(G) - g p for vocabulary id c0 + v_local; columns in [cw, tile end) hold 0.
-template <typename T>
-__global__ void __launch_bounds__(256, 2)
-recompute_dz_kernel(const T* __restrict__ H, int M, int D, const T* __restrict__ W, const float* __restrict__ bias,
-                    int c0, int cw, const float2* __restrict__ lam2, const float* __restrict__ G, int ldG,
-                    const float* __restrict__ g, const int32_t* __restrict__ remap, T* __restrict__ dZ, int chunk) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kFwdBR, kFwdBC, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  __shared__ int sel[kFwdBR];
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  const int work = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int mt = work % nMt;
-  const int vt = work / nMt;
-  const int m0 = mt * kFwdBC;
-  const int vl0 = vt * kFwdBR;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    const int vl = vl0 + tid;
-    sel[tid] = (vl < cw) ? remap[c0 + vl] : -1;
-  }
-  const int any_sel = __syncthreads_or(sel[tid] >= 0);
-  Operand<T> A{W + static_cast<int64_t>(c0) * D, D, cw, D, nullptr, nullptr};
-  Operand<T> B{H, D, M, D, nullptr, nullptr};
-  f32x16 acc[FR][FC];
-  tile_gemm<T, kFwdBR, kFwdBC, BK, Lay::KMajor, Lay::KMajor>(A, B, vl0, m0, 0, D, lds, acc);
-#pragma unroll
-  for (int j = 0; j < FC; ++j) {
-    const int m = m0 + acc_col<kFwdBC>(wave, lane, j);
-    if (m >= M) continue;
-    const float gm = g[m];
-    const float2 l2 = lam2[m];
-    const bool inc = (gm != 0.f);
-#pragma unroll
-    for (int i = 0; i < FR; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int rl0 = acc_row<kFwdBR>(wave, lane, i, 4 * q);  // 4 consecutive rows
-        T out[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int rl = rl0 + e;
-          const int vl = vl0 + rl;
-          float val = 0.f;
-          if (inc && vl < cw) {
-            const float z = acc[i][j][4 * q + e] + (bias ? bias[c0 + vl] : 0.f);
-            const float t = fmaf(z, kLog2e, -l2.x) - l2.y;
-            val = -gm * fast_exp2(t);
-            if (any_sel) {
-              const int jj = sel[rl];
-              if (jj >= 0) val += G[static_cast<int64_t>(m) * ldG + jj];
-            }
-          }
-          out[e] = to_elem<T>(val);
-        }
-        T* dst = dZ + static_cast<int64_t>(m) * chunk + vl0 + rl0;
-        if constexpr (sizeof(T) == 2) {
-          u32x2 w = {static_cast<uint32_t>(out[0]) | (static_cast<uint32_t>(out[1]) << 16),
-                     static_cast<uint32_t>(out[2]) | (static_cast<uint32_t>(out[3]) << 16)};
-          *reinterpret_cast<u32x2*>(dst) = w;
-        } else {
-          *reinterpret_cast<float4*>(dst) = make_float4(out[0], out[1], out[2], out[3]);
-        }
-      }
-  }
-}
-
-// part[s][M][D] += dZ[:, slice s] . W[c0 + slice s, :]; the first chunk (c0 == 0) writes
-// every slice instead (zeros when its k range is empty), so the partials need no clearing.
-template <typename T>
-__global__ void __launch_bounds__(256, 2)
-dh_gemm_kernel(const T* __restrict__ dZ, int M, int chunk, const T* __restrict__ W, int D, int c0, int cw,
-               int slice, float* __restrict__ part) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kBwdB, kBwdB, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  const int nMt = (M + kBwdB - 1) / kBwdB;
-  const int nDt = (D + kBwdB - 1) / kBwdB;
-  const int work = blockIdx.x;
-  const int mt = work % nMt;
-  const int dt = (work / nMt) % nDt;
-  const int s = work / (nMt * nDt);
-  const int m0 = mt * kBwdB, d0 = dt * kBwdB;
-  const int kb = s * slice;
-  const int ke = min(cw, kb + slice);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  Operand<T> A{dZ, chunk, M, cw, nullptr, nullptr};
-  Operand<T> B{W + static_cast<int64_t>(c0) * D, D, D, cw, nullptr, nullptr};
-  f32x16 acc[FR][FC];
-  tile_gemm<T, kBwdB, kBwdB, BK, Lay::KMajor, Lay::RowMajorT>(A, B, m0, d0, kb, ke, lds, acc);
-  const bool first = c0 == 0;
-  if (kb >= ke && !first) return;
-  float* dst = part + static_cast<int64_t>(s) * M * D;
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FC; ++j) {
-      const int d = d0 + acc_col<kBwdB>(wave, lane, j);
-      if (d >= D) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + acc_row<kBwdB>(wave, lane, i, r);
-        if (m < M) {
-          float* p = dst + static_cast<int64_t>(m) * D + d;
-          *p = first ? acc[i][j][r] : *p + acc[i][j][r];
-        }
-      }
-    }
-}
-
-// dW[c0 + v][:] = sum_m dZ[m][v] Ht[:, m]   (Ht: head input transposed, excluded frames zero)
-template <typename T>
-__global__ void __launch_bounds__(256, 2)
-dw_gemm_kernel(const T* __restrict__ dZ, int M, int chunk, const T* __restrict__ Ht, int Mp, int D, int c0, int cw,
-               float* __restrict__ dW) {
-  constexpr int BK = Cfg<T>::BK;
-  using Shape = TileShape<T, kBwdB, kBwdB, BK>;
-  constexpr int FR = Shape::FR, FC = Shape::FC;
-  __shared__ __attribute__((aligned(16))) T lds[Shape::kLdsElems];
-  const int nVt = (cw + kBwdB - 1) / kBwdB;
-  const int work = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int vt = work % nVt;
-  const int dt = work / nVt;
-  const int v0 = vt * kBwdB, d0 = dt * kBwdB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  Operand<T> A{dZ, chunk, cw, M, nullptr, nullptr};
-  Operand<T> B{Ht, Mp, D, M, nullptr, nullptr};
-  f32x16 acc[FR][FC];
-  tile_gemm<T, kBwdB, kBwdB, BK, Lay::RowMajorT, Lay::KMajor>(A, B, v0, d0, 0, M, lds, acc);
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FC; ++j) {
-      const int d = d0 + acc_col<kBwdB>(wave, lane, j);
-      if (d >= D) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int v = v0 + acc_row<kBwdB>(wave, lane, i, r);
-        if (v < cw) dW[static_cast<int64_t>(c0 + v) * D + d] = acc[i][j][r];
-      }
-    }
-}
-
-// Ht[d][m] = H[m][d] for frames with g[m] != 0, else 0; m in [M, Mp) zero.
-template <typename T>
-__global__ void ht_build_kernel(const T* __restrict__ H, int M, int D, const float* __restrict__ g, T* __restrict__ Ht,
-                                int Mp) {
-  __shared__ T tile[64][65];
-  const int m0 = blockIdx.x * 64, d0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 256 threads: 64 x 4
-  for (int r = ty; r < 64; r += 4) {
-    const int m = m0 + r, d = d0 + tx;
-    T v = T(0);
-    if (m < M && d < D && g[m] != 0.f) v = H[static_cast<int64_t>(m) * D + d];
-    tile[r][tx] = v;
-  }
-  __syncthreads();
-  for (int r = ty; r < 64; r += 4) {
-    const int d = d0 + r, m = m0 + tx;
-    if (d < D && m < Mp) Ht[static_cast<int64_t>(d) * Mp + m] = tile[tx][r];
-  }
-}
-
-// dH = sum of the split-K partials (+ extra, the union-column part, when given), in order.
 // dH = sum of the split-K partials (+ extra, which may be dH itself: each element is read
 // before it is written by the same thread)
 __global__ void dh_reduce_kernel(const float* __restrict__ part, int splits, int64_t n, const float* extra,
@@ -702,6 +237,14 @@ __global__ void dh_reduce_kernel(const float* __restrict__ part, int splits, int
   for (int k = 0; k < splits; ++k) s += part[k * n + i];
   if (extra) s += extra[i];
   dH[i] = s;
+}
+
+hipError_t launch_dh_reduce(const float* part, int splits, int64_t n, const float* extra, float* dH,
+                            hipStream_t stream) {
+  Prof pr("dh_reduce", stream);
+  hipLaunchKernelGGL(dh_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream, part,
+                     splits, n, extra, dH);
+  return hipGetLastError();
 }
 
 BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
@@ -738,106 +281,48 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
     cap = static_cast<int>(cmax);
   }
   const size_t es = (dtype == 1) ? 2 : 4;
-  const int tr = (dtype == 1) ? 256 : kBwdB;  // dH tile rows of the kernel used
-  const int tc = (dtype == 1) ? 256 : kBwdB;
-  const int tiles = ((M + tr - 1) / tr) * ((D + tc - 1) / tc);
-  // k-slices of the dH product (one workgroup per CU): when the tiles alone make less than
-  // two 256-workgroup waves, at most ~12,800 columns per slice (a launch of a few long
-  // workgroups is exposed to any CU that is held up); then the fewest slices whose launch
-  // fills its waves to at least 90%, else the fullest; at most 8
-  const int maxs = p.chunk / 256 < 8 ? (p.chunk / 256 > 0 ? p.chunk / 256 : 1) : 8;
-  int mins = (tiles < 512) ? (p.chunk + 12799) / 12800 : 1;
-  if (mins > maxs) mins = maxs;
-  if (mins < 1) mins = 1;
-  int splits = mins;
-  double best = -1.0;
-  for (int sp = mins; sp <= maxs; ++sp) {
-    const int wgs = tiles * sp;
-    const double fill = static_cast<double>(wgs) / (256.0 * ((wgs + 255) / 256));
-    if (fill > best + 1e-9) {
-      best = fill;
-      splits = sp;
+  p.wsplits = 1;
+  if (dtype == 1) {
+    const int tiles = ((M + 255) / 256) * ((D + 255) / 256);
+    // k-slices of the dH product (one workgroup per CU): when the tiles alone make less than
+    // two 256-workgroup waves, at most ~12,800 columns per slice (a launch of a few long
+    // workgroups is exposed to any CU that is held up); then the fewest slices whose launch
+    // fills its waves to at least 90%, else the fullest; at most 8
+    const int maxs = p.chunk / 256 < 8 ? (p.chunk / 256 > 0 ? p.chunk / 256 : 1) : 8;
+    int mins = (tiles < 512) ? (p.chunk + 12799) / 12800 : 1;
+    if (mins > maxs) mins = maxs;
+    if (mins < 1) mins = 1;
+    int splits = mins;
+    double best = -1.0;
+    for (int sp = mins; sp <= maxs; ++sp) {
+      const int wgs = tiles * sp;
+      const double fill = static_cast<double>(wgs) / (256.0 * ((wgs + 255) / 256));
+      if (fill > best + 1e-9) {
+        best = fill;
+        splits = sp;
+      }
+      if (fill >= 0.9) break;
     }
-    if (fill >= 0.9) break;
+    p.splits = splits;
+  } else {
+    plan_products_f32(M, D, p.chunk < V ? p.chunk : V, &p.splits, &p.wsplits);
   }
-  p.splits = splits;
   p.Mp = ((M + 63) / 64) * 64;
   p.dz_bytes = align_up(static_cast<size_t>(M) * cap * es, 256);
   p.ht_bytes = align_up(static_cast<size_t>(D) * p.Mp * es, 256);  // >= M x D (bf16 masked copy of H)
-  // bf16 with a single slice: the dH product accumulates in the caller's dH (no partial buffer)
-  p.part_bytes = (dtype == 1 && splits == 1) ? 0 : align_up(static_cast<size_t>(splits) * M * D * sizeof(float), 256);
+  // a single slice: the dH product accumulates in the caller's dH (no partial buffer)
+  p.part_bytes = p.splits == 1 ? 0 : align_up(static_cast<size_t>(p.splits) * M * D * sizeof(float), 256);
   p.lam2_bytes = align_up(static_cast<size_t>(M) * sizeof(float2), 256);
-  // bf16: per 128-frame tile column sums of dZ for db
-  p.dbpart_bytes = (dtype == 1) ? align_up(static_cast<size_t>((M + 127) / 128) * cap * sizeof(float), 256) : 0;
+  // column sums of dZ for db, per 128-frame tile (bf16) or frame slice (fp32)
+  p.dbpart_bytes =
+      align_up((dtype == 1 ? static_cast<size_t>((M + 127) / 128) * cap : static_cast<size_t>(kDbSlicesF32) * p.chunk) *
+                   sizeof(float), 256);
   // narrow bf16 heads: the dense recompute reads its frames from Hs transposed (whole k-lines)
   p.hst_bytes = (dtype == 1 && D < kWideD && D % 128 == 0) ? align_up(static_cast<size_t>(D) * p.Mp * 2, 256) : 0;
-  p.total = p.dz_bytes + p.ht_bytes + p.part_bytes + p.lam2_bytes + p.dbpart_bytes + p.hst_bytes;
+  // fp32: dW's partial sums over the frame slices past the first
+  p.wpart_bytes = align_up(static_cast<size_t>(p.wsplits - 1) * p.chunk * D * sizeof(float), 256);
+  p.total = p.dz_bytes + p.ht_bytes + p.part_bytes + p.lam2_bytes + p.dbpart_bytes + p.hst_bytes + p.wpart_bytes;
   return p;
-}
-
-// db[v] = sum over frames of dZ[m][v] for the chunk's columns v < cw.
-template <typename T>
-__global__ void dz_colsum_kernel(const T* __restrict__ dZ, int M, int chunk, int cw, float* __restrict__ db) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= cw) return;
-  float s = 0.f;
-  for (int m = 0; m < M; ++m) s += static_cast<float>(dZ[static_cast<int64_t>(m) * chunk + v]);
-  db[v] = s;
-}
-
-template <typename T>
-static hipError_t head_bwd_t(const T* H, int M, int D, const T* W, const float* bias, int V, const float2* lam2,
-                             const float* G, int ldG, const float* g, const int32_t* remap, float* dH, float* dW,
-                             float* db, char* scratch, const BwdPlan& plan, hipStream_t stream) {
-  T* dZ = reinterpret_cast<T*>(scratch);
-  T* Ht = reinterpret_cast<T*>(scratch + plan.dz_bytes);
-  float* part = reinterpret_cast<float*>(scratch + plan.dz_bytes + plan.ht_bytes);
-  const int chunk = plan.chunk;
-  const int nMt = (M + kFwdBC - 1) / kFwdBC;
-  if (dW) {
-    Prof pr("ht_build", stream);
-    hipLaunchKernelGGL(ht_build_kernel<T>, dim3(plan.Mp / 64, (D + 63) / 64), dim3(256), 0, stream, H, M, D, g,
-                       Ht, plan.Mp);
-  }
-  int slice = ((chunk / plan.splits + 63) / 64) * 64;
-  // split-K slices any chunk fills: the first chunk (the widest) writes them all
-  const int nslices = (min(chunk, V) + slice - 1) / slice;
-  for (int c0 = 0; c0 < V; c0 += chunk) {
-    const int cw = min(chunk, V - c0);
-    const int nVt = (cw + kFwdBR - 1) / kFwdBR;
-    {
-      Prof pr("recompute_dz", stream);
-      hipLaunchKernelGGL(recompute_dz_kernel<T>, dim3(nMt * nVt), dim3(256), 0, stream, H, M, D, W, bias, c0, cw,
-                         lam2, G, ldG, g, remap, dZ, chunk);
-    }
-    if (db) {
-      Prof pr("db_colsum", stream);
-      hipLaunchKernelGGL(dz_colsum_kernel<T>, dim3((cw + 255) / 256), dim3(256), 0, stream, dZ, M, chunk, cw,
-                         db + c0);
-    }
-    if (dH) {
-      const int tiles = ((M + kBwdB - 1) / kBwdB) * ((D + kBwdB - 1) / kBwdB);
-      const int ns = (cw + slice - 1) / slice;
-      Prof pr("dh_gemm", stream);
-      hipLaunchKernelGGL(dh_gemm_kernel<T>, dim3(tiles * ns), dim3(256), 0, stream, dZ, M, chunk, W, D, c0, cw,
-                         slice, part);
-    }
-    if (dW) {
-      const int grid = ((cw + kBwdB - 1) / kBwdB) * ((D + kBwdB - 1) / kBwdB);
-      Prof pr("dw_gemm", stream);
-      hipLaunchKernelGGL(dw_gemm_kernel<T>, dim3(grid), dim3(256), 0, stream, dZ, M, chunk, Ht, plan.Mp, D, c0, cw,
-                         dW);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (dH) {
-    const int64_t n = static_cast<int64_t>(M) * D;
-    Prof pr("dh_reduce", stream);
-    hipLaunchKernelGGL(dh_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream, part,
-                       nslices, n, nullptr, dH);
-  }
-  return hipGetLastError();
 }
 
 uint16_t* bwd_hs(void* scratch, const BwdPlan& plan) {
@@ -915,10 +400,7 @@ static hipError_t head_bwd_bf16(const uint16_t* H, int M, int D, const uint16_t*
       if (in_place) {
         if (side->after_dh.fn && (e = side->after_dh.fn(side->after_dh.ctx)) != hipSuccess) return e;
       } else {
-        Prof pr("dh_reduce", side->stream);
-        hipLaunchKernelGGL(dh_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, side->stream,
-                           part, nslices, n, dH_extra, dH);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_dh_reduce(part, nslices, n, dH_extra, dH, side->stream)) != hipSuccess) return e;
       }
       if (dW) {
         // the union columns' dW_u rides in this launch's last round once their bf16 G is written
@@ -953,9 +435,7 @@ static hipError_t head_bwd_bf16(const uint16_t* H, int M, int D, const uint16_t*
     if ((e = hipEventRecord(side->reduced, side->stream)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(stream, side->reduced, 0)) != hipSuccess) return e;
   } else if (dH && !in_place) {
-    Prof pr("dh_reduce", stream);
-    hipLaunchKernelGGL(dh_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream, part,
-                       nslices, n, dH_extra, dH);
+    return launch_dh_reduce(part, nslices, n, dH_extra, dH, stream);
   }
   return hipGetLastError();
 }
@@ -976,7 +456,7 @@ hipError_t launch_head_bwd(int dtype, const void* H, int M, int D, const void* W
   if (dtype == 1)
     return head_bwd_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, V, lam2, G, ldG,
                          g, remap, S, ldS, dH, dW, db, sc, plan, stream, side);
-  return head_bwd_t<float>(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, lam2, G, ldG, g,
+  return head_bwd_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, lam2, G, ldG, g,
                            remap, dH, dW, db, sc, plan, stream);
 }
 

@@ -38,7 +38,6 @@ hipError_t launch_union_remap(const int32_t* targets, int32_t total, int32_t bla
                               void* scratch, hipStream_t stream);
 
 // ---- normaliser and selected log-probabilities ------------------------------------------
-int lse_partitions(int M, int V);
 // Heads with D >= kWideD run their bf16 products on 8-wave 256 x 256 tiles.
 constexpr int kWideD = 2048;
 // Most vocabulary partitions of a normaliser or argmax launch (partial buffer rows): 256,
@@ -88,9 +87,10 @@ struct DwExtra {
 struct BwdPlan {
   int chunk;       // vocabulary columns per step
   int splits;      // k-slices of the dH product per chunk
+  int wsplits;     // frame slices of the dW product per chunk (fp32; bf16: 1)
   int Mp;          // padded frame count (pitch of the transposed head input)
   // hst_bytes: Hs transposed, [D][Mp] bf16, read by the dense recompute of narrow bf16 heads
-  size_t dz_bytes, ht_bytes, part_bytes, lam2_bytes, dbpart_bytes, hst_bytes, total;
+  size_t dz_bytes, ht_bytes, part_bytes, lam2_bytes, dbpart_bytes, hst_bytes, wpart_bytes, total;
 };
 BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk);
 // Column multiple of the default chunk of narrow bf16 heads: the normaliser's partition width
@@ -141,6 +141,23 @@ hipError_t launch_head_bwd(int dtype, const void* H, int M, int D, const void* W
                            const float* S, int ldS, float* dH, float* dW, float* db, void* scratch,
                            const BwdPlan& plan, hipStream_t stream, const BwdSide* side = nullptr);
 hipError_t launch_lam2(const double* lam, int M, float2* lam2, hipStream_t stream);
+
+// dH = sum of the `splits` partial sums of n elements (+ extra, which may be dH), in order.
+hipError_t launch_dh_reduce(const float* part, int splits, int64_t n, const float* extra, float* dH,
+                            hipStream_t stream);
+
+// ---- fp32 kernels on the split engine (head_gemm_f32.hip) --------------------------------
+constexpr int kDbSlicesF32 = 64;  // frame slices of db's column sums
+void plan_products_f32(int M, int D, int cols, int* splits, int* wsplits);
+hipError_t launch_lse_partial_f32(const float* H, int M, int D, const float* W, const float* bias, int V,
+                                  float2* partials, int* P_out, hipStream_t stream);
+hipError_t launch_amax_partial_f32(const float* H, int M, int D, const float* W, const float* bias, int V,
+                                   float2* partials, int* P_out, hipStream_t stream);
+hipError_t launch_gather_s_f32(const float* H, int M, int D, const float* W, const float* bias, const int32_t* u_ids,
+                               const int32_t* K, int K_max, const double* lam, float* S, int ldS, hipStream_t stream);
+hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const float* bias, int V, const float2* lam2,
+                        const float* G, int ldG, const float* g, const int32_t* remap, float* dH, float* dW, float* db,
+                        char* scratch, const BwdPlan& plan, hipStream_t stream);
 
 // ---- bf16 kernels on the direct-to-LDS engine (head_gemm_bf16.hip) ---------------------
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,

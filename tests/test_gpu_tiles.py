@@ -1,0 +1,63 @@
+"""GPU kernels at the sizes where their tiling can go wrong, against the fp64 oracle: edges of
+tiles and of slices, remainders, the smallest and the largest of a rule's range."""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_33645_amd import workloads
+from tests.gpu_util import cosine, loss_rel, rel_err, run_gpu, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _fixed(dtype, T, D, V, seed, blank=0, u_frac=0.2, w_std=None):
+    T = np.asarray(T, np.int32)
+    return workloads.synthesize(name="tiles", dtype=dtype, T=T, U=(T * u_frac).astype(np.int32), D=D, V=V,
+                                rng=np.random.default_rng(seed), token_law="uniform", blank=blank, w_std=w_std)
+
+
+# ---- fp32 products on the split engine ----------------------------------------------------------
+
+@pytest.mark.parametrize("T,D,V,chunk", [
+    ([1], 8, 2, 0),                  # one frame, half a k-tile, one ragged tile of two classes
+    ([255], 16, 255, 0),             # one k-tile; a frame and a class short of whole tiles
+    ([256], 24, 256, 0),             # whole tiles, one k-tile and a half
+    ([200, 57], 264, 257, 256),      # one past whole tiles in frames, width and classes; two chunks
+    ([40] * 30, 520, 1025, 512),     # a narrower last chunk (one class) on the first chunk's dH slices
+    ([100] * 30, 64, 700, 256),      # the frames of dW in slices
+])
+def test_f32_tile_edges(T, D, V, chunk):
+    wl = _fixed("f32", T, D, V, 5 + D + V, blank=V - 1)
+    say(f"f32 tile edges M={wl.M} D={D} V={V} chunk={chunk}")
+    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam)
+    res = run_gpu(wl, chunk=chunk)
+    np.testing.assert_array_equal(res["status"], ref["status"])
+    assert loss_rel(res["loss"], ref["loss"]) <= 1e-5
+    # every product is rounded to about 2^-24 and summed in fp32: far inside the stated 1e-4
+    assert rel_err(res["dH"], ref["dH"]) <= 1e-5
+    assert rel_err(res["dW"], ref["dW"]) <= 1e-5
+
+
+@pytest.mark.parametrize("e", [100, -90])
+def test_f32_split_keeps_the_range(e):
+    """The three bf16 parts of a value keep fp32's exponent range: H 2^e and W 2^-e give the very
+    same logits as H and W (powers of two move through the splits and the sums exactly; every
+    part stays a normal number), and a value too large to round to bf16 stays finite."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("f32", [70], 72, 300, 3)
+    H, W, _ = to_dev(wl)
+    a = prunedctc.lse_select(H, W)["lam"]
+    b = prunedctc.lse_select(H * 2.0 ** e, W * 2.0 ** -e)["lam"]
+    assert torch.equal(a, b)
+    H[:, 0] = 3.4e38  # rounds to infinity in bf16
+    W[:, 0] = 1e-38
+    c = prunedctc.lse_select(H, W)["lam"].cpu().numpy()
+    ref = oracle.log_normalizer(H.cpu().numpy().astype(np.float64), W.cpu().numpy().astype(np.float64))
+    # 1e-38 splits into parts down to 2^-142, below bf16's smallest: its product is good to 2^-8
+    assert np.abs(c - ref).max() <= 3.4 * 2.0 ** -8
