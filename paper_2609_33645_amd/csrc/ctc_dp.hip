@@ -448,15 +448,24 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
 
 // ---------------------------------------------------------------------------------------
 
+// The beams of one mask launch and where their masks go.
+constexpr int kMaskBeams = 9;
+struct MaskBeams {
+  float beam[kMaskBeams];
+  uint8_t* mask[kMaskBeams];
+};
+
 // One workgroup per frame.  Margin of each arc into (t, s):
 //   alpha^(t-1, s') + E_t(s) + beta^(t, s) - (best - beam - slack) >= 0 keeps it.
+// The arcs' scores are read once for all beams of the launch.
+template <int NB>
 __global__ void dp_mask_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__ toff,
                                const int32_t* __restrict__ yoff, const int64_t* __restrict__ soff,
                                const int32_t* __restrict__ y_rel, const int32_t* __restrict__ frame_utt,
                                const int32_t* __restrict__ status, const float* __restrict__ va,
                                const float* __restrict__ vb, const double* __restrict__ sva,
-                               const double* __restrict__ svb, const double* __restrict__ vbest, float beam,
-                               float slack, uint8_t* __restrict__ mask) {
+                               const double* __restrict__ svb, const double* __restrict__ vbest, int nb,
+                               MaskBeams beams, float slack) {
   const int m = blockIdx.x;
   const int n = frame_utt[m];
   if (status[n] != 0) return;
@@ -466,32 +475,35 @@ __global__ void dp_mask_kernel(const float* __restrict__ S, int ldS, const int32
   const int Sp = 2 * U + 1;
   const int64_t base = soff[n];
   const int* y = y_rel + y0;
-  const double thr = vbest[n] - static_cast<double>(beam) - static_cast<double>(slack);
+  const double best = vbest[n], sv_b = svb[m];
+  const double sv_prev = (t > 0) ? sva[m - 1] : 0.0, sv_last = (t == T - 1) ? sva[m] : 0.0;
   const float* row = S + static_cast<int64_t>(m) * ldS;
-  // frame offsets: alpha^ at t-1 and beta^ at t
-  const float off_arc = (t > 0) ? static_cast<float>(sva[m - 1] + svb[m] - thr) : 0.f;
-  const float off_start = static_cast<float>(svb[m] - thr);
-  const float off_final = static_cast<float>(sva[m] - thr);
   for (int s = threadIdx.x; s < Sp; s += blockDim.x) {
     const int c = (s & 1) ? y[(s - 1) >> 1] : 0;
     const float e = row[c];
     const float bt = vb[base + static_cast<int64_t>(t) * Sp + s];
-    uint8_t bits = 0;
-    if (t == 0) {
-      if (s < 2 && e + bt + off_start >= 0.f) bits |= 1;
-    } else {
-      const float* ap = va + base + static_cast<int64_t>(t - 1) * Sp;
-      const float through = e + bt + off_arc;
-      if (ap[s] + through >= 0.f) bits |= 1;
-      if (s >= 1 && ap[s - 1] + through >= 0.f) bits |= 2;
-      const bool skip = (s & 1) && s >= 3 && y[(s - 1) >> 1] != y[(s - 3) >> 1];
-      if (skip && ap[s - 2] + through >= 0.f) bits |= 4;
+    const bool skip = (s & 1) && s >= 3 && y[(s - 1) >> 1] != y[(s - 3) >> 1];
+    const bool last = t == T - 1 && s >= Sp - 2;
+    const float at = last ? va[base + static_cast<int64_t>(t) * Sp + s] : 0.f;
+    const float* ap = va + base + static_cast<int64_t>(t > 0 ? t - 1 : 0) * Sp;
+    const float a0 = ap[s], a1 = (s >= 1) ? ap[s - 1] : 0.f, a2 = skip ? ap[s - 2] : 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (NB > 1 && b >= nb) break;
+      const double thr = best - static_cast<double>(beams.beam[b]) - static_cast<double>(slack);
+      uint8_t bits = 0;
+      if (t == 0) {
+        if (s < 2 && e + bt + static_cast<float>(sv_b - thr) >= 0.f) bits |= 1;
+      } else {
+        // frame offsets: alpha^ at t-1 and beta^ at t
+        const float through = e + bt + static_cast<float>(sv_prev + sv_b - thr);
+        if (a0 + through >= 0.f) bits |= 1;
+        if (s >= 1 && a1 + through >= 0.f) bits |= 2;
+        if (skip && a2 + through >= 0.f) bits |= 4;
+      }
+      if (last && at + static_cast<float>(sv_last - thr) >= 0.f) bits |= 8;
+      beams.mask[b][base + static_cast<int64_t>(t) * Sp + s] = bits;
     }
-    if (t == T - 1 && s >= Sp - 2) {
-      const float at = va[base + static_cast<int64_t>(t) * Sp + s];
-      if (at + off_final >= 0.f) bits |= 8;
-    }
-    mask[base + static_cast<int64_t>(t) * Sp + s] = bits;
   }
 }
 
@@ -735,8 +747,11 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
       }
       if (plan.M > 0) {
         Prof pr("dp_mask", stream);
-        hipLaunchKernelGGL(dp_mask_kernel, dim3(plan.M), dim3(256), 0, stream, S, ldS, toff, yoff, soff, y_rel,
-                           frame_utt, status, tva, tvb, sva, svb, vbest, beam, kKeepSlack, mask);
+        MaskBeams one{};
+        one.beam[0] = beam;
+        one.mask[0] = mask;
+        hipLaunchKernelGGL(dp_mask_kernel<1>, dim3(plan.M), dim3(256), 0, stream, S, ldS, toff, yoff, soff, y_rel,
+                           frame_utt, status, tva, tvb, sva, svb, vbest, 1, one, kKeepSlack);
       }
     }
   }
@@ -766,9 +781,12 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
 // ---------------------------------------------------------------------------------------
 // Discarded posterior mass (App. B.3): delta_n = 1 - (sum over retained alignments) /
 // (sum over all valid alignments), both of prod_t p_{pi_t}(t) on the same scores.  One
-// wavefront per utterance runs the two forward recursions in lockstep in linear space and
-// double precision, with one shared scale per frame (the full recursion's maximum), so
-// the per-frame scaling cancels in the ratio.  The emission factor exp(S - m_t) (m_t the
+// wavefront per utterance and beam runs the two forward recursions in lockstep in linear space
+// and double precision, with one shared scale per frame (a power of two near the full
+// recursion's maximum), so the per-frame scaling is exact and cancels in the ratio.  Bound by
+// the latency of its T sequential frames, so all beams run at once (the full recursion again
+// for each of them): nine beams, 16 utterances of up to 375 frames, 9 x 180 us one after
+// another, 104 us together.  The emission factor exp(S - m_t) (m_t the
 // frame's largest selected score) is formed once in float and used by both recursions.
 // Utterances that are not alignable get NaN.
 // ---------------------------------------------------------------------------------------
@@ -781,10 +799,19 @@ __device__ __forceinline__ double lane_up_d(double x) {
   return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
 }
 
-__device__ __forceinline__ double wave_max_d(double x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-  return x;
+// Maximum over the wavefront of the high words of non-negative doubles (they order as the
+// doubles do, to 20 significand bits).
+template <int CTRL>
+__device__ __forceinline__ int dpp_max_step_i(int v) {
+  return max(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ int wave_max_i(int x) {
+  x = dpp_max_step_i<0xB1>(x);   // quad_perm [1,0,3,2]
+  x = dpp_max_step_i<0x4E>(x);   // quad_perm [2,3,0,1]
+  x = dpp_max_step_i<0x141>(x);  // row_half_mirror
+  x = dpp_max_step_i<0x140>(x);  // row_mirror
+  return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 __device__ __forceinline__ double wave_sum_d(double x) {
 #pragma unroll
@@ -797,9 +824,11 @@ __global__ void __launch_bounds__(64)
 dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__ toff,
                     const int32_t* __restrict__ yoff, const int64_t* __restrict__ soff,
                     const int32_t* __restrict__ y_rel, const int32_t* __restrict__ status,
-                    const uint8_t* __restrict__ mask, double* __restrict__ delta) {
+                    MaskBeams beams, double* __restrict__ delta_all) {
   const int n = blockIdx.x;
   const int lane = threadIdx.x;
+  const uint8_t* const mask = beams.mask[blockIdx.y];
+  double* const delta = delta_all + static_cast<int64_t>(blockIdx.y) * gridDim.x;
   if (status[n] != 0) {
     if (lane == 0) delta[n] = __longlong_as_double(0x7ff8000000000000LL);
     return;
@@ -847,14 +876,16 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
       pe[q] = (valid[q] && x > -INFINITY) ? ldexp(static_cast<double>(fast_exp2(x - fi)), static_cast<int>(fi)) : 0.0;
     }
   };
-  // any positive scale serves (both sums take the same one): an approximate reciprocal of
-  // the wave maximum
+  // any positive scale serves (both sums take the same one): the power of two that brings the
+  // wave's largest value to [1, 2) (its exponent kept within a normal number's), which is exact
+  // and needs only the high words, one register and four DPP steps instead of shuffled doubles
   auto rescale = [&](double (&nf)[Q], double (&np)[Q]) {
-    double c = 0.0;
+    int hi = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) c = fmax(c, nf[q]);
-    c = wave_max_d(c);
-    const double inv = (c > 0.0) ? __builtin_amdgcn_rcp(c) : 0.0;
+    for (int q = 0; q < Q; ++q) hi = max(hi, static_cast<int>(__double_as_longlong(nf[q]) >> 32));
+    hi = wave_max_i(hi);
+    const int ex = min(max(2046 - (hi >> 20), 1), 2046);
+    const double inv = __longlong_as_double(static_cast<long long>(ex) << 52);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       af[q] = nf[q] * inv;
@@ -927,13 +958,14 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
   if (lane == 0) delta[n] = (sf > 0.0) ? 1.0 - sp / sf : __longlong_as_double(0x7ff8000000000000LL);
 }
 
-static hipError_t launch_discarded(int Q, int N, hipStream_t stream, const float* S, int ldS, const int32_t* toff,
-                                   const int32_t* yoff, const int64_t* soff, const int32_t* y_rel,
-                                   const int32_t* status, const uint8_t* mask, double* delta) {
+static hipError_t launch_discarded(int Q, int N, int nb, hipStream_t stream, const float* S, int ldS,
+                                   const int32_t* toff, const int32_t* yoff, const int64_t* soff,
+                                   const int32_t* y_rel, const int32_t* status, const MaskBeams& beams,
+                                   double* delta) {
 #define PCTC_DISC(QQ)                                                                                             \
   case QQ:                                                                                                        \
-    hipLaunchKernelGGL((dp_discarded_kernel<QQ>), dim3(N), dim3(64), 0, stream, S, ldS, toff, yoff, soff, y_rel, \
-                       status, mask, delta);                                                                      \
+    hipLaunchKernelGGL((dp_discarded_kernel<QQ>), dim3(N, nb), dim3(64), 0, stream, S, ldS, toff, yoff, soff,      \
+                       y_rel, status, beams, delta);                                                              \
     break;
   switch (Q) {
     PCTC_DISC(1)
@@ -975,7 +1007,15 @@ hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, co
   double* sva = reinterpret_cast<double*>(sc + plan.off_sc_va);
   double* svb = reinterpret_cast<double*>(sc + plan.off_sc_vb);
   double* vbest = reinterpret_cast<double*>(sc + plan.off_vbest);
-  uint8_t* mask = reinterpret_cast<uint8_t*>(sc + plan.off_mask);
+  // arc masks of kMaskBeams beams: the plan's own, and four each in the two log-sum tables, which
+  // this path does not use (a float per cell)
+  uint8_t* mask_of[kMaskBeams];
+  mask_of[0] = reinterpret_cast<uint8_t*>(sc + plan.off_mask);
+  for (int b = 0; b < 4; ++b) {
+    mask_of[1 + b] = reinterpret_cast<uint8_t*>(sc + plan.off_tab_fa) + b * plan.lattice;
+    mask_of[5 + b] = reinterpret_cast<uint8_t*>(sc + plan.off_tab_fb) + b * plan.lattice;
+  }
+  static_assert(kMaskBeams == 9 && sizeof(float) == 4, "one mask region and two tables of four");
   {
     Prof pr("dp_prep", stream);
     hipLaunchKernelGGL(dp_prep_kernel, dim3(N), dim3(256), 0, stream, toff, yoff, y_rel, K_max, status, dnext, dfirst,
@@ -983,23 +1023,33 @@ hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, co
   }
   const int Q = pick_q(plan.Smax);
   if (Q < 0) return hipErrorInvalidValue;
-  for (int b = 0; b < nbeams; ++b) {
-    hipError_t e;
-    {
-      Prof pr("dp_viterbi", stream);
-      e = launch_pass<true>(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva, svb,
-                            vbest, loss_n, dummy);
-      if (e != hipSuccess) return e;
+  hipError_t e;
+  {  // the best alignments, the same for every beam
+    Prof pr("dp_viterbi", stream);
+    e = launch_pass<true>(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva, svb, vbest,
+                          loss_n, dummy);
+    if (e != hipSuccess) return e;
+  }
+  for (int b0 = 0; b0 < nbeams; b0 += kMaskBeams) {
+    const int nb = nbeams - b0 < kMaskBeams ? nbeams - b0 : kMaskBeams;
+    MaskBeams mb{};
+    for (int b = 0; b < nb; ++b) {
+      mb.beam[b] = beams[b0 + b];
+      mb.mask[b] = mask_of[b];
     }
     if (plan.M > 0) {
       Prof pr("dp_mask", stream);
-      hipLaunchKernelGGL(dp_mask_kernel, dim3(plan.M), dim3(256), 0, stream, S, ldS, toff, yoff, soff, y_rel, frame_utt,
-                         status, tva, tvb, sva, svb, vbest, beams[b], kKeepSlack, mask);
+      if (nb == 1)
+        hipLaunchKernelGGL(dp_mask_kernel<1>, dim3(plan.M), dim3(256), 0, stream, S, ldS, toff, yoff, soff, y_rel,
+                           frame_utt, status, tva, tvb, sva, svb, vbest, nb, mb, kKeepSlack);
+      else
+        hipLaunchKernelGGL(dp_mask_kernel<kMaskBeams>, dim3(plan.M), dim3(256), 0, stream, S, ldS, toff, yoff, soff,
+                           y_rel, frame_utt, status, tva, tvb, sva, svb, vbest, nb, mb, kKeepSlack);
     }
     {
       Prof pr("dp_discarded", stream);
-      e = launch_discarded(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, mask,
-                           delta + static_cast<int64_t>(b) * N);
+      e = launch_discarded(Q, N, nb, stream, S, ldS, toff, yoff, soff, y_rel, status, mb,
+                           delta + static_cast<int64_t>(b0) * N);
       if (e != hipSuccess) return e;
     }
   }

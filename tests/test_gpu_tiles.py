@@ -61,3 +61,24 @@ def test_f32_split_keeps_the_range(e):
     ref = oracle.log_normalizer(H.cpu().numpy().astype(np.float64), W.cpu().numpy().astype(np.float64))
     # 1e-38 splits into parts down to 2^-142, below bf16's smallest: its product is good to 2^-8
     assert np.abs(c - ref).max() <= 3.4 * 2.0 ** -8
+
+
+# ---- discarded mass of several beams in one launch ----------------------------------------------
+
+@pytest.mark.parametrize("nbeams", [1, 2, 9, 10, 20])
+def test_discarded_mass_beam_groups(nbeams):
+    """Nine beams share a launch: around that number, each beam's row against the oracle."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    rng = np.random.default_rng(nbeams)
+    T, U = np.array([30, 1, 90, 17], np.int32), np.array([6, 0, 40, 16], np.int32)
+    K = 23
+    y = rng.integers(1, K, size=int(U.sum())).astype(np.int32)
+    S = workloads.random_scores(nbeams, int(T.sum()), K, integer=True)  # margins are integers ..
+    beams = [0.5 + 3 * b for b in range(nbeams)]                       # .. and thresholds between them
+    got = prunedctc.discarded_mass(torch.from_numpy(S).cuda(), torch.from_numpy(y).cuda(), T, U, beams).cpu().numpy()
+    ref = oracle.discarded_mass(S.astype(np.float64), y, T, U, beams)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    # each sum is of products of T float exponentials (2^-24 each), both recursions on the same ones
+    assert np.nanmax(np.abs(got - ref)) <= 90 * 2.0 ** -23
