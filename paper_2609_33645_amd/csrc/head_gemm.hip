@@ -268,12 +268,13 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
     size_t c = ((v + n - 1) / n + 255) / 256 * 256;
     if (c > cmax) c = cmax;
     if (dtype == 1 && D < kWideD) {
-      // narrow bf16 heads: whole normaliser partitions (kEAlign columns), so that the first
-      // chunk's dZ rows can come from the normaliser (lse_partial_e_bf16)
-      size_t n2 = n, c2 = ((v + n2 - 1) / n2 + kEAlign - 1) / kEAlign * kEAlign;
-      while (c2 > cmax && c2 > static_cast<size_t>(kEAlign)) {
+      // narrow bf16 heads: whole normaliser partitions, so that the first chunk's dZ rows can
+      // come from the normaliser (lse_partial_e_bf16)
+      const size_t al = static_cast<size_t>(lse_part_columns_bf16(M, D, V));
+      size_t n2 = n, c2 = ((v + n2 - 1) / n2 + al - 1) / al * al;
+      while (c2 > cmax && c2 > al) {
         ++n2;
-        c2 = ((v + n2 - 1) / n2 + kEAlign - 1) / kEAlign * kEAlign;
+        c2 = ((v + n2 - 1) / n2 + al - 1) / al * al;
       }
       if (c2 <= cmax) c = c2;
     }
@@ -302,6 +303,23 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
         splits = sp;
       }
       if (fill >= 0.9) break;
+    }
+    if (tiles * maxs < 256 && p.chunk > 256 * maxs) {
+      // few frames: eight slices leave most of the chip idle (331 frames, D = 512, chunks of
+      // 60,000 columns: 16 or 32 workgroups, 160 us a launch).  The count whose launch is
+      // shortest by 0.7 us a 32-deep k-tile and 4 us a workgroup, with every slice's partial sums
+      // read and written at 3 TB/s; at most 32 slices and 32 MiB of them (there 32: 60 us)
+      double best_t = -1;
+      for (int sp = maxs; sp <= 32 && sp * 256 <= p.chunk; ++sp) {
+        const double bytes = static_cast<double>(sp) * M * D * sizeof(float);
+        if (sp > maxs && bytes > 32.0 * 1024 * 1024) break;
+        const int wgs = tiles * sp, len = ((p.chunk / sp + 63) / 64 * 64 + 31) / 32;
+        const double t = ((wgs + 255) / 256) * (len * 0.7 + 4) + 2 * bytes / 3.0e6;
+        if (best_t < 0 || t < best_t) {
+          best_t = t;
+          splits = sp;
+        }
+      }
     }
     p.splits = splits;
   } else {

@@ -93,9 +93,8 @@ struct BwdPlan {
   size_t dz_bytes, ht_bytes, part_bytes, lam2_bytes, dbpart_bytes, hst_bytes, wpart_bytes, total;
 };
 BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk);
-// Column multiple of the default chunk of narrow bf16 heads: the normaliser's partition width
-// (eight 256-row tiles; any V up to PCTC_MAX_VOCAB keeps it within 256 partitions).
-constexpr int kEAlign = 2048;
+// Columns of a normaliser partition (bf16): the default chunk of narrow heads is a multiple.
+int lse_part_columns_bf16(int M, int D, int V);
 // The bf16 fused schedule's side of the recomputed backward.  With a second stream: work i
 // (i < nwork) is enqueued on that stream after chunk i + 1 of the dense part (the caller's
 // stream records gate[i], the second stream waits for it, then work[i].fn(work[i].ctx)
