@@ -9,7 +9,7 @@
 // Kernels:
 //   dp_prep      per utterance: alignability T >= U + r (App. B.1), duplicate-label links,
 //                frame -> utterance map.
-//   dp_pass      one wavefront per (utterance, direction); lane l holds states
+//   dp_pass      one or four wavefronts per (utterance, direction); lane l of them holds states
 //                [lQ, lQ+Q).  Viterbi (max-plus, float) or total score (log-sum-exp,
 //                accumulated in double), renormalised every frame by the wave maximum
 //                with the running offsets kept in double.
@@ -26,14 +26,15 @@
 namespace pctc {
 
 constexpr float kNeg = -1.0e30f;  // "impossible" score; absorbs finite additions
-constexpr int kMaxQ = 32;         // most states per lane of a lattice pass (2U+1 <= 64 kMaxQ)
-static_assert(2 * PCTC_MAX_TARGET + 1 <= 64 * kMaxQ, "the longest target fits a lattice pass");
+constexpr int kMaxQ = 8;          // most states per lane of a lattice pass
+constexpr int kMaxStates = 256 * kMaxQ;
+static_assert(2 * PCTC_MAX_TARGET + 1 <= kMaxStates, "the longest target fits a lattice pass");
 // arc flags of a pass without a mask: every arc kept
 constexpr int kAllArcs = 0x0f;
 // bytes the mask region extends past its last cell: a pass reads each lane's flags as whole
-// aligned words, up to (kMaxQ + 3) / 4 + 1 words from the lane's first cell
+// aligned words, up to (kMaxQ + 5) / 4 + 1 words from the lane's first cell
 constexpr int kMaskPad = 64;
-static_assert(4 * ((kMaxQ + 3) / 4 + 1) <= kMaskPad, "mask padding covers a lane's word reads");
+static_assert(4 * ((kMaxQ + 5) / 4 + 1) <= kMaskPad, "mask padding covers a lane's word reads");
 
 DpPlan plan_dp(int N, const int32_t* T, const int32_t* U, float beam) {
   DpPlan p{};
@@ -69,7 +70,7 @@ DpPlan plan_dp(int N, const int32_t* T, const int32_t* U, float beam) {
   p.off_tab_fb = take(L * sizeof(float));
   p.off_sc_fa = take(M * sizeof(double));
   p.off_sc_fb = take(M * sizeof(double));
-  p.off_dummy = take(static_cast<size_t>(2 * N) * 64 * kMaxQ * sizeof(float));
+  p.off_dummy = take(static_cast<size_t>(2 * N) * kMaxStates * sizeof(float));
   if (p.pruned) {
     p.off_tab_va = take(L * sizeof(float));
     p.off_tab_vb = take(L * sizeof(float));
@@ -93,31 +94,34 @@ __global__ void dp_prep_kernel(const int32_t* __restrict__ toff, const int32_t* 
   const int y0 = yoff[n], U = yoff[n + 1] - y0;
   // the utterance's targets in LDS (every entry point rejects U > PCTC_MAX_TARGET before
   // any launch): the duplicate search below compares every pair
-  __shared__ int y[PCTC_MAX_TARGET];
+  __shared__ __attribute__((aligned(16))) int y[PCTC_MAX_TARGET + 4];
   __shared__ int reps, badlab;
   if (threadIdx.x == 0) {
     reps = 0;
     badlab = 0;
   }
   for (int i = threadIdx.x; i < U; i += blockDim.x) y[i] = y_rel[y0 + i];
+  if (threadIdx.x < 4) y[U + threadIdx.x] = -2;  // up to the next multiple of four: equal to no target
   __syncthreads();
   int myreps = 0;
   for (int i = threadIdx.x; i < U; i += blockDim.x) {
-    if (y[i] < 1 || y[i] >= ncols) badlab = 1;  // not a label column of S
-    if (i > 0 && y[i] == y[i - 1]) ++myreps;
-    int nx = -1;
-    for (int j = i + 1; j < U; ++j)
-      if (y[j] == y[i]) {
-        nx = j;
-        break;
+    const int yi = y[i];
+    if (yi < 1 || yi >= ncols) badlab = 1;  // not a label column of S
+    if (i > 0 && yi == y[i - 1]) ++myreps;
+    // every target four at a time, the same ones in every lane, without a branch (a scan that
+    // stops at its match waits for each read: 400 targets 76 us against 30)
+    int nx = 0x7fffffff, first = 1;
+#pragma unroll 4
+    for (int j = 0; j < U; j += 4) {
+      const int4 v = *reinterpret_cast<const int4*>(y + j);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool eq = (k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w) == yi;
+        first = (eq && j + k < i) ? 0 : first;
+        nx = min(nx, (eq && j + k > i) ? j + k : 0x7fffffff);
       }
-    int first = 1;
-    for (int j = 0; j < i; ++j)
-      if (y[j] == y[i]) {
-        first = 0;
-        break;
-      }
-    dup_next[y0 + i] = nx;
+    }
+    dup_next[y0 + i] = nx == 0x7fffffff ? -1 : nx;
     dup_first[y0 + i] = first;
   }
   if (myreps) atomicAdd(&reps, myreps);
@@ -190,30 +194,47 @@ __device__ __forceinline__ Acc comb3(Acc a, Acc b, Acc c) {
 }
 
 // Frames of emissions (and arc flags) loaded ahead of the recursion: the frames in flight are
-// bounded by the wave's memory counter (63 instructions: per frame Q emission loads, Q table
-// stores and the offset store, and with a mask (Q + 3) / 4 + 1 flag-word loads) and by
-// registers.
+// bounded by the wave's memory counter (63 instructions: per frame Q emission loads (and two of
+// the next wavefront's states), Q table stores and the offset store, and with a mask up to
+// (Q + 5) / 4 + 1 flag-word loads) and by registers.
 template <int Q, bool MASK>
 constexpr int prefetch_depth() {
-  return Q <= 4 ? 8 : (Q <= 8 ? 5 : (Q <= 13 ? 3 : 2));
+  return Q <= 2 ? 8 : (Q <= 4 ? 6 : (Q <= 6 ? 4 : 3));
 }
 // The discarded-mass pass loads one flag byte per state.
 template <int Q>
 constexpr int prefetch_depth_bytes() {
-  return Q <= 3 ? 8 : (Q <= 4 ? 6 : (Q <= 6 ? 4 : (Q <= 8 ? 3 : 2)));
+  return Q <= 3 ? 8 : (Q <= 4 ? 6 : (Q <= 6 ? 4 : 3));
 }
 
-// One wavefront per (utterance, direction), natural-log units.  VIT: Viterbi (max-plus)
+// What the wavefronts of one lattice pass exchange each frame (two sets, used in turn, so that one
+// barrier per frame is enough): their maxima and, of every lane (a write under a lane condition
+// would be a branch in the frame loop), the states next to the neighbour's.
+template <int NWV, typename Acc, int NV>
+struct Exchange {
+  float mx[2][NWV];
+  Acc v[2][64 * NWV][NV];
+};
+// LDS writes of every wavefront of the workgroup done and visible; loads and stores to global
+// memory stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// NWV wavefronts per (utterance, direction), natural-log units.  VIT: Viterbi (max-plus)
 // accumulated in float; otherwise the total score (log-sum-exp) accumulated in double,
-// so the per-frame additions do not round at the magnitude of the emission scores.
+// so the per-frame additions do not round at the magnitude of the path's score.
 // Tables hold scores minus a per-frame offset (rounded to float once); the offsets are
 // kept per frame in double.  Emissions and arc flags for the next PF frames are held in
 // a register ring so that the gathers are issued well before they are needed.
-// kPassWaves wavefronts per workgroup (independent; no barriers), so that the few
-// wavefronts of this latency-bound stage occupy few compute units.
+// kPassWaves wavefronts per workgroup: with NWV = 1 independent ones (no barriers), so that the
+// few wavefronts of this latency-bound stage occupy few compute units; with NWV = 4 the four
+// of one unit, which exchange their maxima and edge states through LDS, one barrier per frame.
+// A frame's time grows with the states per lane (1500 frames, 801 states, beside the products:
+// 3.07 us a frame with 13 states per lane of one wavefront, 0.75 with 4 per lane of four), the
+// exchange costs about 0.1 us; so targets of more than 128 states take four wavefronts.  The
+// maxima are exact and every state's arithmetic is the same, so the tables do not depend on NWV.
 constexpr int kPassWaves = 4;
 
-template <int Q, bool VIT, bool MASK>
+template <int Q, bool VIT, bool MASK, int NWV>
 __global__ void __launch_bounds__(64 * kPassWaves)
 dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__ toff,
                const int32_t* __restrict__ yoff, const int64_t* __restrict__ soff, const int32_t* __restrict__ y_rel,
@@ -222,11 +243,16 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
                double* __restrict__ total_out, double* __restrict__ loss_n, int N, float* __restrict__ dummy) {
   using Acc = typename std::conditional<VIT, float, double>::type;
   constexpr int PF = prefetch_depth<Q, MASK>();
-  const int unit = blockIdx.x * kPassWaves + (threadIdx.x >> 6);  // (utterance, direction)
+  constexpr bool MULTI = NWV > 1;
+  static_assert(NWV == 1 || NWV == kPassWaves, "a unit is one wavefront or the workgroup");
+  __shared__ Exchange<MULTI ? NWV : 1, Acc, 2> xch;
+  const int unit = MULTI ? blockIdx.x : blockIdx.x * kPassWaves + (threadIdx.x >> 6);  // (utterance, direction)
   if (unit >= 2 * N) return;
   const int n = unit >> 1;
   const int dir = unit & 1;
-  const int lane = threadIdx.x & 63;
+  const int wl = threadIdx.x & 63;                        // lane of the wavefront
+  const int wv = MULTI ? static_cast<int>(threadIdx.x >> 6) : 0;
+  const int lane = MULTI ? static_cast<int>(threadIdx.x) : wl;  // lane of the unit
   if (status[n] != 0) return;
   const int t0 = toff[n], T = toff[n + 1] - t0;
   const int y0 = yoff[n], U = yoff[n + 1] - y0;
@@ -240,13 +266,19 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
   // defeating the prefetch ring.
   int zero_v;
   asm volatile("v_mov_b32 %0, 0" : "=v"(zero_v));
-  int col[Q];
-  bool valid[Q], skip_in[Q], skip_out[Q], fin[Q];
+  // HX: the next wavefront's first two states, which the backward pass's last lane needs too
+  constexpr int HX = MULTI ? 2 : 0;
+  int col[Q + HX];
+  bool valid[Q + HX], skip_in[Q], skip_out[Q], fin[Q];
+#pragma unroll
+  for (int q = 0; q < Q + HX; ++q) {
+    const int s = lane * Q + q;
+    valid[q] = s < Sp && (q < Q || (wl == 63 && dir == 1));
+    col[q] = (valid[q] && (s & 1)) ? y[(s - 1) >> 1] : zero_v;
+  }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int s = lane * Q + q;
-    valid[q] = s < Sp;
-    col[q] = (valid[q] && (s & 1)) ? y[(s - 1) >> 1] : zero_v;
     skip_in[q] = valid[q] && (s & 1) && s >= 3 && y[(s - 1) >> 1] != y[(s - 3) >> 1];
     const int s2 = s + 2;
     skip_out[q] = (s2 < Sp) && (s2 & 1) && y[(s2 - 1) >> 1] != y[(s2 - 3) >> 1];
@@ -256,57 +288,150 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
   // of the frame loop sits under a branch (addresses are clamped in bounds, lanes past the
   // last state store to this wave's dummy row): a branch around memory operations makes the
   // compiler wait for every outstanding load at the join, which would serialise the ring.
-  float* const drow = dummy + static_cast<int64_t>(unit) * (64 * Q) + lane * Q;
-  auto fetch = [&](int t, float (&e)[Q], int (&mk)[Q]) {
+  float* const drow = dummy + static_cast<int64_t>(unit) * kMaxStates + lane * Q;
+  // The flags stay as the words that hold them until the frame is used (decode): decoded where
+  // they are fetched, the loop waited for its own loads before it went round.
+  constexpr int NWD = MASK ? (Q + HX + 3) / 4 + 1 : 1;
+  auto flag_at = [&](int t) { return base + static_cast<int64_t>(t) * Sp + min(lane * Q, Sp - 1); };
+  auto fetch = [&](int t, float (&e)[Q + HX], uint32_t (&w)[NWD]) {
     const float* row = S + static_cast<int64_t>(t0 + t) * ldS;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) e[q] = row[col[q]];  // invalid states read the blank column (a valid address)
+    for (int q = 0; q < Q + HX; ++q) e[q] = row[col[q]];  // invalid states read the blank column (a valid address)
     if constexpr (MASK) {
       // this lane's Q flag bytes (from its first cell, clamped into the row) as the NWD aligned
-      // words that cover them, shifted into place: a few loads instead of Q byte loads (the
-      // bytes past the row's end, read only for cells past the last state, are not used)
-      constexpr int NWD = (Q + 3) / 4 + 1;
-      // (the region starts 256-byte aligned, so the offset's low bits are the address's)
-      const int64_t a = base + static_cast<int64_t>(t) * Sp + min(lane * Q, Sp - 1);
-      const uint32_t* wp = reinterpret_cast<const uint32_t*>(mask + (a & ~static_cast<int64_t>(3)));
-      const uint32_t sh = static_cast<uint32_t>(a & 3);
-      uint32_t w[NWD];
+      // words that cover them: a few loads instead of Q byte loads (the bytes past the row's end,
+      // read only for cells past the last state, are not used; the region starts 256-byte aligned,
+      // so the offset's low bits are the address's)
+      const uint32_t* wp = reinterpret_cast<const uint32_t*>(mask + (flag_at(t) & ~static_cast<int64_t>(3)));
 #pragma unroll
       for (int j = 0; j < NWD; ++j) w[j] = wp[j];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const uint32_t d = __builtin_amdgcn_alignbyte(w[(q >> 2) + 1], w[q >> 2], sh);
-        mk[q] = valid[q] ? static_cast<int>((d >> (8 * (q & 3))) & 0xffu) : 0;
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) mk[q] = valid[q] ? kAllArcs : 0;
     }
   };
-  auto renorm_store = [&](Acc (&v)[Q], double& off, float* tab, double* sc, int t) {
+  auto decode = [&](int t, const uint32_t (&w)[NWD], int (&mk)[Q + HX]) {
+    const uint32_t sh = MASK ? static_cast<uint32_t>(flag_at(t) & 3) : 0u;
+#pragma unroll
+    for (int q = 0; q < Q + HX; ++q) {
+      if constexpr (MASK) {
+        const uint32_t d = __builtin_amdgcn_alignbyte(w[(q >> 2) + 1], w[q >> 2], sh);
+        mk[q] = valid[q] ? static_cast<int>((d >> (8 * (q & 3))) & 0xffu) : 0;
+      } else {
+        mk[q] = valid[q] ? kAllArcs : 0;
+      }
+    }
+  };
+  int par = 0;  // exchange set in use
+  // The edge states a wavefront hands to its neighbour, and (mx) its maximum of a frame, into the
+  // exchange set in use; read are, forward, lane 63's last state and the one before (Q = 1: lane
+  // 62's), backward lane 0's first two (Q = 1: lane 1's second).
+  auto publish = [&](const Acc (&v)[Q], float mx) {
+    xch.mx[par][wv] = mx;  // the same value in every lane
+    xch.v[par][MULTI ? lane : 0][0] = dir == 0 ? v[Q - 1] : v[0];
+    if (Q >= 2) xch.v[par][MULTI ? lane : 0][1] = dir == 0 ? v[Q >= 2 ? Q - 2 : 0] : v[Q >= 2 ? 1 : 0];
+  };
+  // The other side, after a barrier: the maximum of all wavefronts' mx, and h0, h1: the previous
+  // wavefront's last two states (forward: h0 the last) or the next one's first two (backward: h0
+  // the first); kNeg at the ends.
+  auto collect = [&](Acc& h0, Acc& h1) {
+    float mx = kNeg;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) mx = fmaxf(mx, xch.mx[par][MULTI ? w : 0]);
+    const int nb = dir == 0 ? wv - 1 : wv + 1;
+    const bool have = nb >= 0 && nb < NWV;
+    const int at = MULTI ? (have ? nb : 0) * 64 + (dir == 0 ? 63 : 0) : 0;
+    const Acc x0 = xch.v[par][at][0];
+    const Acc x1 = Q >= 2 ? xch.v[par][at][Q >= 2 ? 1 : 0] : xch.v[par][MULTI ? (dir == 0 ? at - 1 : at + 1) : 0][0];
+    h0 = have ? x0 : neg;
+    h1 = have ? x1 : neg;
+    par ^= 1;
+    return mx;
+  };
+  auto lane_max = [&](const Acc (&v)[Q]) {
     float mx = kNeg;
 #pragma unroll
     for (int q = 0; q < Q; ++q) mx = fmaxf(mx, static_cast<float>(v[q]));
-    mx = wave_max_dpp(mx);
-    if (mx <= kNeg * 0.5f || mx != mx) mx = 0.f;  // all impossible (or NaN): keep as is
-#pragma unroll
-    for (int q = 0; q < Q; ++q) v[q] = (v[q] <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : v[q] - Acc(mx);
-    off += static_cast<double>(mx);
+    return wave_max_dpp(mx);
+  };
+  // Table row of a frame: the scores below mx, mx's running total beside them.
+  auto store_row = [&](const Acc (&v)[Q], double off, float* tab, double* sc, int t) {
     float* trow = tab + base + static_cast<int64_t>(t) * Sp + lane * Q;
 #pragma unroll
     for (int q = 0; q < Q; ++q) *(valid[q] ? trow + q : drow + q) = static_cast<float>(v[q]);
-    sc[t0 + t] = off;  // wave-uniform: every lane stores the same value
+    sc[t0 + t] = off;  // uniform: every lane stores the same value
   };
+  // A frame's end.  Viterbi (float: the scores must not round at the magnitude of the whole path)
+  // and one wavefront: renormalised by its maximum and stored.  Total score over four wavefronts:
+  // the recursion goes on with the scores as they are (double holds any path's score to 1e-10 and
+  // better) and only the stored row is taken below the frame's maximum, so the maximum
+  // (conversions, DPP steps, four scalar reads) is not between a frame and the next: a frame's
+  // maxima travel with the next frame's edge states and its row is stored one frame late (vp, mwp;
+  // first: none is pending).  1000 frames, 401 / 801 states: 542 -> 459, 809 -> 701 us; one
+  // wavefront is bound by its instructions, about 170 a frame, not by this chain.
+  Acc vp[Q];
+  float mwp = kNeg;
+  auto settle = [&](float mx) { return (mx <= kNeg * 0.5f || mx != mx) ? 0.f : mx; };  // all impossible (or NaN): as is
+  auto store_below = [&](const Acc (&v)[Q], float mx, float* tab, double* sc, int t) {
+    Acc r[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r[q] = (v[q] <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : v[q] - Acc(mx);
+    store_row(r, static_cast<double>(mx), tab, sc, t);
+  };
+  auto finish = [&](auto first, Acc (&v)[Q], Acc& h0, Acc& h1, double& off, float* tab, double* sc, int t) {
+    if constexpr (VIT || !MULTI) {
+      float mx = lane_max(v);
+      if constexpr (MULTI) {
+        publish(v, mx);
+        lds_barrier();
+        mx = collect(h0, h1);
+      }
+      mx = settle(mx);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = (v[q] <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : v[q] - Acc(mx);
+      if constexpr (MULTI) {
+        h0 = (h0 <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : h0 - Acc(mx);
+        h1 = (h1 <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : h1 - Acc(mx);
+      }
+      off += static_cast<double>(mx);
+      store_row(v, off, tab, sc, t);
+      return;
+    }
+    // impossible states stay at kNeg (an emission of -inf would make the next frame's differences
+    // NaN; NaN scores stay NaN)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = (v[q] <= Acc(kNeg * 0.5f)) ? Acc(kNeg) : v[q];
+    if constexpr (!VIT && MULTI) {
+      publish(v, mwp);
+      lds_barrier();
+      const float mx = settle(collect(h0, h1));
+      if constexpr (!decltype(first)::value) store_below(vp, mx, tab, sc, dir == 0 ? t - 1 : t + 1);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) vp[q] = v[q];
+      mwp = lane_max(v);
+    }
+  };
+  // The row still pending after the last frame.
+  auto flush = [&](float* tab, double* sc, int t) {
+    if constexpr (!VIT && MULTI) {
+      Acc x0, x1;
+      publish(vp, mwp);
+      lds_barrier();
+      store_below(vp, settle(collect(x0, x1)), tab, sc, t);
+    }
+  };
+  constexpr std::true_type kFirst{};
+  constexpr std::false_type kLater{};
 
-  float ring_e[PF][Q];
-  int ring_m[PF][Q];
+  float ring_e[PF][Q + HX];
+  uint32_t ring_m[PF][NWD];
+  Acc h0 = neg, h1 = neg;
   if (dir == 0) {
     // ---------------- forward ----------------
     Acc a[Q];
     {
-      float e[Q];
-      int mk[Q];
-      fetch(0, e, mk);
+      float e[Q + HX];
+      uint32_t w[NWD];
+      int mk[Q + HX];
+      fetch(0, e, w);
+      decode(0, w, mk);
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const int s = lane * Q + q;
@@ -316,33 +441,38 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
 #pragma unroll
     for (int k = 0; k < PF; ++k) fetch(min(1 + k, T - 1), ring_e[k], ring_m[k]);
     double off = 0.0;
-    renorm_store(a, off, tab_f, sc_f, 0);
+    finish(kFirst, a, h0, h1, off, tab_f, sc_f, 0);
     // frame t from ring slot k, which then prefetches frame t + PF (clamped to the last)
-    auto fstep = [&](int t, float (&re)[Q], int (&rm)[Q]) {
+    auto fstep = [&](int t, float (&re)[Q + HX], uint32_t (&rm)[NWD]) {
           float e[Q];
-          int mk[Q];
+          int mk[Q + HX];
 #pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            e[q] = re[q];
-            mk[q] = rm[q];
-          }
+          for (int q = 0; q < Q; ++q) e[q] = re[q];
+          decode(t, rm, mk);
           fetch(min(t + PF, T - 1), re, rm);
-          const Acc up1 = lane_up(a[Q - 1]);
-          const Acc up2 = (Q >= 2) ? lane_up(a[Q >= 2 ? Q - 2 : 0]) : lane_up(up1);
+          // lane 0 of a wavefront takes the previous wavefront's last states
+          Acc up1 = lane_up(a[Q - 1]);
+          if (MULTI && wl == 0) up1 = h0;
+          Acc up2 = (Q >= 2) ? lane_up(a[Q >= 2 ? Q - 2 : 0]) : lane_up(up1);
+          if (MULTI && wl == 0) up2 = h1;
           Acc na[Q];
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
             const Acc p0 = a[q];
             const Acc p1 = (q >= 1) ? a[q >= 1 ? q - 1 : 0] : up1;
             const Acc p2 = (q >= 2) ? a[q >= 2 ? q - 2 : 0] : (q == 1 ? up1 : up2);
-            const Acc c0 = (mk[q] & 1) ? p0 : neg;
-            const Acc c1 = (mk[q] & 2) ? p1 : neg;
-            const Acc c2 = (skip_in[q] && (mk[q] & 4)) ? p2 : neg;
-            na[q] = valid[q] ? static_cast<Acc>(e[q]) + comb3<VIT, Acc>(c0, c1, c2) : neg;
+            // a mask has bits of arcs that exist only; without one every arc that exists is kept.
+            // States past the last keep none, and e + kNeg is as impossible as kNeg: the result is
+            // not selected by valid[q] (the compiler makes a branch of that, with a wait for the
+            // loads in flight at its end: 331 frames, 111 states 220 us against 148)
+            const Acc c0 = (MASK ? (mk[q] & 1) != 0 : valid[q]) ? p0 : neg;
+            const Acc c1 = (MASK ? (mk[q] & 2) != 0 : valid[q]) ? p1 : neg;
+            const Acc c2 = (MASK ? (mk[q] & 4) != 0 : skip_in[q]) ? p2 : neg;
+            na[q] = static_cast<Acc>(e[q]) + comb3<VIT, Acc>(c0, c1, c2);
           }
 #pragma unroll
           for (int q = 0; q < Q; ++q) a[q] = na[q];
-          renorm_store(a, off, tab_f, sc_f, t);
+          finish(kLater, a, h0, h1, off, tab_f, sc_f, t);
     };
     int tb = 1;
     for (; tb + PF <= T; tb += PF) {
@@ -352,17 +482,27 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
 #pragma unroll
     for (int k = 0; k < PF; ++k)
       if (tb + k < T) fstep(tb + k, ring_e[k], ring_m[k]);
+    flush(tab_f, sc_f, T - 1);
     // total over final states (with final-arc flags)
-    int fk[Q];
+    int fk[Q + HX];
     {
-      float e[Q];
-      fetch(T - 1, e, fk);
+      float e[Q + HX];
+      uint32_t w[NWD];
+      fetch(T - 1, e, w);
+      decode(T - 1, w, fk);
     }
     float fm = kNeg;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       if (fin[q] && (fk[q] & 8)) fm = fmaxf(fm, static_cast<float>(a[q]));
     fm = wave_max_dpp(fm);
+    if constexpr (MULTI) {
+      if (wl == 0) xch.mx[par][wv] = fm;
+      lds_barrier();
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) fm = fmaxf(fm, xch.mx[par][w]);
+      par ^= 1;
+    }
     double total;
     if (VIT) {
       total = off + static_cast<double>(fm);
@@ -372,6 +512,13 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
       for (int q = 0; q < Q; ++q)
         if (fin[q] && (fk[q] & 8)) s += fast_exp2(static_cast<float>(a[q] - Acc(fm)) * kLog2e);
       s = wave_sum(s);
+      if constexpr (MULTI) {
+        if (wl == 0) xch.mx[par][wv] = s;
+        lds_barrier();
+        s = 0.f;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) s += xch.mx[par][w];
+      }
       total = off + static_cast<double>(fm) + static_cast<double>(fast_log2(s) * kLn2);
       if (fm <= kNeg * 0.5f) total = -INFINITY;
     }
@@ -388,9 +535,11 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
     // ---------------- backward ----------------
     Acc b[Q];
     {
-      float e[Q];
-      int mk[Q];
-      fetch(T - 1, e, mk);
+      float e[Q + HX];
+      uint32_t w[NWD];
+      int mk[Q + HX];
+      fetch(T - 1, e, w);
+      decode(T - 1, w, mk);
 #pragma unroll
       for (int q = 0; q < Q; ++q) b[q] = (fin[q] && (mk[q] & 8)) ? Acc(0) : neg;
     }
@@ -398,25 +547,32 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
 #pragma unroll
     for (int k = 0; k < PF; ++k) fetch(max(T - 1 - k, 0), ring_e[k], ring_m[k]);
     double off = 0.0;
-    renorm_store(b, off, tab_b, sc_b, T - 1);
+    finish(kFirst, b, h0, h1, off, tab_b, sc_b, T - 1);
     // frame t uses the emissions and arcs of frame t + 1 from ring slot k, which then
     // prefetches frame t + 1 - PF (clamped to the first)
-    auto bstep = [&](int t, float (&re)[Q], int (&rm)[Q]) {
-          float e[Q];
-          int mk[Q];
+    auto bstep = [&](int t, float (&re)[Q + HX], uint32_t (&rm)[NWD]) {
+          float e[Q + HX];
+          int mk[Q + HX];
 #pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            e[q] = re[q];
-            mk[q] = rm[q];
-          }
+          for (int q = 0; q < Q + HX; ++q) e[q] = re[q];
+          decode(t + 1, rm, mk);
           fetch(max(t + 1 - PF, 0), re, rm);
           Acc nb[Q];
 #pragma unroll
           for (int q = 0; q < Q; ++q) nb[q] = valid[q] ? static_cast<Acc>(e[q]) + b[q] : neg;
-          const Acc dn0 = lane_down(nb[0]);
-          const Acc dn1 = (Q >= 2) ? lane_down(nb[Q >= 2 ? 1 : 0]) : lane_down(dn0);
-          const int mdn0 = lane_down_i(mk[0]);
-          const int mdn1 = (Q >= 2) ? lane_down_i(mk[Q >= 2 ? 1 : 0]) : lane_down_i(mdn0);
+          // the last lane of a wavefront takes the next wavefront's first states
+          Acc dn0 = lane_down(nb[0]);
+          int mdn0 = lane_down_i(mk[0]);
+          if (MULTI && wl == 63) {
+            dn0 = valid[Q + HX - 2] ? static_cast<Acc>(e[Q + HX - 2]) + h0 : neg;
+            mdn0 = mk[Q + HX - 2];
+          }
+          Acc dn1 = (Q >= 2) ? lane_down(nb[Q >= 2 ? 1 : 0]) : lane_down(dn0);
+          int mdn1 = (Q >= 2) ? lane_down_i(mk[Q >= 2 ? 1 : 0]) : lane_down_i(mdn0);
+          if (MULTI && wl == 63) {
+            dn1 = valid[Q + HX - 1] ? static_cast<Acc>(e[Q + HX - 1]) + h1 : neg;
+            mdn1 = mk[Q + HX - 1];
+          }
           Acc nbb[Q];
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
@@ -426,14 +582,14 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
             const int m0 = mk[q];
             const int m1 = (q + 1 < Q) ? mk[q + 1 < Q ? q + 1 : 0] : mdn0;
             const int m2 = (q + 2 < Q) ? mk[q + 2 < Q ? q + 2 : 0] : (q + 1 < Q ? mdn0 : mdn1);
-            const Acc c0 = (m0 & 1) ? s0 : neg;
-            const Acc c1 = (m1 & 2) ? s1 : neg;
-            const Acc c2 = (skip_out[q] && (m2 & 4)) ? s2 : neg;
-            nbb[q] = valid[q] ? comb3<VIT, Acc>(c0, c1, c2) : neg;
+            const Acc c0 = (MASK ? (m0 & 1) != 0 : valid[q]) ? s0 : neg;
+            const Acc c1 = (MASK ? (m1 & 2) != 0 : valid[q]) ? s1 : neg;
+            const Acc c2 = (MASK ? (m2 & 4) != 0 : skip_out[q]) ? s2 : neg;
+            nbb[q] = comb3<VIT, Acc>(c0, c1, c2);
           }
 #pragma unroll
           for (int q = 0; q < Q; ++q) b[q] = nbb[q];
-          renorm_store(b, off, tab_b, sc_b, t);
+          finish(kLater, b, h0, h1, off, tab_b, sc_b, t);
     };
     int tb = T - 2;
     for (; tb - (PF - 1) >= 0; tb -= PF) {
@@ -443,6 +599,7 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
 #pragma unroll
     for (int k = 0; k < PF; ++k)
       if (tb - k >= 0) bstep(tb - k, ring_e[k], ring_m[k]);
+    flush(tab_b, sc_b, 0);
   }
 }
 
@@ -649,46 +806,39 @@ hipError_t launch_forecast_check(int N, const int32_t* status, const float* weig
 // ---------------------------------------------------------------------------------------
 
 template <bool VIT>
-static hipError_t launch_pass(int Q, int N, hipStream_t stream, const float* S, int ldS, const int32_t* toff,
+static hipError_t launch_pass(int Q, int nwv, int N, hipStream_t stream, const float* S, int ldS, const int32_t* toff,
                               const int32_t* yoff, const int64_t* soff, const int32_t* y_rel, int32_t* status,
                               const uint8_t* mask, float* tf, float* tb, double* sf, double* sb, double* total,
                               double* loss_n, float* dummy) {
-#define PCTC_PASS(QQ)                                                                                         \
-  case QQ:                                                                                                    \
-    if (mask)                                                                                                 \
-      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, !VIT>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS, toff, \
-                         yoff, soff, y_rel, status, mask, tf, tb, sf, sb, total, loss_n, N, dummy);           \
-    else                                                                                                      \
-      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, false>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS,   \
-                         toff, yoff, soff, y_rel, status, nullptr, tf, tb, sf, sb, total, loss_n, N, dummy);  \
-    break;
-  const dim3 grid((2 * N + kPassWaves - 1) / kPassWaves);
-  switch (Q) {
-    PCTC_PASS(1)
-    PCTC_PASS(2)
-    PCTC_PASS(3)
-    PCTC_PASS(4)
-    PCTC_PASS(6)
-    PCTC_PASS(8)
-    PCTC_PASS(10)
-    PCTC_PASS(13)
-    PCTC_PASS(16)
-    PCTC_PASS(20)
-    PCTC_PASS(24)
-    PCTC_PASS(32)
-    default:
-      return hipErrorInvalidValue;
+#define PCTC_PASS(QQ, NWV)                                                                                        \
+  if (Q == QQ && nwv == NWV) {                                                                                    \
+    const dim3 grid(NWV > 1 ? 2 * N : (2 * N + kPassWaves - 1) / kPassWaves);                                     \
+    if (mask)                                                                                                     \
+      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, !VIT, NWV>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS,     \
+                         toff, yoff, soff, y_rel, status, mask, tf, tb, sf, sb, total, loss_n, N, dummy);         \
+    else                                                                                                          \
+      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, false, NWV>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS,    \
+                         toff, yoff, soff, y_rel, status, nullptr, tf, tb, sf, sb, total, loss_n, N, dummy);      \
+    return hipGetLastError();                                                                                     \
   }
+  PCTC_PASS(1, 1)
+  PCTC_PASS(2, 1)
+  PCTC_PASS(1, 4)
+  PCTC_PASS(2, 4)
+  PCTC_PASS(3, 4)
+  PCTC_PASS(4, 4)
+  PCTC_PASS(6, 4)
+  PCTC_PASS(8, 4)
 #undef PCTC_PASS
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
-static int pick_q(int Smax) {
-  static const int qs[] = {1, 2, 3, 4, 6, 8, 10, 13, 16, 20, 24, kMaxQ};
-  const int need = (Smax + 63) / 64;
-  for (int q : qs)
-    if (q >= need) return q;
-  return -1;
+// States per lane and wavefronts per utterance and direction (or beam) for lattices of up to
+// Smax states per frame.
+static void pick_lanes(int Smax, int* Q, int* nwv) {
+  *nwv = Smax <= 128 ? 1 : 4;
+  const int need = (Smax + 64 * *nwv - 1) / (64 * *nwv);
+  *Q = need <= 4 ? need : (need <= 6 ? 6 : kMaxQ);
 }
 
 hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U, const float* S, int ldS,
@@ -713,8 +863,8 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
   double* sfa = reinterpret_cast<double*>(sc + plan.off_sc_fa);
   double* sfb = reinterpret_cast<double*>(sc + plan.off_sc_fb);
   hipError_t e;
-  const int Q = pick_q(plan.Smax);
-  if (Q < 0) return hipErrorInvalidValue;
+  int Q, nwv;
+  pick_lanes(plan.Smax, &Q, &nwv);
   uint8_t* mask = plan.pruned ? reinterpret_cast<uint8_t*>(sc + plan.off_mask) : nullptr;
   if (prep) {
     // G and g start at zero: excluded utterances and unused columns stay zero.
@@ -741,7 +891,7 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
       double* vbest = reinterpret_cast<double*>(sc + plan.off_vbest);
       {
         Prof pr("dp_viterbi", stream);
-        e = launch_pass<true>(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva,
+        e = launch_pass<true>(Q, nwv, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva,
                               svb, vbest, loss_n, dummy);
         if (e != hipSuccess) return e;
       }
@@ -758,7 +908,7 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
   if (!back || N == 0) return hipGetLastError();
   {
     Prof pr("dp_alpha_beta", stream);
-    e = launch_pass<false>(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, mask, tfa, tfb, sfa, sfb,
+    e = launch_pass<false>(Q, nwv, N, stream, S, ldS, toff, yoff, soff, y_rel, status, mask, tfa, tfb, sfa, sfb,
                            logp, loss_n, dummy);
     if (e != hipSuccess) return e;
   }
@@ -819,14 +969,20 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
-template <int Q>
-__global__ void __launch_bounds__(64)
+template <int Q, int NWV>
+__global__ void __launch_bounds__(64 * NWV)
 dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__ toff,
                     const int32_t* __restrict__ yoff, const int64_t* __restrict__ soff,
                     const int32_t* __restrict__ y_rel, const int32_t* __restrict__ status,
                     MaskBeams beams, double* __restrict__ delta_all) {
   const int n = blockIdx.x;
-  const int lane = threadIdx.x;
+  constexpr bool MULTI = NWV > 1;
+  __shared__ struct {
+    int hi[2][NWV];
+    double v[2][MULTI ? 64 * NWV : 1][4];  // each lane's last two states: full, retained, full, retained
+  } xch;
+  const int lane = threadIdx.x;  // of the utterance's wavefronts
+  const int wl = lane & 63, wv = MULTI ? lane >> 6 : 0;
   const uint8_t* const mask = beams.mask[blockIdx.y];
   double* const delta = delta_all + static_cast<int64_t>(blockIdx.y) * gridDim.x;
   if (status[n] != 0) {
@@ -849,6 +1005,8 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
     fin[q] = valid[q] && s >= Sp - 2;
   }
   double af[Q], ap[Q];  // full and retained forward sums, scaled per frame
+  double edge[4];       // the previous wavefront's last two states, scaled alike
+  int par = 0;          // exchange set in use
   // Emissions and arc flags of the next PF frames are held in a register ring; the loop has
   // only loads and no branch around them (clamped addresses), so each frame waits only for
   // its own ring slot.
@@ -884,12 +1042,33 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
 #pragma unroll
     for (int q = 0; q < Q; ++q) hi = max(hi, static_cast<int>(__double_as_longlong(nf[q]) >> 32));
     hi = wave_max_i(hi);
+    if constexpr (MULTI) {
+      xch.v[par][lane][0] = nf[Q - 1];
+      xch.v[par][lane][1] = np[Q - 1];
+      if (Q >= 2) {
+        xch.v[par][lane][2] = nf[Q >= 2 ? Q - 2 : 0];
+        xch.v[par][lane][3] = np[Q >= 2 ? Q - 2 : 0];
+      }
+      xch.hi[par][wv] = hi;
+      lds_barrier();
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) hi = max(hi, xch.hi[par][w]);
+    }
     const int ex = min(max(2046 - (hi >> 20), 1), 2046);
     const double inv = __longlong_as_double(static_cast<long long>(ex) << 52);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       af[q] = nf[q] * inv;
       ap[q] = np[q] * inv;
+    }
+    if constexpr (MULTI) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {  // (Q = 1: the state before the last is lane 62's last)
+        const int at = (wv > 0 ? wv - 1 : 0) * 64 + 63;
+        const double x = (Q == 1 && i >= 2) ? xch.v[par][at - 1][i - 2] : xch.v[par][at][i];
+        edge[i] = (wv > 0) ? x * inv : 0.0;
+      }
+      par ^= 1;
     }
   };
   {  // frame 0: the start arcs
@@ -920,9 +1099,17 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
     load_frame(min(t + PF, T - 1), re, rm);
     double pe[Q], nf[Q], np[Q];
     emit(e, pe);
-    const double uf1 = lane_up_d(af[Q - 1]), up1 = lane_up_d(ap[Q - 1]);
-    const double uf2 = (Q >= 2) ? lane_up_d(af[Q >= 2 ? Q - 2 : 0]) : lane_up_d(uf1);
-    const double up2 = (Q >= 2) ? lane_up_d(ap[Q >= 2 ? Q - 2 : 0]) : lane_up_d(up1);
+    double uf1 = lane_up_d(af[Q - 1]), up1 = lane_up_d(ap[Q - 1]);
+    if (MULTI && wl == 0) {
+      uf1 = edge[0];
+      up1 = edge[1];
+    }
+    double uf2 = (Q >= 2) ? lane_up_d(af[Q >= 2 ? Q - 2 : 0]) : lane_up_d(uf1);
+    double up2 = (Q >= 2) ? lane_up_d(ap[Q >= 2 ? Q - 2 : 0]) : lane_up_d(up1);
+    if (MULTI && wl == 0) {
+      uf2 = edge[2];
+      up2 = edge[3];
+    }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const double f0 = af[q], p0 = ap[q];
@@ -955,36 +1142,42 @@ dp_discarded_kernel(const float* __restrict__ S, int ldS, const int32_t* __restr
   }
   sf = wave_sum_d(sf);
   sp = wave_sum_d(sp);
+  if constexpr (MULTI) {
+    if (wl == 0) {
+      xch.v[par][wv][0] = sf;  // any slot of this set
+      xch.v[par][wv][1] = sp;
+    }
+    lds_barrier();
+    sf = sp = 0.0;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) {
+      sf += xch.v[par][w][0];
+      sp += xch.v[par][w][1];
+    }
+  }
   if (lane == 0) delta[n] = (sf > 0.0) ? 1.0 - sp / sf : __longlong_as_double(0x7ff8000000000000LL);
 }
 
-static hipError_t launch_discarded(int Q, int N, int nb, hipStream_t stream, const float* S, int ldS,
+static hipError_t launch_discarded(int Q, int nwv, int N, int nb, hipStream_t stream, const float* S, int ldS,
                                    const int32_t* toff, const int32_t* yoff, const int64_t* soff,
                                    const int32_t* y_rel, const int32_t* status, const MaskBeams& beams,
                                    double* delta) {
-#define PCTC_DISC(QQ)                                                                                             \
-  case QQ:                                                                                                        \
-    hipLaunchKernelGGL((dp_discarded_kernel<QQ>), dim3(N, nb), dim3(64), 0, stream, S, ldS, toff, yoff, soff,      \
-                       y_rel, status, beams, delta);                                                              \
-    break;
-  switch (Q) {
-    PCTC_DISC(1)
-    PCTC_DISC(2)
-    PCTC_DISC(3)
-    PCTC_DISC(4)
-    PCTC_DISC(6)
-    PCTC_DISC(8)
-    PCTC_DISC(10)
-    PCTC_DISC(13)
-    PCTC_DISC(16)
-    PCTC_DISC(20)
-    PCTC_DISC(24)
-    PCTC_DISC(32)
-    default:
-      return hipErrorInvalidValue;
+#define PCTC_DISC(QQ, NWV)                                                                                     \
+  if (Q == QQ && nwv == NWV) {                                                                                 \
+    hipLaunchKernelGGL((dp_discarded_kernel<QQ, NWV>), dim3(N, nb), dim3(64 * NWV), 0, stream, S, ldS, toff, yoff, \
+                       soff, y_rel, status, beams, delta);                                                     \
+    return hipGetLastError();                                                                                  \
   }
+  PCTC_DISC(1, 1)
+  PCTC_DISC(2, 1)
+  PCTC_DISC(1, 4)
+  PCTC_DISC(2, 4)
+  PCTC_DISC(3, 4)
+  PCTC_DISC(4, 4)
+  PCTC_DISC(6, 4)
+  PCTC_DISC(8, 4)
 #undef PCTC_DISC
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, const int32_t* y_rel, const float* beams,
@@ -1021,12 +1214,12 @@ hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, co
     hipLaunchKernelGGL(dp_prep_kernel, dim3(N), dim3(256), 0, stream, toff, yoff, y_rel, K_max, status, dnext, dfirst,
                        frame_utt, loss_n);
   }
-  const int Q = pick_q(plan.Smax);
-  if (Q < 0) return hipErrorInvalidValue;
+  int Q, nwv;
+  pick_lanes(plan.Smax, &Q, &nwv);
   hipError_t e;
   {  // the best alignments, the same for every beam
     Prof pr("dp_viterbi", stream);
-    e = launch_pass<true>(Q, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva, svb, vbest,
+    e = launch_pass<true>(Q, nwv, N, stream, S, ldS, toff, yoff, soff, y_rel, status, nullptr, tva, tvb, sva, svb, vbest,
                           loss_n, dummy);
     if (e != hipSuccess) return e;
   }
@@ -1048,7 +1241,7 @@ hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, co
     }
     {
       Prof pr("dp_discarded", stream);
-      e = launch_discarded(Q, N, nb, stream, S, ldS, toff, yoff, soff, y_rel, status, mb,
+      e = launch_discarded(Q, nwv, N, nb, stream, S, ldS, toff, yoff, soff, y_rel, status, mb,
                            delta + static_cast<int64_t>(b0) * N);
       if (e != hipSuccess) return e;
     }

@@ -112,3 +112,65 @@ def test_greedy_few_frames(M, V):
     top = Z.max(1)
     # the products' rounding (fp32 sums of 128 products) may pick another class within it
     assert np.all(Z[np.arange(M), ids] >= top - 1e-5 * np.abs(top))
+
+
+# ---- lattice passes over one and four wavefronts --------------------------------------------------
+
+@pytest.mark.parametrize("U", [0, 31, 63, 64, 127, 128, 255, 256, 384, 512, 700, 767, 768, 1022])
+@pytest.mark.parametrize("beam", [math.inf, 6.5])
+def test_lattice_wavefront_edges(U, beam):
+    """Targets around every change of the states per lane and of the wavefront count, with repeated
+    labels at the wavefronts' edges, beside a short utterance: losses, occupancies and kept arcs."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    rng = np.random.default_rng(U)
+    Us = np.array([U, 3], np.int32)
+    K = 40
+    y = rng.integers(1, K, size=int(Us.sum())).astype(np.int32)
+    y[1:U][rng.random(max(U - 1, 0)) < 0.2] = 1
+    T = np.array([U + int((y[1:U] == y[:U - 1][:max(U - 1, 0)]).sum()) + 23, 9], np.int32)
+    S = workloads.random_scores(U + 1, int(T.sum()), K, integer=True)  # margins >= 0.499 from the beam
+    say(f"lattice edges T={T.tolist()} U={U} beam={beam}")
+    ref = oracle.ctc_from_scores(S.astype(np.float64), y, T, Us, beam=beam)
+    out = prunedctc.ctc_dp(torch.from_numpy(S).cuda(), torch.from_numpy(y).cuda(), T, Us, beam=beam,
+                           want_mask=math.isfinite(beam))
+    np.testing.assert_array_equal(out["status"].cpu().numpy(), ref["status"])
+    np.testing.assert_allclose(out["loss_per_utt"].cpu().numpy(), ref["loss_n"], rtol=2e-6)
+    # the tables keep each state's score below its frame's best in float32 (2^-24 relative, in alpha
+    # and in beta), and the state an alignment needs may lie that far below: at most the sum of the
+    # utterance's scores, each frame's largest magnitude counted
+    depth = float(np.abs(S[:T[0]]).max(1).sum())
+    assert np.abs(out["G"].cpu().numpy() - ref["G"]).max() < 2e-5 + 2.0 ** -23 * depth
+    if math.isfinite(beam):
+        mask, base = out["mask"].cpu().numpy(), 0
+        for n in range(2):
+            if ref["status"][n] != 0:
+                base += int(T[n]) * (2 * int(Us[n]) + 1)
+                continue
+            Sp, mg = 2 * int(Us[n]) + 1, ref["per_utt"][n]["margins"]
+            stay = mg["stay"].copy()
+            stay[0] = mg["start"]
+            want = (stay >= 0) | ((mg["step"] >= 0) << 1) | ((mg["skip"] >= 0) << 2)
+            want[T[n] - 1] |= (mg["final"] >= 0) << 3
+            np.testing.assert_array_equal(mask[base:base + int(T[n]) * Sp].reshape(int(T[n]), Sp), want)
+            base += int(T[n]) * Sp
+
+
+@pytest.mark.parametrize("U", [63, 64, 127, 128, 300, 520, 800])
+def test_discarded_mass_wavefront_edges(U):
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    rng = np.random.default_rng(U)
+    K, Us = 30, np.array([U], np.int32)
+    y = rng.integers(1, K, size=U).astype(np.int32)
+    # three frames a label: the recursion's doubles, scaled by the frame's largest, keep the final
+    # states while they lie within 2^1000 of it (targets that nearly fill their frames may not)
+    T = np.array([3 * U + 15], np.int32)
+    S = workloads.random_scores(U, int(T[0]), K, integer=True)
+    beams = [2.5, 7.5]
+    got = prunedctc.discarded_mass(torch.from_numpy(S).cuda(), torch.from_numpy(y).cuda(), T, Us, beams).cpu().numpy()
+    ref = oracle.discarded_mass(S.astype(np.float64), y, T, Us, beams)
+    # T float emission factors (2^-23 each, the same in both recursions)
+    assert np.abs(got - ref).max() <= float(T[0]) * 2.0 ** -23
