@@ -17,7 +17,7 @@
 //                at least (best alignment) - beam - slack.
 //   dp_occupancy gamma_t(s) = alpha_t(s) beta_t(s) / P, summed per selected class into
 //                G = dL/dS = -gamma (Algorithm 1 output), and g = row sums of G.
-//   loss_reduce  sum of finite per-utterance losses (Algorithm 1, zero nonfinite).
+//   dp_tail      sum of finite per-utterance losses (Algorithm 1, zero nonfinite), outputs.
 #include <type_traits>
 
 #include "pctc_internal.h"
@@ -85,10 +85,18 @@ DpPlan plan_dp(int N, const int32_t* T, const int32_t* U, float beam) {
 
 // ---------------------------------------------------------------------------------------
 
-__global__ void dp_prep_kernel(const int32_t* __restrict__ toff, const int32_t* __restrict__ yoff,
+// Per-utterance set-up, and the inclusion forecast (g_pred, pred; null: none).  For an included
+// utterance every frame's occupancies sum to one (each retained alignment occupies exactly one
+// state per frame), so g_m = -w_n there and 0 on excluded utterances.  Before the lattice runs an
+// utterance is forecast included when its targets fit its frames (T_n >= U_n + repeats) and
+// w_n != 0; the lattice's statuses are checked against it afterwards (dp_tail).
+__global__ void __launch_bounds__(256)
+dp_prep_kernel(const int32_t* __restrict__ toff, const int32_t* __restrict__ yoff,
                                const int32_t* __restrict__ y_rel, int ncols, int32_t* __restrict__ status,
                                int32_t* __restrict__ dup_next, int32_t* __restrict__ dup_first,
-                               int32_t* __restrict__ frame_utt, double* __restrict__ loss_n) {
+                               int32_t* __restrict__ frame_utt, double* __restrict__ loss_n, float* __restrict__ g,
+                               const float* __restrict__ weight, float* __restrict__ g_pred,
+                               int32_t* __restrict__ pred) {
   const int n = blockIdx.x;
   const int t0 = toff[n], T = toff[n + 1] - t0;
   const int y0 = yoff[n], U = yoff[n + 1] - y0;
@@ -125,8 +133,17 @@ __global__ void dp_prep_kernel(const int32_t* __restrict__ toff, const int32_t* 
     dup_first[y0 + i] = first;
   }
   if (myreps) atomicAdd(&reps, myreps);
-  for (int t = threadIdx.x; t < T; t += blockDim.x) frame_utt[t0 + t] = n;
+  for (int t = threadIdx.x; t < T; t += blockDim.x) {
+    frame_utt[t0 + t] = n;
+    if (g) g[t0 + t] = 0.f;  // excluded utterances' frames stay zero
+  }
   __syncthreads();
+  if (g_pred) {
+    const float w = weight ? weight[n] : 1.f;
+    const bool inc = T >= U + reps && w != 0.f;
+    for (int t = threadIdx.x; t < T; t += blockDim.x) g_pred[t0 + t] = inc ? -w : 0.f;
+    if (threadIdx.x == 0) pred[n] = inc ? 1 : 0;
+  }
   if (threadIdx.x == 0) {
     // 3: a relabelled target is not a label column; the lattice is not evaluated
     status[n] = badlab ? 3 : ((T >= U + reps) ? 0 : 1);
@@ -723,83 +740,48 @@ dp_occupancy_kernel(const int32_t* __restrict__ toff, const int32_t* __restrict_
   }
 }
 
-// loss = sum over included utterances of w_n L_n (w_n = 1 without weights)
-__global__ void loss_reduce_kernel(int N, const double* __restrict__ loss_n, const int32_t* __restrict__ status,
-                                   const float* __restrict__ weight, double* __restrict__ loss) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double s = 0.0;
-  for (int n = 0; n < N; ++n)
-    if (status[n] == 0) s += (weight ? static_cast<double>(weight[n]) : 1.0) * loss_n[n];
-  *loss = s;
-}
-
-hipError_t launch_loss_reduce(int N, const double* loss_n, const int32_t* status, const float* weight, double* loss,
-                              hipStream_t stream) {
-  Prof pr("loss_reduce", stream);
-  hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(64), 0, stream, N, loss_n, status, weight, loss);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------
-// Inclusion forecast.  For an included utterance every frame's occupancies sum to one
-// (each retained alignment occupies exactly one state per frame), so g_m = -w_n there and
-// 0 on excluded utterances.  Before the lattice runs, an utterance is forecast included when
-// its targets fit its frames (T_n >= U_n + repeats), w_n != 0 and, when lam is given, every
-// frame has a finite normaliser (else a nonfinite normaliser shows up in the lattice's
-// status); the lattice's statuses are checked against the forecast afterwards.
-// ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-g_forecast_kernel(const int32_t* __restrict__ toff, const int32_t* __restrict__ yoff, const int32_t* __restrict__ y_rel,
-                  const double* __restrict__ lam, const float* __restrict__ weight, float* __restrict__ g_pred,
-                  int32_t* __restrict__ pred) {
-  const int n = blockIdx.x;
-  const int t0 = toff[n], T = toff[n + 1] - t0;
-  const int y0 = yoff[n], U = yoff[n + 1] - y0;
-  int reps = 0, bad = 0;
-  for (int i = 1 + threadIdx.x; i < U; i += blockDim.x) reps += (y_rel[y0 + i] == y_rel[y0 + i - 1]);
-  if (lam)
-    for (int t = threadIdx.x; t < T; t += blockDim.x) {
-      const double l = lam[t0 + t];
-      bad |= !(l > -INFINITY && l < INFINITY);  // NaN fails both
-    }
-  __shared__ int sreps;
-  if (threadIdx.x == 0) sreps = 0;
-  __syncthreads();
-  if (reps) atomicAdd(&sreps, reps);
-  const int anybad = __syncthreads_or(bad);
-  const float w = weight ? weight[n] : 1.f;
-  const bool inc = !anybad && T >= U + sreps && w != 0.f;
-  for (int t = threadIdx.x; t < T; t += blockDim.x) g_pred[t0 + t] = inc ? -w : 0.f;
-  if (threadIdx.x == 0) pred[n] = inc ? 1 : 0;
-}
-
-// flag = 1 if any utterance's inclusion (status 0 and w_n != 0) differs from the forecast
-__global__ void forecast_check_kernel(int N, const int32_t* __restrict__ status, const float* __restrict__ weight,
-                                      const int32_t* __restrict__ pred, int32_t* __restrict__ flag) {
+// The lattice's end in one launch: loss = sum over included utterances of w_n L_n (w_n = 1 without
+// weights), in order; the caller's copies of the losses and statuses; and, in the two-stream
+// schedule, flag = 1 if an utterance's inclusion (status 0 and w_n != 0) differs from the forecast
+// (dp_prep).  The values pass through LDS: one thread adding 160 losses from memory took 20 us.
+constexpr int kTailThreads = 256;
+__global__ void __launch_bounds__(kTailThreads)
+dp_tail_kernel(int N, const double* __restrict__ loss_n, const int32_t* __restrict__ status,
+               const float* __restrict__ weight, const int32_t* __restrict__ pred, double* __restrict__ loss,
+               double* __restrict__ loss_out, int32_t* __restrict__ status_out, int32_t* __restrict__ flag) {
+  __shared__ double term[kTailThreads];
+  double sum = 0.0;
   int bad = 0;
-  for (int n = threadIdx.x; n < N; n += blockDim.x) {
-    const float w = weight ? weight[n] : 1.f;
-    const int inc = (status[n] == 0 && w != 0.f) ? 1 : 0;
-    bad |= (inc != pred[n]);
+  for (int b = 0; b < N; b += kTailThreads) {
+    const int n = b + threadIdx.x;
+    double x = 0.0;
+    if (n < N) {
+      const double l = loss_n[n];
+      const int st = status[n];
+      const float w = weight ? weight[n] : 1.f;
+      if (st == 0) x = static_cast<double>(w) * l;
+      if (loss_out) loss_out[n] = l;
+      if (status_out) status_out[n] = st;
+      if (pred) bad |= ((st == 0 && w != 0.f) ? 1 : 0) != pred[n];
+    }
+    term[threadIdx.x] = x;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int i = 0; i < min(kTailThreads, N - b); ++i) sum += term[i];
+    __syncthreads();
   }
   bad = __syncthreads_or(bad);
-  if (threadIdx.x == 0) flag[0] = bad;
+  if (threadIdx.x == 0) {
+    *loss = sum;
+    if (pred) *flag = bad;
+  }
 }
 
-hipError_t launch_g_forecast(const DpPlan& plan, void* scratch, const int32_t* y_rel, const double* lam,
-                             const float* weight, float* g_pred, int32_t* pred, hipStream_t stream) {
-  if (plan.N == 0) return hipSuccess;
-  char* sc = static_cast<char*>(scratch);
-  const int32_t* toff = reinterpret_cast<const int32_t*>(sc + plan.off_toff);
-  const int32_t* yoff = reinterpret_cast<const int32_t*>(sc + plan.off_yoff);
-  hipLaunchKernelGGL(g_forecast_kernel, dim3(plan.N), dim3(256), 0, stream, toff, yoff, y_rel, lam, weight, g_pred,
-                     pred);
-  return hipGetLastError();
-}
-
-hipError_t launch_forecast_check(int N, const int32_t* status, const float* weight, const int32_t* pred,
-                                 int32_t* flag, hipStream_t stream) {
-  hipLaunchKernelGGL(forecast_check_kernel, dim3(1), dim3(256), 0, stream, N, status, weight, pred, flag);
+hipError_t launch_dp_tail(int N, const double* loss_n, const int32_t* status, const float* weight, const int32_t* pred,
+                          double* loss, double* loss_out, int32_t* status_out, int32_t* flag, hipStream_t stream) {
+  Prof pr("dp_tail", stream);
+  hipLaunchKernelGGL(dp_tail_kernel, dim3(1), dim3(kTailThreads), 0, stream, N, loss_n, status, weight, pred, loss,
+                     loss_out, status_out, flag);
   return hipGetLastError();
 }
 
@@ -844,10 +826,10 @@ static void pick_lanes(int Smax, int* Q, int* nwv) {
 hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U, const float* S, int ldS,
                          const int32_t* y_rel, float beam, const float* weight, double* loss_n, int32_t* status,
                          float* G, float* g, uint8_t* keep_mask_out, void* scratch, int K_max, hipStream_t stream,
-                         void*, int phase) {
+                         int phase, bool g_zeroed, float* g_pred, int32_t* pred) {
   const int N = plan.N;
-  const bool prep = phase == kDpAll || phase == kDpFront || phase == kDpPrep;
-  const bool vit = phase == kDpAll || phase == kDpFront || phase == kDpVit;
+  const bool prep = phase == kDpAll || phase == kDpPrep;
+  const bool vit = phase == kDpAll || phase == kDpVit;
   const bool back = phase == kDpAll || phase == kDpBack;
   char* sc = static_cast<char*>(scratch);
   int32_t* toff = reinterpret_cast<int32_t*>(sc + plan.off_toff);
@@ -867,19 +849,15 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
   pick_lanes(plan.Smax, &Q, &nwv);
   uint8_t* mask = plan.pruned ? reinterpret_cast<uint8_t*>(sc + plan.off_mask) : nullptr;
   if (prep) {
-    // G and g start at zero: excluded utterances and unused columns stay zero.
-    if (plan.M > 0) {
+    // G starts at zero: excluded utterances and unused columns stay zero
+    if (plan.M > 0 && !g_zeroed) {
       e = hipMemsetAsync(G, 0, static_cast<size_t>(plan.M) * ldS * sizeof(float), stream);
-      if (e != hipSuccess) return e;
-      e = hipMemsetAsync(g, 0, static_cast<size_t>(plan.M) * sizeof(float), stream);
       if (e != hipSuccess) return e;
     }
     if (N == 0) return hipSuccess;
-    {
-      Prof pr("dp_prep", stream);
-      hipLaunchKernelGGL(dp_prep_kernel, dim3(N), dim3(256), 0, stream, toff, yoff, y_rel, K_max, status, dnext,
-                         dfirst, frame_utt, loss_n);
-    }
+    Prof pr("dp_prep", stream);
+    hipLaunchKernelGGL(dp_prep_kernel, dim3(N), dim3(256), 0, stream, toff, yoff, y_rel, K_max, status, dnext, dfirst,
+                       frame_utt, loss_n, g, weight, g_pred, pred);
   }
   if (N == 0) return hipGetLastError();
   if (vit) {
@@ -1212,7 +1190,7 @@ hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, co
   {
     Prof pr("dp_prep", stream);
     hipLaunchKernelGGL(dp_prep_kernel, dim3(N), dim3(256), 0, stream, toff, yoff, y_rel, K_max, status, dnext, dfirst,
-                       frame_utt, loss_n);
+                       frame_utt, loss_n, nullptr, nullptr, nullptr, nullptr);
   }
   int Q, nwv;
   pick_lanes(plan.Smax, &Q, &nwv);

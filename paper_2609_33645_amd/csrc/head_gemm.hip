@@ -214,13 +214,13 @@ hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, 
 
 hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W, const float* bias,
                            const int32_t* u_ids, const int32_t* K, int K_max, const double* lam, float* S, int ldS,
-                           hipStream_t stream) {
+                           hipStream_t stream, float* Gz) {
   if (M <= 0) return hipSuccess;
   if (dtype == 1)
     return launch_gather_s_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, u_ids, K,
-                                K_max, lam, S, ldS, stream);
+                                K_max, lam, S, ldS, stream, nullptr, Gz);
   return launch_gather_s_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, u_ids, K, K_max,
-                             lam, S, ldS, stream);
+                             lam, S, ldS, stream, Gz);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -383,8 +383,10 @@ static hipError_t head_bwd_bf16(const uint16_t* H, int M, int D, const uint16_t*
   auto start_side = [&](int upto) -> hipError_t {  // enqueue works [started, upto)
     for (; started < upto && started < nwork; ++started) {
       hipError_t err;
-      if ((err = hipEventRecord(side->gate[started], stream)) != hipSuccess) return err;
-      if ((err = hipStreamWaitEvent(side->stream, side->gate[started], 0)) != hipSuccess) return err;
+      if (!side->eager) {
+        if ((err = hipEventRecord(side->gate[started], stream)) != hipSuccess) return err;
+        if ((err = hipStreamWaitEvent(side->stream, side->gate[started], 0)) != hipSuccess) return err;
+      }
       if ((err = side->work[started].fn(side->work[started].ctx)) != hipSuccess) return err;
     }
     return hipSuccess;
@@ -398,6 +400,8 @@ static hipError_t head_bwd_bf16(const uint16_t* H, int M, int D, const uint16_t*
     if ((err = hipStreamWaitEvent(side->stream, side->front_gate, 0)) != hipSuccess) return err;
     return side->front.fn(side->front.ctx);
   };
+  if (two && side->eager && (e = start_side(1)) != hipSuccess) return e;
+  auto due = [&](bool last, int done) { return last || (two && side->eager) ? nwork : done; };
   int ci = 0;  // chunk index
   for (int c0 = 0; c0 < V; c0 += chunk, ++ci) {
     const int cw = min(chunk, V - c0);
@@ -437,12 +441,12 @@ static hipError_t head_bwd_bf16(const uint16_t* H, int M, int D, const uint16_t*
       e = launch_bwd_chunk_bf16(Hs, M, D, W, bias, c0, cw, lam2, G, ldG, g, remap, S, ldS, dZ, chunk, part, sl,
                                 false, false, dW != nullptr, dW, db, dbpart, stream, nullptr, ce, Hst, plan.Mp);
       if (e != hipSuccess) return e;
-      if ((e = start_side(last ? nwork : ci + 1)) != hipSuccess) return e;
+      if ((e = start_side(due(last, ci + 1))) != hipSuccess) return e;
     } else {
       e = launch_bwd_chunk_bf16(Hs, M, D, W, bias, c0, cw, lam2, G, ldG, g, remap, S, ldS, dZ, chunk, part, sl,
                                 true, dH != nullptr, dW != nullptr, dW, db, dbpart, stream, nullptr, ce, Hst, plan.Mp);
       if (e != hipSuccess) return e;
-      if ((e = start_side(last ? nwork : ci + 1)) != hipSuccess) return e;
+      if ((e = start_side(due(last, ci + 1))) != hipSuccess) return e;
     }
   }
   if ((e = start_front()) != hipSuccess) return e;

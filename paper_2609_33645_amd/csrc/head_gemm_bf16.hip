@@ -303,7 +303,8 @@ amax_partial_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* 
 __global__ void __launch_bounds__(256, 2)
 gather_s_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* __restrict__ W,
               const float* __restrict__ bias, const int32_t* __restrict__ u_ids, const int32_t* __restrict__ Kdev,
-              const double* __restrict__ lam, float* __restrict__ S, int ldS, double* __restrict__ Zd) {
+              const double* __restrict__ lam, float* __restrict__ S, int ldS, double* __restrict__ Zd,
+              float* __restrict__ Gz) {
   using G = GFwdGather;
   constexpr int FR = G::FR, FC = G::FC;
   PCTC_STAGES_G(G)
@@ -336,6 +337,7 @@ gather_s_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* __re
             Zd[static_cast<int64_t>(m) * ldS + jj] = z;
           else
             S[static_cast<int64_t>(m) * ldS + jj] = static_cast<float>(z - l);
+          if (Gz) Gz[static_cast<int64_t>(m) * ldS + jj] = 0.f;
         }
       }
   }
@@ -828,15 +830,28 @@ __global__ void hs_scale_bf16(const uint16_t* __restrict__ Hs, int64_t n, int D,
 // Gb [M][2 ldK]: columns j and K + j hold the hi and lo halves of G[m][j] for j < K (K the
 // union size found on the device, <= ldK) and the columns from 2K on hold zeros (a product's
 // copy of a k-run may reach past 2K; those values meet zero rows of W_U, and must be finite).
+//
+// WU2 [2 ldK][D] (null: not wanted), in the same launch, its workgroups from `nsplit` on: rows j and
+// K + j hold W[U_j] for j < K; the rows past 2K are never read.
 __global__ void __launch_bounds__(256)
-union_split_bf16(const float* __restrict__ G, int ldG, const int32_t* __restrict__ Kdev, int ldK, int M,
-                 uint16_t* __restrict__ Gb) {
+union_prep_bf16(const float* __restrict__ G, int ldG, const int32_t* __restrict__ Kdev, int ldK, int M,
+                uint16_t* __restrict__ Gb, int nsplit, const uint16_t* __restrict__ W, int D,
+                const int32_t* __restrict__ u_ids, uint16_t* __restrict__ WU2) {
   const int K = *Kdev;
+  if (static_cast<int>(blockIdx.x) >= nsplit) {
+    for (int r = blockIdx.x - nsplit; r < 2 * K; r += gridDim.x - nsplit) {
+      const int j = r < K ? r : r - K;
+      const uint16_t* src = W + static_cast<int64_t>(u_ids[j]) * D;
+      for (int d = threadIdx.x * 8; d < D; d += 256 * 8)
+        *reinterpret_cast<u32x4*>(WU2 + static_cast<int64_t>(r) * D + d) = *reinterpret_cast<const u32x4*>(src + d);
+    }
+    return;
+  }
   const int64_t n = static_cast<int64_t>(M) * ldK;
   // a few hundred workgroups stride over the elements: the launch runs beside a recompute,
   // whose compute units it should not churn with thousands of tiny workgroups
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * 256) {
+       i += static_cast<int64_t>(nsplit) * 256) {
     const int m = static_cast<int>(i / ldK), j = static_cast<int>(i % ldK);
     const float* grow = G + static_cast<int64_t>(m) * ldG;
     uint16_t* row = Gb + static_cast<int64_t>(m) * (2 * ldK);
@@ -855,29 +870,44 @@ union_split_bf16(const float* __restrict__ G, int ldG, const int32_t* __restrict
   }
 }
 
-// WU2 [2 ldK][D]: rows j and K + j hold W[U_j] for j < K; the rows past 2K are never read.
-__global__ void __launch_bounds__(256)
-union_rows_bf16(const uint16_t* __restrict__ W, int D, const int32_t* __restrict__ u_ids,
-                const int32_t* __restrict__ Kdev, uint16_t* __restrict__ WU2) {
-  const int K = *Kdev;
-  for (int r = blockIdx.x; r < 2 * K; r += gridDim.x) {
-    const int j = r < K ? r : r - K;
-    const uint16_t* src = W + static_cast<int64_t>(u_ids[j]) * D;
-    for (int d = threadIdx.x * 8; d < D; d += 256 * 8)
-      *reinterpret_cast<u32x4*>(WU2 + static_cast<int64_t>(r) * D + d) = *reinterpret_cast<const u32x4*>(src + d);
-  }
-}
-
-// dbp[z][j] = sum of G[m][j] over the frames of slice z (fp32, in frame order)
+// dbp[z][j] = sum of G[m][j] over the frames of slice z (fp32): 256 columns per workgroup, four per
+// lane, its four wavefronts taking every fourth frame (a thread per column walking a sixteenth
+// of the frames: 210 us at M = 4,347, K_max = 710, longer than the recompute beside it)
 __global__ void __launch_bounds__(256)
 union_colsum_bf16(const float* __restrict__ G, int ldG, int M, int K_max, int mper, float* __restrict__ dbp) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  __shared__ float4 x[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = blockIdx.x * 256 + lane * 4;  // ldG is a multiple of 4, at least K_max
   const int z = blockIdx.y;
-  if (j >= K_max) return;
   const int mb = z * mper, me = min(M, mb + mper);
-  float acc = 0.f;
-  for (int m = mb; m < me; ++m) acc += G[static_cast<int64_t>(m) * ldG + j];
-  dbp[static_cast<int64_t>(z) * K_max + j] = acc;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (j < K_max) {
+#pragma unroll 4
+    for (int m = mb + wave; m < me; m += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(G + static_cast<int64_t>(m) * ldG + j);
+      s.x += v.x;
+      s.y += v.y;
+      s.z += v.z;
+      s.w += v.w;
+    }
+  }
+  x[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const float4 v = x[w][lane];
+      s.x += v.x;
+      s.y += v.y;
+      s.z += v.z;
+      s.w += v.w;
+    }
+    float* const o = dbp + static_cast<int64_t>(z) * K_max + j;
+    if (j < K_max) o[0] = s.x;
+    if (j + 1 < K_max) o[1] = s.y;
+    if (j + 2 < K_max) o[2] = s.z;
+    if (j + 3 < K_max) o[3] = s.w;
+  }
 }
 
 // dW[U_j, :] += sum over the frame slices of dW_u2[j, :] + dW_u2[K + j, :];
@@ -907,7 +937,7 @@ union_merge_bf16(const int32_t* __restrict__ Kdev, const int32_t* __restrict__ u
 }
 
 namespace {
-constexpr int kColSlices = 16;
+constexpr int kColSlices = 64;
 struct UnionCorrLayout {
   int ldK, nz, mslice;  // dW_u over nz slices of mslice frames (one: every frame)
   size_t o_dwu, o_wu, o_dbp, total;
@@ -959,16 +989,17 @@ hipError_t launch_union_part_bf16(const float* G, int ldG, const int32_t* Kdev, 
   const UnionCorrLayout L = union_corr_layout(M, D, K_max, want_dW);
   char* sc = static_cast<char*>(scratch);
   const int k2 = 2 * L.ldK;
+  uint16_t* WU2 = reinterpret_cast<uint16_t*>(sc + L.o_wu);
   if (want_dH || want_dW) {
     Prof pr("union_prep", stream);
     const int64_t n = static_cast<int64_t>(M) * L.ldK;
     const int64_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(union_split_bf16, dim3(static_cast<unsigned>(blocks < 512 ? blocks : 512)), dim3(256), 0,
-                       stream, G, ldG, Kdev, L.ldK, M, Gb);
+    const int nsplit = static_cast<int>(blocks < 512 ? blocks : 512);
+    const int nrows = want_dH ? (k2 < 256 ? k2 : 256) : 0;
+    hipLaunchKernelGGL(union_prep_bf16, dim3(nsplit + nrows), dim3(256), 0, stream, G, ldG, Kdev, L.ldK, M, Gb, nsplit,
+                       W, D, u_ids, WU2);
   }
   if (want_dH) {
-    uint16_t* WU2 = reinterpret_cast<uint16_t*>(sc + L.o_wu);
-    hipLaunchKernelGGL(union_rows_bf16, dim3(k2 < 256 ? k2 : 256), dim3(256), 0, stream, W, D, u_ids, Kdev, WU2);
     if (!dh_later) {
       const int tiles = ((M + GUh::kBR - 1) / GUh::kBR) * ((D + GUh::kBC - 1) / GUh::kBC);
       Prof pr("union_dh", stream);
@@ -1115,12 +1146,12 @@ hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint1
 
 hipError_t launch_gather_s_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias,
                                 const int32_t* u_ids, const int32_t* K, int K_max, const double* lam, float* S, int ldS,
-                                hipStream_t stream, double* Zd) {
+                                hipStream_t stream, double* Zd, float* Gz) {
   const int nMt = (M + kFC - 1) / kFC;
   const int nJt = (K_max + kFR - 1) / kFR;
   Prof pr("gather_s", stream);
   hipLaunchKernelGGL(gather_s_bf16, dim3(nMt * nJt), dim3(GFwd::kThreads), 0, stream, H, M, D, W, bias, u_ids, K, lam,
-                     S, ldS, Zd);
+                     S, ldS, Zd, Gz);
   return hipGetLastError();
 }
 

@@ -134,7 +134,7 @@ amax_partial_f32(const float* __restrict__ H, int M, int D, const float* __restr
 __global__ void __launch_bounds__(512, 1)
 gather_s_f32(const float* __restrict__ H, int M, int D, const float* __restrict__ W, const float* __restrict__ bias,
              const int32_t* __restrict__ u_ids, const int32_t* __restrict__ Kdev, const double* __restrict__ lam,
-             float* __restrict__ S, int ldS) {
+             float* __restrict__ S, int ldS, float* __restrict__ Gz) {
   using G = GZGather;
   PCTC_F3_STAGES
   const int nMt = (M + kTile - 1) / kTile;
@@ -169,6 +169,7 @@ gather_s_f32(const float* __restrict__ H, int M, int D, const float* __restrict_
           double v = static_cast<double>(e == 0 ? z.x : e == 1 ? z.y : e == 2 ? z.z : z.w);
           if (bias) v += static_cast<double>(bias[u_ids[jj]]);
           srow[jj] = static_cast<float>(v - l);
+          if (Gz) Gz[static_cast<int64_t>(mw + f) * ldS + jj] = 0.f;
         }
       }
     }
@@ -462,10 +463,11 @@ hipError_t launch_amax_partial_f32(const float* H, int M, int D, const float* W,
 }
 
 hipError_t launch_gather_s_f32(const float* H, int M, int D, const float* W, const float* bias, const int32_t* u_ids,
-                               const int32_t* K, int K_max, const double* lam, float* S, int ldS, hipStream_t stream) {
+                               const int32_t* K, int K_max, const double* lam, float* S, int ldS, hipStream_t stream,
+                               float* Gz) {
   const int tiles = ((M + kTile - 1) / kTile) * ((K_max + kTile - 1) / kTile);
   Prof pr("gather_s", stream);
-  hipLaunchKernelGGL(gather_s_f32, dim3(tiles), dim3(512), 0, stream, H, M, D, W, bias, u_ids, K, lam, S, ldS);
+  hipLaunchKernelGGL(gather_s_f32, dim3(tiles), dim3(512), 0, stream, H, M, D, W, bias, u_ids, K, lam, S, ldS, Gz);
   return hipGetLastError();
 }
 

@@ -343,6 +343,24 @@ static hipError_t side_stream(hipStream_t caller, hipStream_t* out) {
   return hipSuccess;
 }
 
+static int t_max_of(int N, const int32_t* T) {
+  int t = 0;
+  for (int n = 0; n < N; ++n) t = std::max(t, T[n]);
+  return t;
+}
+
+// Whether the lattice (T sequential frames a pass, whatever the batch) is more than half as long as
+// the dense part of the backward beside it, by 1 PFLOP/s and by what a frame takes: 0.45 us a
+// total-score pass on one wavefront (up to 128 states), 0.3 + 0.12 per state a lane on four,
+// about two thirds of that for the Viterbi pass, and 100 us of small launches around them.
+// 331 frames, D = 512, V = 180,000 (dense part 180 us, lattice 350): 661 us ungated against
+// 686; 16 utterances of up to 375 frames there (2400 us, 380): gated.
+static bool lattice_leads(const DpPlan& dp, int t_max, int D, int V) {
+  const double dense = 6.0 * dp.M * static_cast<double>(V) * D / 1e9;
+  const double frame = dp.Smax <= 128 ? 0.45 : 0.3 + 0.12 * ((dp.Smax + 255) / 256);
+  return 100.0 + t_max * frame * (dp.pruned ? 1.65 : 1.0) > 0.5 * dense;
+}
+
 }  // namespace pctc
 
 using namespace pctc;
@@ -443,12 +461,11 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
   // the normaliser writes the first chunk's dZ rows as E = exp(z) (dense part only: no bias,
   // no db); einv: its range check, rowscale (escale) and Hp: that chunk's factors
   const bool use_e = overlap && L.eparts > 0 && !bias && !db && (dH || dW);
-  // a short lattice (every utterance at most kFrontDeferT frames) starts its front beside the
-  // first chunk's dW product, which it slows less than that chunk's dH; a longer one is on the
-  // critical path and starts as soon as S is formed
-  int t_max = 0;
-  for (int n = 0; n < N; ++n) t_max = std::max(t_max, input_lengths[n]);
-  const bool defer_front = overlap && t_max <= kFrontDeferT;
+  // The lattice's front waits for the first chunk's dH product, so that it starts beside that
+  // chunk's dW, which it slows less, and its other works are gated chunk by chunk, unless the
+  // lattice would then end the call (lattice_leads): it runs at once, ungated
+  const bool eager = overlap && lattice_leads(L.dp, t_max_of(N, input_lengths), D, V);
+  const bool defer_front = overlap && !eager;
   int32_t* einv = Kdev + 3;
   float* escale = use_e ? reinterpret_cast<float*>(ws + L.o_escale) : nullptr;
   ChunkE chunk_e;
@@ -502,8 +519,10 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
     PCTC_HIP(upload_offsets(L.dp, dps, toff, yoff, soff, offsets_img, dps_stream));
     PCTC_HIP(launch_union_remap(targets, L.Y, blank, V, remap, u_ids, y_rel, Kdev, err, ws + L.o_ubits, dps_stream));
     g_pred = reinterpret_cast<float*>(ws + L.o_gpred);
-    int32_t* pred = reinterpret_cast<int32_t*>(ws + L.o_pred);
-    PCTC_HIP(launch_g_forecast(L.dp, dps, y_rel, nullptr, utt_weight, g_pred, pred, dps_stream));
+    // the lattice's set-up (per-utterance prep, which does not read S) with the forecast
+    PCTC_HIP(launch_ctc_dp(L.dp, input_lengths, target_lengths, S, L.ldS, y_rel, beam, utt_weight, loss_n, status,
+                           G, g, nullptr, dps, L.K_max, dps_stream, kDpPrep, true, g_pred,
+                           reinterpret_cast<int32_t*>(ws + L.o_pred)));
     if (dH || dW) {
       uint16_t* Hst = bwd_hst(bws, L.bwd);
       if (Hst)
@@ -513,10 +532,7 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
         PCTC_HIP(launch_hs_build_bf16(static_cast<const uint16_t*>(H), L.M, D, g_pred, bwd_hs(bws, L.bwd), dps_stream));
     }
     PCTC_HIP(launch_gather_s_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W), bias,
-                                  u_ids, Kdev, L.K_max, nullptr, nullptr, L.ldS, dps_stream, Zd));
-    // the lattice's set-up (zeroing of G and g, per-utterance prep), which does not read S
-    PCTC_HIP(launch_ctc_dp(L.dp, input_lengths, target_lengths, S, L.ldS, y_rel, beam, utt_weight, loss_n, status,
-                           G, g, nullptr, dps, L.K_max, dps_stream, nullptr, kDpPrep));
+                                  u_ids, Kdev, L.K_max, nullptr, nullptr, L.ldS, dps_stream, Zd, G));
     PCTC_HIP(hipEventRecord(ev.sel, dps_stream));
     // S = logits - lambda once both are done
     PCTC_HIP(hipStreamWaitEvent(stream, ev.sel, 0));
@@ -535,7 +551,7 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
     PCTC_HIP(launch_union_remap(targets, L.Y, blank, V, remap, u_ids, y_rel, Kdev, err, ws + L.o_ubits, stream));
     // online full-vocabulary log-sum-exp, then S = X W_U^T - lambda
     PCTC_HIP(launch_lse(dt, H, L.M, D, W, bias, V, partials, lam, lam2, stream));
-    PCTC_HIP(launch_gather_s(dt, H, L.M, D, W, bias, u_ids, Kdev, L.K_max, lam, S, L.ldS, stream));
+    PCTC_HIP(launch_gather_s(dt, H, L.M, D, W, bias, u_ids, Kdev, L.K_max, lam, S, L.ldS, stream, G));
   }
   // lattice, total scores, zeroing of nonfinite losses, G = dL/dS; then the loss and the
   // per-utterance outputs
@@ -557,13 +573,10 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
     static hipError_t run(void* p) {
       const DpTail& d = *static_cast<const DpTail*>(p);
       hipError_t e = launch_ctc_dp(*d.dp, d.T, d.U, d.S, d.ldS, d.y_rel, d.beam, d.weight, d.loss_n, d.status, d.G,
-                                   d.g, nullptr, d.dps, d.K_max, d.stream, nullptr, d.phase);
-      if (e == hipSuccess) e = launch_loss_reduce(d.N, d.loss_n, d.status, d.weight, d.loss, d.stream);
-      if (e == hipSuccess && d.loss_per_utt && d.N > 0)
-        e = hipMemcpyAsync(d.loss_per_utt, d.loss_n, d.N * sizeof(double), hipMemcpyDeviceToDevice, d.stream);
-      if (e == hipSuccess && d.utt_status && d.N > 0)
-        e = hipMemcpyAsync(d.utt_status, d.status, d.N * sizeof(int32_t), hipMemcpyDeviceToDevice, d.stream);
-      if (e == hipSuccess && d.pred) e = launch_forecast_check(d.N, d.status, d.weight, d.pred, d.fflag, d.stream);
+                                   d.g, nullptr, d.dps, d.K_max, d.stream, d.phase, true);
+      if (e == hipSuccess)
+        e = launch_dp_tail(d.N, d.loss_n, d.status, d.weight, d.pred, d.loss, d.loss_per_utt, d.utt_status, d.fflag,
+                           d.stream);
       return e;
     }
   } dpt{&L.dp, input_lengths, target_lengths, y_rel, S, L.ldS, L.K_max, N, beam, utt_weight, loss_n, loss,
@@ -579,7 +592,7 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
       static hipError_t run(void* p) {
         const DpTail& d = *static_cast<const DpTail*>(p);
         return launch_ctc_dp(*d.dp, d.T, d.U, d.S, d.ldS, d.y_rel, d.beam, d.weight, d.loss_n, d.status, d.G, d.g,
-                             nullptr, d.dps, d.K_max, d.stream, nullptr, d.phase);
+                             nullptr, d.dps, d.K_max, d.stream, d.phase);
       }
     };
     if (!defer_front) PCTC_HIP(FrontWork::run(&front));
@@ -627,6 +640,7 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
     side.stream = dps_stream;
     side.gate[0] = ev.gate0;
     side.gate[1] = ev.gate1;
+    side.eager = eager;
     side.dh_done = ev.dh_done;
     side.reduced = ev.join;
     if (defer_front) {
@@ -814,7 +828,7 @@ int32_t pctc_ctc_dp(const float* S, int32_t ldS, int32_t K_max, const int32_t* y
   std::vector<char> img;
   PCTC_HIP(upload_offsets(dp, dps, toff, yoff, soff, img, stream));
   PCTC_HIP(launch_ctc_dp(dp, input_lengths, target_lengths, S, ldS, y_rel, beam, nullptr, loss_per_utt, utt_status, G, g,
-                         keep_mask, dps, K_max, stream, nullptr));
+                         keep_mask, dps, K_max, stream));
   PCTC_HIP(hipStreamSynchronize(stream));
   prof_flush();
   return PCTC_OK;

@@ -62,7 +62,7 @@ hipError_t launch_lse_finalize(const float2* partials, int M, int P, double* lam
                                float* rowscale = nullptr, int32_t* einv = nullptr);
 hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W, const float* bias,
                            const int32_t* u_ids, const int32_t* K, int K_max, const double* lam, float* S, int ldS,
-                           hipStream_t stream);
+                           hipStream_t stream, float* Gz = nullptr);
 
 // ---- greedy emission head -----------------------------------------------------------------
 // partials: lse_partial_bytes(M, D); ids [M]; tokens [M] (utterance n at toff[n]); lengths [N].
@@ -124,6 +124,9 @@ struct BwdSide {
   SideWork front;
   hipEvent_t front_gate = nullptr;
   int nwork = 0;
+  // the lattice is longer than the dense part: no gates, work[0] enqueued before the first chunk and
+  // the rest right after it
+  bool eager = false;
   const float* dH_extra = nullptr;
   bool hs_built = false;
   DwExtra udw;  // the union columns' dW_u, folded into the last chunk's dW launch (dH wanted)
@@ -153,7 +156,8 @@ hipError_t launch_lse_partial_f32(const float* H, int M, int D, const float* W, 
 hipError_t launch_amax_partial_f32(const float* H, int M, int D, const float* W, const float* bias, int V,
                                    float2* partials, int* P_out, hipStream_t stream);
 hipError_t launch_gather_s_f32(const float* H, int M, int D, const float* W, const float* bias, const int32_t* u_ids,
-                               const int32_t* K, int K_max, const double* lam, float* S, int ldS, hipStream_t stream);
+                               const int32_t* K, int K_max, const double* lam, float* S, int ldS, hipStream_t stream,
+                               float* Gz = nullptr);
 hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const float* bias, int V, const float2* lam2,
                         const float* G, int ldG, const float* g, const int32_t* remap, float* dH, float* dW, float* db,
                         char* scratch, const BwdPlan& plan, hipStream_t stream);
@@ -161,11 +165,12 @@ hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const floa
 // ---- bf16 kernels on the direct-to-LDS engine (head_gemm_bf16.hip) ---------------------
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                    float2* partials, int* P_out, hipStream_t stream);
+// Gz (may be null): also Gz[m * ldS + j] = 0 for j < *K (the lattice's G, before it is written).
 // Zd (may be null): write the selected logits in double (Zd[m * ldS + j]) instead of S; lam
 // is then not read (launch_lse_finalize subtracts it).
 hipError_t launch_gather_s_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias,
                                 const int32_t* u_ids, const int32_t* K, int K_max, const double* lam, float* S, int ldS,
-                                hipStream_t stream, double* Zd = nullptr);
+                                hipStream_t stream, double* Zd = nullptr, float* Gz = nullptr);
 // One chunk of the recomputed backward: the recompute of dZ (when `recompute`), then the dH
 // and dW products it feeds.
 // The backward's first chunk when the normaliser wrote its dZ rows as E = exp(z) without the
@@ -247,30 +252,23 @@ DpPlan plan_dp(int N, const int32_t* T, const int32_t* U, float beam);
 // Uploads the host offsets into the scratch (async) and runs the whole lattice stage.
 // weight: device float [N] loss weights of the utterances, or null (all 1): G rows of
 // utterance n are -w_n gamma.
-// phase: kDpAll, or kDpFront (zeroing of G and g, prep, the Viterbi pass and the arc mask)
-// then kDpBack (the log-sum passes and the occupancies, G and g) on the same stream; kDpFront
-// may itself be split into kDpPrep (the zeroing and prep, which do not read S) and kDpVit.
-constexpr int kDpAll = 0, kDpFront = 1, kDpBack = 2, kDpPrep = 3, kDpVit = 4;
-// Longest utterance (frames) whose lattice front the two-stream schedule starts beside the first
-// chunk's dW product rather than at once.
-constexpr int kFrontDeferT = 512;
+// phase: kDpAll, or kDpPrep (prep, which does not read S), kDpVit (the Viterbi pass and the arc
+// mask) and kDpBack (the log-sum passes and the occupancies, G and g) in this order on the same
+// stream.  g_zeroed: G is zero already (else prep clears it).  g_pred [M], pred [N] (or null): prep
+// also writes the forecast of g that dp_tail checks: -w_n on utterances whose targets fit their
+// frames (and w_n != 0), else 0; pred[n] = 1/0.
+constexpr int kDpAll = 0, kDpBack = 2, kDpPrep = 3, kDpVit = 4;
 hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U, const float* S, int ldS,
                          const int32_t* y_rel, float beam, const float* weight, double* loss_n, int32_t* status,
                          float* G, float* g, uint8_t* keep_mask_out, void* scratch, int K_max, hipStream_t stream,
-                         void* host_staging, int phase = kDpAll);
+                         int phase = kDpAll, bool g_zeroed = false, float* g_pred = nullptr, int32_t* pred = nullptr);
 // delta [nbeams][N]: discarded posterior mass of each utterance at each beam (host beams).
 // Needs a plan made with a finite beam (the Viterbi tables and the arc mask).
 hipError_t launch_discarded_mass(const DpPlan& plan, const float* S, int ldS, const int32_t* y_rel, const float* beams,
                                  int nbeams, double* delta, void* scratch, int K_max, hipStream_t stream);
-hipError_t launch_loss_reduce(int N, const double* loss_n, const int32_t* status, const float* weight, double* loss,
-                              hipStream_t stream);
-// Forecast of g before the lattice runs: g_pred[m] = -w_n on utterances whose targets fit
-// their frames and whose normalisers are finite (and w_n != 0), else 0; pred[n] = 1/0.
-// Needs the offsets uploaded into the lattice scratch.
-hipError_t launch_g_forecast(const DpPlan& plan, void* scratch, const int32_t* y_rel, const double* lam,
-                             const float* weight, float* g_pred, int32_t* pred, hipStream_t stream);
-// flag[0] = 1 when the lattice's inclusions differ from the forecast.
-hipError_t launch_forecast_check(int N, const int32_t* status, const float* weight, const int32_t* pred,
-                                 int32_t* flag, hipStream_t stream);
+// loss, loss_out [N], status_out [N] (the last two may be null) and, with pred, flag[0] = 1 when
+// the lattice's inclusions differ from the forecast.
+hipError_t launch_dp_tail(int N, const double* loss_n, const int32_t* status, const float* weight, const int32_t* pred,
+                          double* loss, double* loss_out, int32_t* status_out, int32_t* flag, hipStream_t stream);
 
 }  // namespace pctc

@@ -174,3 +174,28 @@ def test_discarded_mass_wavefront_edges(U):
     ref = oracle.discarded_mass(S.astype(np.float64), y, T, Us, beams)
     # T float emission factors (2^-23 each, the same in both recursions)
     assert np.abs(got - ref).max() <= float(T[0]) * 2.0 ** -23
+
+
+# ---- union in one launch (small vocabularies) and in two ------------------------------------------
+
+@pytest.mark.parametrize("V", [2, 2047, 2048, 2049, 4096, 32_767, 32_768, 32_769])
+def test_union_block_edges(V):
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    rng = np.random.default_rng(V)
+    blank = int(rng.integers(0, V))
+    ids = rng.integers(0, V - 1, size=500)
+    ids = np.where(ids >= blank, ids + 1, ids)
+    ids[:3] = [v for v in (0, V - 1, (V - 1) // 2048 * 2048) if v != blank][0]  # a block's first or last class
+    y = torch.from_numpy(ids.astype(np.int32)).cuda()
+    out = prunedctc.union_remap(y, blank, V)
+    ref = oracle.union_remap(ids, np.array([ids.size]), blank=blank, V=V)
+    np.testing.assert_array_equal(out["u_ids"].cpu().numpy(), ref["u_ids"])
+    np.testing.assert_array_equal(out["remap"].cpu().numpy(), ref["remap"])
+    np.testing.assert_array_equal(out["y_rel"].cpu().numpy(), ref["y_rel"])
+    bad = y.clone()
+    bad[7] = V
+    with pytest.raises(prunedctc.PrunedCTCError) as err:
+        prunedctc.union_remap(bad, blank, V)
+    assert err.value.code == -2
