@@ -870,16 +870,17 @@ struct GemmMidA64 : Gemm<256, 256, 32, LL::KC, LL::MC, 4, WR, WC, true> {
     sl[5] = b3;
   }
 
-  template <int EXTRA, class Epi>
+  // init(t, acc) sets the accumulators before tile t's first product (zero by default).
+  template <int EXTRA, class Epi, class Init = typename Base::ZeroInit>
   __device__ static __forceinline__ void seq_aligned(const GOp& A, const GOp& B, int row0, int col0, int ntiles,
-                                                     int K, f32x16 (&acc)[FR][FC], Epi&& epi) {
+                                                     int K, f32x16 (&acc)[FR][FC], Epi&& epi, Init&& init = Init{}) {
     char* sl[6];
     stages(sl);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    Base::zero(acc);
     const int nk = K / 32;  // the caller guarantees K % 128 == 0
     if (nk <= 0 || ntiles <= 0) return;
+    init(0, acc);
     const int klimA = min(A.kmax, K), klimB = min(B.kmax, K);
     CA ca;
     CB cb;
@@ -930,12 +931,11 @@ struct GemmMidA64 : Gemm<256, 256, 32, LL::KC, LL::MC, 4, WR, WC, true> {
     group();
     for (int gi = 1; gi < ng; ++gi) group();
     epi(0, acc);
-    Base::zero(acc);
     for (int t = 1; t < ntiles; ++t) {
+      init(t, acc);
       relaxed_group();
       for (int gi = 1; gi < ng; ++gi) group();
       epi(t, acc);
-      Base::zero(acc);
     }
     wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt(0xC07F);

@@ -96,10 +96,19 @@ hipError_t launch_lam2(const double* lam, int M, float2* lam2, hipStream_t strea
 }
 
 hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                      float2* partials, double* lam, float2* lam2, hipStream_t stream) {
+                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht) {
   if (M <= 0) return hipSuccess;
   int P = 0;
-  hipError_t e = launch_lse_partials(dtype, H, M, D, W, bias, V, partials, &P, stream);
+  hipError_t e;
+  if (dtype == 1 && Ht) {
+    const int Mp = (M + 63) / 64 * 64;
+    e = launch_ht_build_bf16(static_cast<const uint16_t*>(H), M, D, nullptr, nullptr, Ht, Mp, stream);
+    if (e == hipSuccess)
+      e = launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, V,
+                                    partials, &P, nullptr, 0, 0, nullptr, stream, Ht, Mp);
+  } else {
+    e = launch_lse_partials(dtype, H, M, D, W, bias, V, partials, &P, stream);
+  }
   if (e != hipSuccess) return e;
   return launch_lse_finalize(partials, M, P, lam, lam2, nullptr, nullptr, nullptr, 0, stream);
 }
@@ -187,12 +196,18 @@ ctc_collapse_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__
 
 hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
                          const int32_t* toff, int N, int blank, float2* partials, int32_t* ids, int32_t* tokens,
-                         int32_t* lengths, hipStream_t stream) {
+                         int32_t* lengths, hipStream_t stream, uint16_t* Ht) {
   if (M > 0) {
     int Pfin;
-    hipError_t e =
+    hipError_t e;
+    const int Mp = (M + 63) / 64 * 64;
+    if (Ht) {
+      e = launch_ht_build_bf16(static_cast<const uint16_t*>(H), M, D, nullptr, nullptr, Ht, Mp, stream);
+      if (e != hipSuccess) return e;
+    }
+    e =
         dtype == 1 ? launch_amax_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W),
-                                              bias, V, partials, &Pfin, stream)
+                                              bias, V, partials, &Pfin, stream, Ht, Mp)
                    : launch_amax_partial_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V,
                                              partials, &Pfin, stream);
     if (e != hipSuccess) return e;

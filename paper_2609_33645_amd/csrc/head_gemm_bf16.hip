@@ -164,11 +164,12 @@ __device__ __forceinline__ void lse_e_update(const f32x16 (&a)[FR][FC], int j, f
 // exactly like lse_partial_bf16.  einv (the check flag) is cleared here, before the finalize
 // sets it.
 // HT: the frames come from Ht [D][Mp] (the transposed head input) instead of H [M][D].
-template <bool HT>
+// BIAS (HT, no E partitions): the accumulators start at b, which lies where E would be staged.
+template <bool HT, bool BIAS = false>
 __global__ void __launch_bounds__(512, 1)
 lse_partial_e_bf16(const uint16_t* __restrict__ H, const uint16_t* __restrict__ Ht, int Mp, int M, int D,
-                   const uint16_t* __restrict__ W, int V, int P, int vper, float2* __restrict__ partials,
-                   uint16_t* __restrict__ E, int epitch, int eparts, int32_t* __restrict__ einv) {
+                   const uint16_t* __restrict__ W, const float* __restrict__ bias, int V, int P, int vper,
+                   float2* __restrict__ partials, uint16_t* __restrict__ E, int epitch, int eparts, int32_t* __restrict__ einv) {
   using G = std::conditional_t<HT, GMidTW, GMid>;
   constexpr int FR = G::FR, FC = G::FC, TR = G::kBR, TC = G::kBC;
   static_assert(FR == 4 && FC == 2 && G::NW == 8 && TR == 256, "waves of 128 vocabulary rows x 64 frames");
@@ -178,7 +179,7 @@ lse_partial_e_bf16(const uint16_t* __restrict__ H, const uint16_t* __restrict__ 
   const int w = xcd_swz(blockIdx.x, gridDim.x);
   const int mt = w % nMt;
   const int p = w / nMt;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *einv = 0;
+  if (einv && blockIdx.x == 0 && threadIdx.x == 0) *einv = 0;
   if (p >= P) return;
   const int m0 = mt * TC;
   const int vbeg = p * vper;
@@ -201,9 +202,19 @@ lse_partial_e_bf16(const uint16_t* __restrict__ H, const uint16_t* __restrict__ 
       if (v0 + TR > vend) mask_rows_inf<FR, FC, G>(a, v0, vend, wave, lane);
       lse_tile_update<FR, FC, G>(a, run_max, run_sum);
     };
-    if constexpr (HT) G::template seq_aligned<0>(A, B, vbeg, m0, ntiles, D, acc, epi);
-    else G::run_seq(A, B, vbeg, m0, ntiles, D, st, acc, epi);
-  } else {
+    if constexpr (BIAS) {
+      float* const bsh = reinterpret_cast<float*>(stg_);
+      for (int r = tid; r < ntiles * TR; r += G::kThreads) bsh[r] = (vbeg + r < vend) ? bias[vbeg + r] : 0.f;
+      __syncthreads();
+      G::template seq_aligned<0>(A, B, vbeg, m0, ntiles, D, acc, epi, [&](int i, f32x16 (&a)[FR][FC]) {
+        bias_init<FR, FC, G>(a, bsh + i * TR, wave, lane);
+      });
+    } else if constexpr (HT) {
+      G::template seq_aligned<0>(A, B, vbeg, m0, ntiles, D, acc, epi);
+    } else {
+      G::run_seq(A, B, vbeg, m0, ntiles, D, st, acc, epi);
+    }
+  } else if constexpr (!BIAS) {
     const int wr = wave / (G::NW / 2), wc = wave % (G::NW / 2);
     const uint64_t zb = reinterpret_cast<uint64_t>(E + static_cast<int64_t>(m0) * epitch);
     const uint64_t zbu =
@@ -259,11 +270,14 @@ lse_partial_e_bf16(const uint16_t* __restrict__ H, const uint16_t* __restrict__ 
 // ---------------------------------------------------------------------------------------
 template <class G, bool BIAS, int OCC>
 __global__ void __launch_bounds__(G::kThreads, OCC)
-amax_partial_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* __restrict__ W,
-                  const float* __restrict__ bias, int V, int P, int vper, float2* __restrict__ partials) {
+amax_partial_bf16(const uint16_t* __restrict__ H, const uint16_t* __restrict__ Ht, int Mp, int M, int D,
+                  const uint16_t* __restrict__ W, const float* __restrict__ bias, int V, int P, int vper,
+                  float2* __restrict__ partials) {
   extern __shared__ float bsh[];  // BIAS: b over this partition's rows
   constexpr int FR = G::FR, FC = G::FC, TR = G::kBR, TC = G::kBC;
+  constexpr bool HT = std::is_same_v<G, GMidTW>;  // frames from Ht [D][Mp], as the normaliser's
   PCTC_STAGES_G(G)
+  __shared__ char xch_[HT ? 4096 : 16];
   const int nMt = (M + TC - 1) / TC;
   int mt, p;
   if (!grouped_tile(xcd_swz(blockIdx.x, gridDim.x), nMt, P, mt, p)) return;
@@ -277,7 +291,7 @@ amax_partial_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* 
     __syncthreads();
   }
   const GOp A{W, D, vend, D, nullptr};
-  const GOp B{H, D, M, D, nullptr};
+  const GOp B = HT ? GOp{Ht, Mp, M, D, nullptr} : GOp{H, D, M, D, nullptr};
   float bv[FC];
   int bi[FC];
 #pragma unroll
@@ -291,13 +305,13 @@ amax_partial_bf16(const uint16_t* __restrict__ H, int M, int D, const uint16_t* 
     if (v0 + TR > vend) mask_rows_inf<FR, FC, G>(a, v0, vend, wave, lane);  // -inf never replaces the best
     amax_tile_update<FR, FC, G>(a, v0, wave, lane, bv, bi);
   };
-  if (BIAS)
-    G::run_seq(A, B, vbeg, m0, ntiles, D, st, acc, epi, [&](int it, f32x16 (&a)[FR][FC]) {
-      bias_init<FR, FC, G>(a, bsh + it * TR, wave, lane);
-    });
-  else
-    G::run_seq(A, B, vbeg, m0, ntiles, D, st, acc, epi);
-  amax_store_partials<G>(bv, bi, st0_, wave, lane, m0, M, partials + static_cast<int64_t>(p) * M);
+  auto init = [&](int it, f32x16 (&a)[FR][FC]) {
+    if constexpr (BIAS) bias_init<FR, FC, G>(a, bsh + it * TR, wave, lane);
+    else G::zero(a);
+  };
+  if constexpr (HT) G::template seq_aligned<0>(A, B, vbeg, m0, ntiles, D, acc, epi, init);
+  else G::run_seq(A, B, vbeg, m0, ntiles, D, st, acc, epi, init);
+  amax_store_partials<G>(bv, bi, HT ? xch_ : st0_, wave, lane, m0, M, partials + static_cast<int64_t>(p) * M);
 }
 
 __global__ void __launch_bounds__(256, 2)
@@ -1119,28 +1133,34 @@ hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16
   return hipGetLastError();
 }
 
+// The argmax's frames come from H transposed (Ht, lse_ht_bytes_bf16) for narrow heads of more than two
+// frame tiles: below that the transpose's launch costs what its whole lines save (150 frames 46 us
+// either way; 4,347 frames, D = 512, V = 180,000: 767 -> 727 us).
+bool amax_reads_ht_bf16(int M, int D) { return M > 512 && lse_ht_bytes_bf16(M, D) > 0; }
+
 hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
-                                    float2* partials, int* P_out, hipStream_t stream) {
+                                    float2* partials, int* P_out, hipStream_t stream, const uint16_t* Ht, int Mp) {
   const LseSplit sp = lse_split_bf16(M, D, V);
   const int vper = sp.vper, Peff = sp.P;
   *P_out = Peff;
   Prof pr("amax_partial", stream);
   const size_t bsh = bias ? static_cast<size_t>(vper) * sizeof(float) : 0;
   const dim3 grid(grouped_grid(sp.nM, Peff));
+#define PCTC_AMAX(G)                                                                                               \
+  if (bias)                                                                                                        \
+    hipLaunchKernelGGL((amax_partial_bf16<G, true, 1>), grid, dim3(G::kThreads), bsh, stream, H, Ht, Mp, M, D, W,  \
+                       bias, V, Peff, vper, partials);                                                             \
+  else                                                                                                             \
+    hipLaunchKernelGGL((amax_partial_bf16<G, false, 1>), grid, dim3(G::kThreads), 0, stream, H, Ht, Mp, M, D, W,   \
+                       bias, V, Peff, vper, partials);
   if (sp.wide) {
-    if (bias)
-      hipLaunchKernelGGL((amax_partial_bf16<GWide, true, 1>), grid, dim3(GWide::kThreads), bsh, stream, H, M, D, W,
-                         bias, V, Peff, vper, partials);
-    else
-      hipLaunchKernelGGL((amax_partial_bf16<GWide, false, 1>), grid, dim3(GWide::kThreads), 0, stream, H, M, D, W,
-                         bias, V, Peff, vper, partials);
-  } else if (bias) {
-    hipLaunchKernelGGL((amax_partial_bf16<GMid, true, 1>), grid, dim3(GMid::kThreads), bsh, stream, H, M, D, W, bias,
-                       V, Peff, vper, partials);
+    PCTC_AMAX(GWide)
+  } else if (Ht) {
+    PCTC_AMAX(GMidTW)
   } else {
-    hipLaunchKernelGGL((amax_partial_bf16<GMid, false, 1>), grid, dim3(GMid::kThreads), 0, stream, H, M, D, W, bias,
-                       V, Peff, vper, partials);
+    PCTC_AMAX(GMid)
   }
+#undef PCTC_AMAX
   return hipGetLastError();
 }
 
@@ -1251,19 +1271,35 @@ int lse_e_parts_bf16(int M, int D, int V, int chunk) {
   return ep < sp.P ? ep : sp.P;
 }
 
-hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, int V, float2* partials,
-                                     int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
+hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
+                                     float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
                                      hipStream_t stream, const uint16_t* Ht, int Mp) {
   const LseSplit sp = lse_split_bf16(M, D, V);
   *P_out = sp.P;
+  const dim3 grid(sp.nM * sp.P), block(GMid::kThreads);
   Prof pr("lse_partial", stream);
-  if (Ht)
-    hipLaunchKernelGGL(lse_partial_e_bf16<true>, dim3(sp.nM * sp.P), dim3(GMid::kThreads), 0, stream, H, Ht, Mp, M, D,
-                       W, V, sp.P, sp.vper, partials, E, epitch, eparts, einv);
-  else
-    hipLaunchKernelGGL(lse_partial_e_bf16<false>, dim3(sp.nM * sp.P), dim3(GMid::kThreads), 0, stream, H, Ht, Mp, M,
-                       D, W, V, sp.P, sp.vper, partials, E, epitch, eparts, einv);
+  if (bias) {
+    // the partition's bias takes the 32 KB that E is staged through
+    if (!Ht || eparts > 0 || sp.vper * sizeof(float) > 32768) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((lse_partial_e_bf16<true, true>), grid, block, 0, stream, H, Ht, Mp, M, D, W, bias, V, sp.P,
+                       sp.vper, partials, E, epitch, 0, einv);
+  } else if (Ht) {
+    hipLaunchKernelGGL((lse_partial_e_bf16<true>), grid, block, 0, stream, H, Ht, Mp, M, D, W, bias, V, sp.P, sp.vper,
+                       partials, E, epitch, eparts, einv);
+  } else {
+    hipLaunchKernelGGL((lse_partial_e_bf16<false>), grid, block, 0, stream, H, Ht, Mp, M, D, W, bias, V, sp.P, sp.vper,
+                       partials, E, epitch, eparts, einv);
+  }
   return hipGetLastError();
+}
+
+// Bytes of H transposed [D][Mp] for the normaliser's and the argmax's calls outside the fused one,
+// 0 where they do not read it: k-tile groups are 128 deep, wide heads have their own tiles, and a
+// transposed H of 2 GiB or more would not be addressed with 32-bit byte offsets.
+size_t lse_ht_bytes_bf16(int M, int D) {
+  if (M <= 0 || D >= kWideD || D % 128 != 0) return 0;
+  if (static_cast<size_t>(D) * (M + 63) * sizeof(uint16_t) >= (1ull << 31)) return 0;
+  return align_up(static_cast<size_t>(D) * ((M + 63) / 64 * 64) * sizeof(uint16_t), 256);
 }
 
 hipError_t launch_ht_build_bf16(const uint16_t* H, int M, int D, const float* g, uint16_t* Hs, uint16_t* Ht, int Mp,

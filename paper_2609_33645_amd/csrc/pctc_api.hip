@@ -500,16 +500,17 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
       uint16_t* Ht = L.o_ht ? reinterpret_cast<uint16_t*>(ws + L.o_ht) : nullptr;
       if (Ht)
         PCTC_HIP(launch_ht_build_bf16(static_cast<const uint16_t*>(H), L.M, D, nullptr, nullptr, Ht, L.bwd.Mp, stream));
-      PCTC_HIP(launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W), V,
-                                         partials, &P, reinterpret_cast<uint16_t*>(bws), L.bwd.chunk, L.eparts, einv,
-                                         stream, Ht, L.bwd.Mp));
-    } else if (dt == 1 && !bias && L.o_ht) {
-      // no E rows: the same kernel with none of its partitions writing them, frames from H^T
+      PCTC_HIP(launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W),
+                                         nullptr, V, partials, &P, reinterpret_cast<uint16_t*>(bws), L.bwd.chunk,
+                                         L.eparts, einv, stream, Ht, L.bwd.Mp));
+    } else if (dt == 1 && L.o_ht && (!bias || D < kWideD)) {
+      // no E rows (a bias, db or no room): the same kernel with none of its partitions writing
+      // them, frames from H^T
       uint16_t* Ht = reinterpret_cast<uint16_t*>(ws + L.o_ht);
       PCTC_HIP(launch_ht_build_bf16(static_cast<const uint16_t*>(H), L.M, D, nullptr, nullptr, Ht, L.bwd.Mp, stream));
-      PCTC_HIP(launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W), V,
-                                         partials, &P, reinterpret_cast<uint16_t*>(bws), L.bwd.chunk, 0, einv, stream,
-                                         Ht, L.bwd.Mp));
+      PCTC_HIP(launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W),
+                                         bias, V, partials, &P, reinterpret_cast<uint16_t*>(bws), L.bwd.chunk, 0,
+                                         einv, stream, Ht, L.bwd.Mp));
     } else {
       PCTC_HIP(launch_lse_partials(dt, H, L.M, D, W, bias, V, partials, &P, stream));
     }
@@ -782,7 +783,8 @@ int32_t pctc_union_remap(const int32_t* targets, int32_t total_targets, int32_t 
 
 size_t pctc_lse_scratch_bytes(int32_t M, int32_t D) {
   return (M < 0 || D <= 0 || D > PCTC_MAX_DIM) ? 0
-                           : lse_partial_bytes(M, D) + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(float2), 256);
+                           : lse_partial_bytes(M, D) + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(float2), 256) +
+                                 lse_ht_bytes_bf16(M, D);
 }
 
 int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, const void* W, int32_t V,
@@ -793,9 +795,13 @@ int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, c
     return PCTC_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
   const int dt = (dtype == PCTC_BF16) ? 1 : 0;
-  // scratch = [partials][lam2]
   float2* lam2 = reinterpret_cast<float2*>(static_cast<char*>(partials) + lse_partial_bytes(M, D));
-  PCTC_HIP(launch_lse(dt, H, M, D, W, nullptr, V, static_cast<float2*>(partials), lam, lam2, stream));
+  // scratch: [partials][lam2][H transposed]
+  uint16_t* Ht = (dt == 1 && lse_ht_bytes_bf16(M, D))
+                     ? reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(lam2) +
+                                                   align_up(static_cast<size_t>(M) * sizeof(float2), 256))
+                     : nullptr;
+  PCTC_HIP(launch_lse(dt, H, M, D, W, nullptr, V, static_cast<float2*>(partials), lam, lam2, stream, Ht));
   if (S && u_ids && K) PCTC_HIP(launch_gather_s(dt, H, M, D, W, nullptr, u_ids, K, K_max, lam, S, ldS, stream));
   PCTC_HIP(hipStreamSynchronize(stream));
   prof_flush();
@@ -834,18 +840,19 @@ int32_t pctc_ctc_dp(const float* S, int32_t ldS, int32_t K_max, const int32_t* y
   return PCTC_OK;
 }
 
-// Greedy decode workspace: argmax partials, frame offsets, and the ids when not returned.
-static size_t greedy_layout(int32_t N, int32_t M, int32_t D, size_t* o_toff, size_t* o_ids) {
+// Greedy decode workspace: argmax partials, frame offsets, the ids when not returned, H transposed.
+static size_t greedy_layout(int32_t N, int32_t M, int32_t D, size_t* o_toff, size_t* o_ids, size_t* o_ht) {
   const size_t part = lse_partial_bytes(M > 0 ? M : 1, D);
   *o_toff = part;
   *o_ids = part + align_up(static_cast<size_t>(N + 1) * sizeof(int32_t), 256);
-  return *o_ids + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(int32_t), 256);
+  *o_ht = *o_ids + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(int32_t), 256);
+  return *o_ht + (amax_reads_ht_bf16(M, D) ? lse_ht_bytes_bf16(M, D) : 0);
 }
 
 size_t pctc_greedy_workspace_size(int32_t N, int32_t M, int32_t D) {
   if (N < 0 || M < 0 || D <= 0 || D > PCTC_MAX_DIM) return 0;
-  size_t a, b;
-  return greedy_layout(N, M, D, &a, &b);
+  size_t a, b, c;
+  return greedy_layout(N, M, D, &a, &b, &c);
 }
 
 int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const void* W, const float* bias, int32_t V,
@@ -863,8 +870,8 @@ int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const voi
   if (M64 > INT32_MAX) return PCTC_EINVAL;
   const int M = static_cast<int>(M64);
   if (M > 0 && (!H || !tokens || !token_lengths)) return PCTC_EINVAL;
-  size_t o_toff, o_ids;
-  const size_t need = greedy_layout(N, M, D, &o_toff, &o_ids);
+  size_t o_toff, o_ids, o_ht;
+  const size_t need = greedy_layout(N, M, D, &o_toff, &o_ids, &o_ht);
   if (!workspace || workspace_bytes < need) return PCTC_EWORKSPACE;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return PCTC_EINVAL;
   if (N == 0) return PCTC_OK;
@@ -876,7 +883,9 @@ int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const voi
   PCTC_HIP(hipMemcpyAsync(dtoff, toff.data(), (N + 1) * sizeof(int32_t), hipMemcpyHostToDevice, stream));
   int32_t* idv = ids ? ids : reinterpret_cast<int32_t*>(ws + o_ids);
   PCTC_HIP(launch_greedy(dtype == PCTC_BF16 ? 1 : 0, H, M, D, W, bias, V, dtoff, N, blank,
-                         reinterpret_cast<float2*>(ws), idv, tokens, token_lengths, stream));
+                         reinterpret_cast<float2*>(ws), idv, tokens, token_lengths, stream,
+                         dtype == PCTC_BF16 && amax_reads_ht_bf16(M, D) ? reinterpret_cast<uint16_t*>(ws + o_ht)
+                                                                        : nullptr));
   PCTC_HIP(hipStreamSynchronize(stream));  // the host offsets must outlive the copy
   prof_flush();
   return PCTC_OK;
@@ -973,11 +982,11 @@ int32_t pctc_head_bwd(pctc_dtype dtype, const void* H, int32_t M, int32_t D, con
 }
 
 // Grouped logits: one workspace serves both directions.
-//   [small 256 B][remap V][ forward: partials | lse_O | lam2 | zero | complement bias ]
+//   [small 256 B][remap V][ forward: partials | lse_O | lam2 | zero | complement bias | H^T ]
 //                         [ backward: G M x K | g | lam2 | recomputed-backward scratch ]
 struct GroupedLayout {
   BwdPlan plan;
-  size_t o_remap, o_part, o_lamo, o_lam2f, o_zero, o_bo, o_G, o_g, o_lam2b, o_bwd, total;
+  size_t o_remap, o_part, o_lamo, o_lam2f, o_zero, o_bo, o_ht, o_G, o_g, o_lam2b, o_bwd, total;
 };
 static GroupedLayout grouped_layout(int dt, int M, int D, int V, int K, int chunk) {
   GroupedLayout L;
@@ -989,7 +998,8 @@ static GroupedLayout grouped_layout(int dt, int M, int D, int V, int K, int chun
   L.o_lam2f = L.o_lamo + m8;
   L.o_zero = L.o_lam2f + m8;
   L.o_bo = L.o_zero + m8;
-  const size_t fwd_end = L.o_bo + align_up(static_cast<size_t>(V) * 4, 256);
+  L.o_ht = L.o_bo + align_up(static_cast<size_t>(V) * 4, 256);
+  const size_t fwd_end = L.o_ht + (dt == 1 ? lse_ht_bytes_bf16(M, D) : 0);
   L.o_G = L.o_part;
   L.o_g = L.o_G + align_up(static_cast<size_t>(M) * K * 4, 256);
   L.o_lam2b = L.o_g + align_up(static_cast<size_t>(M > 0 ? M : 1) * 4, 256);
@@ -1042,7 +1052,8 @@ int32_t pctc_grouped_logprobs(pctc_dtype dtype, const void* H, int32_t M, int32_
     // the complement's log-sum-exp: the normaliser pass with the selected rows masked out
     PCTC_HIP(launch_grouped_comp_bias(bias, remap, V, bo, stream));
     PCTC_HIP(launch_lse(dt, H, M, D, W, bo, V, reinterpret_cast<float2*>(ws + L.o_part), lse_o,
-                        reinterpret_cast<float2*>(ws + L.o_lam2f), stream));
+                        reinterpret_cast<float2*>(ws + L.o_lam2f), stream,
+                        dt == 1 && lse_ht_bytes_bf16(M, D) ? reinterpret_cast<uint16_t*>(ws + L.o_ht) : nullptr));
   } else {
     PCTC_HIP(launch_fill_d(lse_o, M, -INFINITY, stream));
   }

@@ -46,8 +46,10 @@ constexpr int kMaxLseParts = 1024;
 inline int lse_max_parts(int D) { return D >= kWideD ? kMaxLseParts : 256; }
 size_t lse_partial_bytes(int M, int D);
 // bias: device float [V] or null (logits H W^T + b).
+// Ht (null: none): lse_ht_bytes_bf16(M, D) bytes of scratch for H transposed, from which the bf16
+// normaliser reads its frames in whole lines.
 hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                      float2* partials, double* lam, float2* lam2, hipStream_t stream);
+                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht = nullptr);
 // The same in two halves: the partial (max, sum) pairs over the vocabulary partitions
 // (P_out: partitions written), then lambda and its hi/lo pair from them; with Zd the second
 // half also writes S[m * ldS + j] = float(Zd[m * ldS + j] - lambda_m) for j < *K.
@@ -65,12 +67,14 @@ hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W
                            hipStream_t stream, float* Gz = nullptr);
 
 // ---- greedy emission head -----------------------------------------------------------------
+// Ht: scratch of lse_ht_bytes_bf16(M, D) where amax_reads_ht_bf16 (bf16), else null.
 // partials: lse_partial_bytes(M, D); ids [M]; tokens [M] (utterance n at toff[n]); lengths [N].
 hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
                          const int32_t* toff, int N, int blank, float2* partials, int32_t* ids, int32_t* tokens,
-                         int32_t* lengths, hipStream_t stream);
+                         int32_t* lengths, hipStream_t stream, uint16_t* Ht);
+bool amax_reads_ht_bf16(int M, int D);
 hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
-                                    float2* partials, int* P_out, hipStream_t stream);
+                                    float2* partials, int* P_out, hipStream_t stream, const uint16_t* Ht, int Mp);
 
 // A second operand set for a dW product's launch: out[v][:] = sum over frames of Z[m][v] Hs[m][:]
 // for v < cols (cut to 2 *kdev when kdev is set), Z [M][ld] bf16.  The union columns' dW_u
@@ -192,12 +196,14 @@ hipError_t launch_bwd_chunk_bf16(const uint16_t* Hs, int M, int D, const uint16_
 // Partitions of the normaliser that can write E for a first chunk of `chunk` columns (0: none;
 // narrow heads with D a multiple of 128, chunk a multiple of the partition width).
 int lse_e_parts_bf16(int M, int D, int V, int chunk);
-// The normaliser (no bias) that also writes E = exp(z) in bf16 at E[m * epitch + v] for the
+// The normaliser that also writes E = exp(z) in bf16 at E[m * epitch + v] for the
 // rows of its first eparts partitions, and clears *einv (see launch_lse_finalize).  With Ht
 // (H transposed, [D][Mp], from launch_ht_build_bf16) the frames are read from there.
-hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, int V, float2* partials,
-                                     int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
+// With bias (float [V]; needs Ht, eparts 0) the logits include it.
+hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
+                                     float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
                                      hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0);
+size_t lse_ht_bytes_bf16(int M, int D);
 // rowscale/Hp of ChunkE from the finalize's s_m (in rowscale) and its check flag.
 hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t* einv, float* rowscale, uint16_t* Hp,
                                 hipStream_t stream);

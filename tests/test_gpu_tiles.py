@@ -199,3 +199,39 @@ def test_union_block_edges(V):
     with pytest.raises(prunedctc.PrunedCTCError) as err:
         prunedctc.union_remap(bad, blank, V)
     assert err.value.code == -2
+
+
+# ---- frames from H transposed: argmax and normaliser with bias -------------------------------------
+
+@pytest.mark.parametrize("M,V,bias", [(513, 2000, False), (700, 2305, True), (512, 300, True)])
+def test_greedy_transposed_frames(M, V, bias):
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("bf16", [M], 256, V, M + V, u_frac=0.0)
+    H, W, _ = to_dev(wl)
+    b = np.random.default_rng(1).standard_normal(V).astype(np.float32) if bias else np.zeros(V, np.float32)
+    ids = prunedctc.greedy_decode(H, W, [M], bias=torch.from_numpy(b).cuda() if bias else None)["ids"].cpu().numpy()
+    Z = wl.H.astype(np.float64) @ wl.W.astype(np.float64).T + b
+    top = Z.max(1)
+    # the products' rounding (fp32 sums of 256 products) may pick another class within it
+    assert np.all(Z[np.arange(M), ids] >= top - 1e-5 * np.abs(top))
+
+
+@pytest.mark.parametrize("M,D,V", [(70, 128, 700), (300, 256, 2049), (33, 72, 300), (260, 2048, 513)])
+def test_grouped_bias_normaliser(M, D, V):
+    """The complement's normaliser with its -inf bias (frames from H transposed where D is a multiple
+    of 128 and below the wide heads)."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("bf16", [M], D, V, M + D, u_frac=0.0)
+    H, W, _ = to_dev(wl)
+    g = np.random.default_rng(D)
+    u = np.concatenate([[0], 1 + np.sort(g.choice(V - 1, 20, replace=False))]).astype(np.int32)
+    b = torch.from_numpy(g.standard_normal(V).astype(np.float32)).cuda()
+    ud = torch.from_numpy(u).cuda()
+    f = prunedctc.grouped_logprobs(H, W, ud, b)
+    ref = oracle.grouped_logprobs(wl.H, wl.W, u, bias=b.cpu().numpy())
+    assert np.abs(f["lam"].cpu().numpy() - ref["lam"]).max() < 2e-5
+    assert np.abs(f["logp"].cpu().numpy() - ref["logp"]).max() < 5e-5
