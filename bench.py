@@ -25,14 +25,16 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 matrix-core peak
-PEAK_F32_TFLOPS = 157.3     # MI355X fp32 matrix/vector peak
+# fp32 heads run on the bf16 matrix cores, six bf16 products for one of fp32 (the fp32 units
+# themselves peak at 157.3)
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0
 
 # every matrix-product kernel of the fused step: the dense products, the selected-logit product
 # and the union-column part's two products (their event times include any wait for free
 # compute units beside the dense part, so the fraction below is a lower bound)
-GEMM_KERNELS = ("lse_partial", "recompute_dz", "recompute_check", "dh_gemm", "dw_gemm", "gather_s", "union_dh",
-                "union_dw")
+GEMM_KERNELS = ("lse_partial", "recompute_dz", "recompute_check", "dh_gemm", "dw_gemm", "products", "gather_s",
+                "union_dh", "union_dw")
 
 
 def parse():
@@ -231,8 +233,9 @@ def bench_extra(a):
         def step():
             e = prunedctc.grouped_logprobs(H, W, uid)
             prunedctc.grouped_backward(H, W, uid, e["logp"], e["lam"], dl, chunk=a.chunk)
-        kernels = ("lse_partial", "recompute_dz", "dh_gemm", "dw_gemm")
-        flops = {k: 2.0 * M * V * D for k in kernels}
+        kernels = ("lse_partial", "recompute_dz", "dh_gemm", "dw_gemm", "products")
+        # fp32 heads: dH and dW of a chunk in one launch ("products")
+        flops = {k: (4.0 if k == "products" else 2.0) * M * V * D for k in kernels}
         metric = "frames/sec grouped-logit export fwd + bwd (stock-CTC interface) at V=180K"
         del ex
     else:
@@ -373,12 +376,14 @@ def main():
     # backward chunk's gradient rows itself where pctc_normaliser_chunk_columns says so (the
     # recompute then covers V - ecols columns; its guard launch, "recompute_check", only
     # recomputes when some lambda leaves the range that allows it, which no workload here does).
-    # The union-column products run on G split into bf16 hi and lo halves (2 K columns).
+    # The union-column products (bf16 heads) run on G split into bf16 hi and lo halves (2 K columns).
     ecols = prunedctc.normaliser_chunk_columns(1 if wl.dtype == "bf16" else 0, T, U, D, V, wl.beam, a.chunk,
                                                not a.frozen_head)
     gemm_flops = {"lse_partial": 2.0 * M * V * D, "recompute_dz": 2.0 * M * (V - ecols) * D,
                   "recompute_check": 0.0, "dh_gemm": 2.0 * M * V * D,
                   "dw_gemm": 0.0 if a.frozen_head else 2.0 * M * V * D, "gather_s": 2.0 * M * K * D,
+                  # fp32 heads: both of a chunk's gradient products in one launch
+                  "products": (2.0 if a.frozen_head else 4.0) * M * V * D,
                   "union_dh": 2.0 * M * 2 * K * D, "union_dw": 0.0 if a.frozen_head else 2.0 * M * 2 * K * D}
     kernel_ms = {k: v["total_ms"] / a.steps for k, v in prof.items()}
     launches = {k: v["launches"] / a.steps for k, v in prof.items()}
