@@ -213,7 +213,8 @@ int32_t pctc_union_remap(const int32_t* targets, int32_t total_targets, int32_t 
  * with the subtraction in double and one rounding to float, for j < K (K read from the
  * device scalar), S row pitch ldS >= K_max.  K_max bounds K (1 + total targets).
  * partials: device scratch of pctc_lse_scratch_bytes(M, D) bytes (8 bytes per frame and
- * vocabulary partition: 256 partitions, 1024 for D >= 2048; independent of V).  Returns 0
+ * vocabulary partition: 256 partitions, 1024 for D >= 2048; independent of V; H transposed
+ * uses what the partitions of this V leave).  Returns 0
  * for M < 0 or D <= 0. */
 size_t pctc_lse_scratch_bytes(int32_t M, int32_t D);
 int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, const void* W,

@@ -262,8 +262,9 @@ hipError_t launch_dh_reduce(const float* part, int splits, int64_t n, const floa
   return hipGetLastError();
 }
 
-BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
+BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk, bool lean) {
   BwdPlan p{};
+  p.lean = lean;
   int cap;  // columns the gradient buffer holds (sizes the workspace; independent of V)
   if (chunk > 0) {
     // a step never needs more columns than the vocabulary has (rounded up to whole tiles)
@@ -285,7 +286,8 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
     if (dtype == 1 && D < kWideD) {
       // narrow bf16 heads: whole normaliser partitions, so that the first chunk's dZ rows can
       // come from the normaliser (lse_partial_e_bf16)
-      const size_t al = static_cast<size_t>(lse_part_columns_bf16(M, D, V));
+      size_t al = static_cast<size_t>(lse_part_columns_bf16(M, D, V));
+      if (2048 % al == 0) al = 2048;  // whole partitions of every number of frames that has such runs
       size_t n2 = n, c2 = ((v + n2 - 1) / n2 + al - 1) / al * al;
       while (c2 > cmax && c2 > al) {
         ++n2;
@@ -297,7 +299,8 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
     cap = static_cast<int>(cmax);
   }
   const size_t es = (dtype == 1) ? 2 : 4;
-  p.wsplits = 1;
+  p.splits = p.wsplits = 1;
+  int room = 0;  // slices the partial buffer has room for, if more than p.splits
   if (dtype == 1) {
     const int tiles = ((M + 255) / 256) * ((D + 255) / 256);
     // k-slices of the dH product (one workgroup per CU): when the tiles alone make less than
@@ -319,11 +322,14 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
       }
       if (fill >= 0.9) break;
     }
-    if (tiles * maxs < 256 && p.chunk > 256 * maxs) {
+    if (!lean && tiles * maxs < 256 && p.chunk > 256 * maxs) {
       // few frames: eight slices leave most of the chip idle (331 frames, D = 512, chunks of
       // 60,000 columns: 16 or 32 workgroups, 160 us a launch).  The count whose launch is
       // shortest by 0.7 us a 32-deep k-tile and 4 us a workgroup, with every slice's partial sums
-      // read and written at 3 TB/s; at most 32 slices and 32 MiB of them (there 32: 60 us)
+      // read and written at 3 TB/s; at most 32 slices and 32 MiB of them (there 32: 60 us).  The
+      // buffer holds the most slices of any vocabulary: its size does not grow with V
+      room = std::min(32, static_cast<int>(32.0 * 1024 * 1024 / (static_cast<double>(M) * D * sizeof(float))));
+      room = std::min(room, cap / 256);
       double best_t = -1;
       for (int sp = maxs; sp <= 32 && sp * 256 <= p.chunk; ++sp) {
         const double bytes = static_cast<double>(sp) * M * D * sizeof(float);
@@ -337,18 +343,20 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk) {
       }
     }
     p.splits = splits;
-  } else {
+  } else if (!lean) {
     plan_products_f32(M, D, p.chunk < V ? p.chunk : V, &p.splits, &p.wsplits);
   }
   p.Mp = ((M + 63) / 64) * 64;
   p.dz_bytes = align_up(static_cast<size_t>(M) * cap * es, 256);
   p.ht_bytes = align_up(static_cast<size_t>(D) * p.Mp * es, 256);  // >= M x D (bf16 masked copy of H)
   // a single slice: the dH product accumulates in the caller's dH (no partial buffer)
-  p.part_bytes = p.splits == 1 ? 0 : align_up(static_cast<size_t>(p.splits) * M * D * sizeof(float), 256);
+  p.part_bytes =
+      p.splits == 1 ? 0 : align_up(static_cast<size_t>(std::max(p.splits, room)) * M * D * sizeof(float), 256);
   p.lam2_bytes = align_up(static_cast<size_t>(M) * sizeof(float2), 256);
   // column sums of dZ for db, per 128-frame tile (bf16) or frame slice (fp32)
   p.dbpart_bytes =
-      align_up((dtype == 1 ? static_cast<size_t>((M + 127) / 128) * cap : static_cast<size_t>(kDbSlicesF32) * p.chunk) *
+      align_up((dtype == 1 ? static_cast<size_t>((M + 127) / 128) * cap
+                           : (lean ? 0 : static_cast<size_t>(kDbSlicesF32) * p.chunk)) *
                    sizeof(float), 256);
   // narrow bf16 heads: the dense recompute reads its frames from Hs transposed (whole k-lines)
   p.hst_bytes = (dtype == 1 && D < kWideD && D % 128 == 0) ? align_up(static_cast<size_t>(D) * p.Mp * 2, 256) : 0;

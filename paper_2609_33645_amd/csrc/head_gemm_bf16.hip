@@ -1112,6 +1112,7 @@ static LseSplit lse_split_bf16(int M, int D, int V) {
 }
 
 int lse_part_columns_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V).vper; }
+int lse_parts_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V).P; }
 
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                    float2* partials, int* P_out, hipStream_t stream) {

@@ -382,7 +382,7 @@ hs_build_f32(const float* __restrict__ H, int64_t n, int D, const float* __restr
 // columns walking all frames took 6.0 ms at M = 16,000, V = 5,000 (a 16,000-load serial chain
 // on 20 workgroups).
 __global__ void __launch_bounds__(256)
-db_colsum_f32(const float* __restrict__ dZ, int M, int chunk, int mper, float* __restrict__ dbpart) {
+db_colsum_f32(const float* dZ, int M, int chunk, int mper, float* dbpart) {  // dbpart may be dZ (one slice)
   __shared__ float4 x[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int v = blockIdx.x * 256 + lane * 4;  // the chunk's pitch is a multiple of 256
@@ -551,13 +551,14 @@ hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const floa
         hipLaunchKernelGGL(recompute_dz_f32<false>, grid, dim3(512), 0, stream, H, M, D, W, bias, c0, cw, lam2, G, ldG,
                            g, remap, dZ, chunk);
     }
-    if (db) {
-      const int mper = ((M + kDbSlicesF32 - 1) / kDbSlicesF32 + 3) / 4 * 4;
+    auto col_sums = [&](int maxs, float* sums) {
+      const int mper = ((M + maxs - 1) / maxs + 3) / 4 * 4;
       const int slices = (M + mper - 1) / mper;
       Prof pr("db_colsum", stream);
-      hipLaunchKernelGGL(db_colsum_f32, dim3(nVt, slices), dim3(256), 0, stream, dZ, M, chunk, mper, dbpart);
-      hipLaunchKernelGGL(db_reduce_f32, dim3(nVt), dim3(256), 0, stream, dbpart, slices, chunk, cw, db + c0);
-    }
+      hipLaunchKernelGGL(db_colsum_f32, dim3(nVt, slices), dim3(256), 0, stream, dZ, M, chunk, mper, sums);
+      hipLaunchKernelGGL(db_reduce_f32, dim3(nVt), dim3(256), 0, stream, sums, slices, chunk, cw, db + c0);
+    };
+    if (db && !plan.lean) col_sums(kDbSlicesF32, dbpart);
     if (dH || dW) {
       ProductsF32 p;
       p.dZ = dZ;
@@ -590,6 +591,9 @@ hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const floa
                            wpart, nz - 1, n, p.dW);
       }
     }
+    // one slice; its sums go to the first row of dZ, dead after the products (a workgroup has read
+    // its columns before it writes them)
+    if (db && plan.lean) col_sums(1, dZ);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -154,7 +154,7 @@ static int32_t check_args(pctc_dtype dtype, int32_t N, const int32_t* T, const i
 // allow_e: the layout may serve the two-stream schedule (room for the normaliser's E chunk).
 constexpr size_t kEMaxExtra = static_cast<size_t>(64) << 20;
 static Layout make_layout(pctc_dtype dtype, int32_t N, const int32_t* T, const int32_t* U, int32_t D, int32_t V,
-                          float beam, int32_t chunk, bool want_dW = true, bool allow_e = true) {
+                          float beam, int32_t chunk, bool want_dW = true, bool allow_e = true, bool lean = false) {
   Layout L{};
   L.N = N;
   L.dp = plan_dp(N, T, U, beam);
@@ -163,7 +163,7 @@ static Layout make_layout(pctc_dtype dtype, int32_t N, const int32_t* T, const i
   L.pruned = L.dp.pruned;
   L.K_max = (1 + L.Y < V) ? 1 + L.Y : V;
   L.ldS = static_cast<int>(align_up(static_cast<size_t>(L.K_max), 4));
-  L.bwd = plan_bwd(dtype == PCTC_BF16 ? 1 : 0, L.M, D, V, chunk);
+  L.bwd = plan_bwd(dtype == PCTC_BF16 ? 1 : 0, L.M, D, V, chunk, lean);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -188,7 +188,7 @@ static Layout make_layout(pctc_dtype dtype, int32_t N, const int32_t* T, const i
   if (dtype == PCTC_BF16) {  // the overlapped schedule: forecast g and the union-column part
     L.o_gpred = take(static_cast<size_t>(L.M) * 4);
     L.o_pred = take(static_cast<size_t>(N) * 4);
-    L.o_corr = take(union_corr_bytes(L.M, D, L.K_max, want_dW));
+    if (!lean) L.o_corr = take(union_corr_bytes(L.M, D, L.K_max, want_dW));  // not read on one stream
   }
   L.o_dp = take(L.dp.total);
   L.o_bwd = take(L.bwd.total);
@@ -740,17 +740,24 @@ int32_t pruned_ctc_fwd_bwd_noalloc(pctc_dtype dtype, const void* H, int32_t D, c
   if (st != PCTC_OK) return st;
   if (blank < 0 || blank >= V || !loss || !W || misaligned16(W) || misaligned16(H)) return PCTC_EINVAL;
   Layout L = make_layout(dtype, N, input_lengths, target_lengths, D, V, beam, chunk, dW != nullptr, false);
-  if (chunk == 0 && L.total > kNoAllocScratchBytes) {
-    // the widest backward chunk (a multiple of 256 columns) whose layout fits the scratch;
-    // the layout is not monotone in the chunk (the dH product's split count changes with
-    // it), so every width is tried from the default down
-    for (int c = L.bwd.chunk / 256 * 256; c >= 256; c -= 256) {
-      const Layout Lc = make_layout(dtype, N, input_lengths, target_lengths, D, V, beam, c, dW != nullptr, false);
-      if (Lc.total <= kNoAllocScratchBytes) {
-        L = Lc;
-        break;
+  if (L.total > kNoAllocScratchBytes) {
+    // the widest backward chunk (a multiple of 256 columns; or the caller's) whose layout fits the
+    // scratch; the layout is not monotone in the chunk (the products' slice counts change with
+    // it), so every width is tried from the default down.  The lean plan, whose products have
+    // few slices (and which leaves out what only the two-stream schedule needs), is taken where the other fits at no width or at less than half of its width
+    auto widest = [&](bool lean, Layout* out) {
+      int c = chunk ? chunk : L.bwd.chunk / 256 * 256;
+      for (; c >= 1; c -= 256) {
+        *out = make_layout(dtype, N, input_lengths, target_lengths, D, V, beam, c, dW != nullptr, false, lean);
+        if (out->total <= kNoAllocScratchBytes) return c;
+        if (chunk) break;
       }
-    }
+      return 0;
+    };
+    Layout full, lean;
+    const int cf = widest(false, &full), cl = widest(true, &lean);
+    if (cl > 0 && 2 * cf < cl) L = lean;
+    else if (cf > 0) L = full;
   }
   if (L.total > kNoAllocScratchBytes) {
     snprintf(g_last_error, sizeof(g_last_error),
@@ -783,8 +790,7 @@ int32_t pctc_union_remap(const int32_t* targets, int32_t total_targets, int32_t 
 
 size_t pctc_lse_scratch_bytes(int32_t M, int32_t D) {
   return (M < 0 || D <= 0 || D > PCTC_MAX_DIM) ? 0
-                           : lse_partial_bytes(M, D) + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(float2), 256) +
-                                 lse_ht_bytes_bf16(M, D);
+                           : lse_partial_bytes(M, D) + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(float2), 256);
 }
 
 int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, const void* W, int32_t V,
@@ -796,11 +802,15 @@ int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, c
   hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
   const int dt = (dtype == PCTC_BF16) ? 1 : 0;
   float2* lam2 = reinterpret_cast<float2*>(static_cast<char*>(partials) + lse_partial_bytes(M, D));
-  // scratch: [partials][lam2][H transposed]
-  uint16_t* Ht = (dt == 1 && lse_ht_bytes_bf16(M, D))
-                     ? reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(lam2) +
-                                                   align_up(static_cast<size_t>(M) * sizeof(float2), 256))
-                     : nullptr;
+  // scratch: [partials][lam2]; H transposed past the partitions that are written, where it fits
+  // there (V = 180,000: up to D = 640) and is aligned for the kernels' 16-byte pieces
+  uint16_t* Ht = nullptr;
+  if (dt == 1 && !misaligned16(partials)) {
+    const size_t ht = lse_ht_bytes_bf16(M, D);
+    const size_t used = ht ? align_up(static_cast<size_t>(lse_parts_bf16(M, D, V)) * M * sizeof(float2), 256) : 0;
+    if (ht && used + ht <= lse_partial_bytes(M, D))
+      Ht = reinterpret_cast<uint16_t*>(static_cast<char*>(partials) + used);
+  }
   PCTC_HIP(launch_lse(dt, H, M, D, W, nullptr, V, static_cast<float2*>(partials), lam, lam2, stream, Ht));
   if (S && u_ids && K) PCTC_HIP(launch_gather_s(dt, H, M, D, W, nullptr, u_ids, K, K_max, lam, S, ldS, stream));
   PCTC_HIP(hipStreamSynchronize(stream));

@@ -92,11 +92,14 @@ struct BwdPlan {
   int chunk;       // vocabulary columns per step
   int splits;      // k-slices of the dH product per chunk
   int wsplits;     // frame slices of the dW product per chunk (fp32; bf16: 1)
+  bool lean;       // fp32: no slices, db's sums through dead rows of dZ
   int Mp;          // padded frame count (pitch of the transposed head input)
   // hst_bytes: Hs transposed, [D][Mp] bf16, read by the dense recompute of narrow bf16 heads
   size_t dz_bytes, ht_bytes, part_bytes, lam2_bytes, dbpart_bytes, hst_bytes, wpart_bytes, total;
 };
-BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk);
+// lean: the least memory (the allocation-free entry's last resort): fp32 products in one slice each,
+// bf16 dH in at most eight.
+BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk, bool lean = false);
 // Columns of a normaliser partition (bf16): the default chunk of narrow heads is a multiple.
 int lse_part_columns_bf16(int M, int D, int V);
 // The bf16 fused schedule's side of the recomputed backward.  With a second stream: work i
@@ -204,6 +207,7 @@ hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint
                                      float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
                                      hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0);
 size_t lse_ht_bytes_bf16(int M, int D);
+int lse_parts_bf16(int M, int D, int V);  // partitions that a normaliser launch of this shape writes
 // rowscale/Hp of ChunkE from the finalize's s_m (in rowscale) and its check flag.
 hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t* einv, float* rowscale, uint16_t* Hp,
                                 hipStream_t stream);

@@ -111,6 +111,19 @@ def test_noalloc_fp32_then_smaller():
         _run_pair(wl)
 
 
+def test_noalloc_fp32_tight():
+    """A lattice that leaves room for the products only in one slice each: still accepted, with the
+    bias's gradient summed through dead gradient rows; 256-column chunks."""
+    from paper_2609_33645_amd import prunedctc
+    T = np.full(8, 1440, np.int32)
+    wl = workloads.synthesize(name="tight", dtype="f32", T=T, U=T // 3, D=64, V=1500, w_std=0.5,
+                              rng=np.random.default_rng(205))
+    assert prunedctc.workspace_size(0, wl.input_lengths, wl.target_lengths, wl.D, wl.V, wl.beam, 256) > \
+        prunedctc.noalloc_scratch_bytes()
+    say(f"no-alloc fp32, tight: M={wl.M}")
+    _run_pair(wl, bias=np.linspace(-1, 1, wl.V).astype(np.float32), want_db=True)
+
+
 @pytest.mark.timeout(300)
 def test_noalloc_full_size_zipformer_m():
     """The benchmark's workload: the scratch cannot hold the default 60,160-column backward
