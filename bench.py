@@ -66,6 +66,8 @@ def parse():
 
 KERNEL_SOURCES = ("paper_2609_33645_amd/csrc/head_gemm_bf16.hip", "paper_2609_33645_amd/csrc/gemm_bf16.h",
                   "paper_2609_33645_amd/csrc/pctc_device.h", "paper_2609_33645_amd/csrc/head_gemm.hip",
+                  "paper_2609_33645_amd/csrc/head_gemm_f32.hip", "paper_2609_33645_amd/csrc/gemm_f32.h",
+                  "paper_2609_33645_amd/csrc/head_tiles.h",
                   "paper_2609_33645_amd/csrc/ctc_dp.hip", "paper_2609_33645_amd/csrc/grouped_head.hip",
                   "paper_2609_33645_amd/csrc/union_remap.hip", "paper_2609_33645_amd/csrc/pctc_api.hip")
 
