@@ -96,7 +96,7 @@ hipError_t launch_lam2(const double* lam, int M, float2* lam2, hipStream_t strea
 }
 
 hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht) {
+                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht, bool any_m) {
   if (M <= 0) return hipSuccess;
   int P = 0;
   hipError_t e;
@@ -105,21 +105,21 @@ hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, con
     e = launch_ht_build_bf16(static_cast<const uint16_t*>(H), M, D, nullptr, nullptr, Ht, Mp, stream);
     if (e == hipSuccess)
       e = launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, V,
-                                    partials, &P, nullptr, 0, 0, nullptr, stream, Ht, Mp);
+                                    partials, &P, nullptr, 0, 0, nullptr, stream, Ht, Mp, any_m);
   } else {
-    e = launch_lse_partials(dtype, H, M, D, W, bias, V, partials, &P, stream);
+    e = launch_lse_partials(dtype, H, M, D, W, bias, V, partials, &P, stream, any_m);
   }
   if (e != hipSuccess) return e;
   return launch_lse_finalize(partials, M, P, lam, lam2, nullptr, nullptr, nullptr, 0, stream);
 }
 
 hipError_t launch_lse_partials(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                               float2* partials, int* P_out, hipStream_t stream) {
+                               float2* partials, int* P_out, hipStream_t stream, bool any_m) {
   *P_out = 0;
   if (M <= 0) return hipSuccess;
   if (dtype == 1)
     return launch_lse_partial_bf16(static_cast<const uint16_t*>(H), M, D, static_cast<const uint16_t*>(W), bias, V,
-                                   partials, P_out, stream);
+                                   partials, P_out, stream, any_m);
   return launch_lse_partial_f32(static_cast<const float*>(H), M, D, static_cast<const float*>(W), bias, V, partials,
                                 P_out, stream);
 }

@@ -1076,13 +1076,14 @@ hipError_t launch_union_merge_bf16(const int32_t* Kdev, int K_max, const int32_t
 // of workgroups (few frames or a small vocabulary); then the run whose rounds are shortest by a
 // tile's time (0.5 us a 32-deep k-tile, 4 us the epilogue) and 4 us a workgroup: 331 frames,
 // D = 512, V = 180,000, 176 workgroups of 8 tiles 125 us, 236 of 6 101 us; 150 frames (argmax),
-// 88 of 8 tiles 94 us, 235 of 3 46 us.
+// 88 of 8 tiles 94 us, 235 of 3 46 us.  any_m: the runs of many frames whatever M, so that a
+// frame's lambda does not depend, to the last bit, on how many frames are beside it.
 struct LseSplit {
   bool wide;  // D >= kWideD: one vocabulary tile per partition (argmax: GWide tiles)
   int vper, P, nM;
 };
 
-static LseSplit lse_split_bf16(int M, int D, int V) {
+static LseSplit lse_split_bf16(int M, int D, int V, bool any_m = false) {
   LseSplit s;
   s.wide = D >= kWideD;
   constexpr int TR = 256, TC = 256;
@@ -1094,7 +1095,7 @@ static LseSplit lse_split_bf16(int M, int D, int V) {
   if (!s.wide && run < kMidRun) {
     const int least = run > 1 ? run : 1;
     run = kMidRun;
-    if (s.nM * ((vtiles + kMidRun - 1) / kMidRun) < 256) {
+    if (!any_m && s.nM * ((vtiles + kMidRun - 1) / kMidRun) < 256) {
       double best = -1;
       for (int r = kMidRun; r >= least; --r) {
         const int wgs = s.nM * ((vtiles + r - 1) / r);
@@ -1112,11 +1113,11 @@ static LseSplit lse_split_bf16(int M, int D, int V) {
 }
 
 int lse_part_columns_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V).vper; }
-int lse_parts_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V).P; }
+int lse_parts_bf16(int M, int D, int V, bool any_m) { return lse_split_bf16(M, D, V, any_m).P; }
 
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
-                                   float2* partials, int* P_out, hipStream_t stream) {
-  const LseSplit sp = lse_split_bf16(M, D, V);
+                                   float2* partials, int* P_out, hipStream_t stream, bool any_m) {
+  const LseSplit sp = lse_split_bf16(M, D, V, any_m);
   const int vper = sp.vper, Peff = sp.P;
   *P_out = Peff;
   Prof pr("lse_partial", stream);
@@ -1274,8 +1275,8 @@ int lse_e_parts_bf16(int M, int D, int V, int chunk) {
 
 hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                      float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
-                                     hipStream_t stream, const uint16_t* Ht, int Mp) {
-  const LseSplit sp = lse_split_bf16(M, D, V);
+                                     hipStream_t stream, const uint16_t* Ht, int Mp, bool any_m) {
+  const LseSplit sp = lse_split_bf16(M, D, V, any_m);
   *P_out = sp.P;
   const dim3 grid(sp.nM * sp.P), block(GMid::kThreads);
   Prof pr("lse_partial", stream);

@@ -47,14 +47,16 @@ inline int lse_max_parts(int D) { return D >= kWideD ? kMaxLseParts : 256; }
 size_t lse_partial_bytes(int M, int D);
 // bias: device float [V] or null (logits H W^T + b).
 // Ht (null: none): lse_ht_bytes_bf16(M, D) bytes of scratch for H transposed, from which the bf16
-// normaliser reads its frames in whole lines.
+// normaliser reads its frames in whole lines.  any_m: vocabulary partitions that do not depend on M
+// (fp32's never do), so that lambda's last bit does not depend on the frames beside it.
 hipError_t launch_lse(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht = nullptr);
+                      float2* partials, double* lam, float2* lam2, hipStream_t stream, uint16_t* Ht = nullptr,
+                      bool any_m = false);
 // The same in two halves: the partial (max, sum) pairs over the vocabulary partitions
 // (P_out: partitions written), then lambda and its hi/lo pair from them; with Zd the second
 // half also writes S[m * ldS + j] = float(Zd[m * ldS + j] - lambda_m) for j < *K.
 hipError_t launch_lse_partials(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
-                               float2* partials, int* P_out, hipStream_t stream);
+                               float2* partials, int* P_out, hipStream_t stream, bool any_m = false);
 // With g (forecast dense-part factors), also rowscale[m] = -g_m exp(-lambda_m) and *einv = 1
 // if any lambda_m lies outside [kEMin, kEMax] (the normaliser's E = exp(z) is then unusable:
 // bf16 overflow or significant underflow).
@@ -171,7 +173,7 @@ hipError_t head_bwd_f32(const float* H, int M, int D, const float* W, const floa
 
 // ---- bf16 kernels on the direct-to-LDS engine (head_gemm_bf16.hip) ---------------------
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
-                                   float2* partials, int* P_out, hipStream_t stream);
+                                   float2* partials, int* P_out, hipStream_t stream, bool any_m = false);
 // Gz (may be null): also Gz[m * ldS + j] = 0 for j < *K (the lattice's G, before it is written).
 // Zd (may be null): write the selected logits in double (Zd[m * ldS + j]) instead of S; lam
 // is then not read (launch_lse_finalize subtracts it).
@@ -205,9 +207,9 @@ int lse_e_parts_bf16(int M, int D, int V, int chunk);
 // With bias (float [V]; needs Ht, eparts 0) the logits include it.
 hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                      float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
-                                     hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0);
+                                     hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0, bool any_m = false);
 size_t lse_ht_bytes_bf16(int M, int D);
-int lse_parts_bf16(int M, int D, int V);  // partitions that a normaliser launch of this shape writes
+int lse_parts_bf16(int M, int D, int V, bool any_m);  // partitions that a normaliser launch of this shape writes
 // rowscale/Hp of ChunkE from the finalize's s_m (in rowscale) and its check flag.
 hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t* einv, float* rowscale, uint16_t* Hp,
                                 hipStream_t stream);

@@ -102,6 +102,22 @@ def test_few_frames_slices(T, D, V):
     assert cosine(res["dW"], ref["dW"]) >= 0.99999
 
 
+@pytest.mark.parametrize("D,V", [(256, 20_001), (72, 20_001), (2048, 700)])
+def test_lse_select_does_not_depend_on_the_batch(D, V):
+    """A frame's lambda and S are the same, to the last bit, alone and in a batch: S decides the
+    arcs at a beam's edge, where its last bit moves the discarded mass."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("bf16", [8200], D, V, 17, u_frac=0.0)
+    H, W, _ = to_dev(wl)
+    u = torch.arange(0, V, 37, dtype=torch.int32, device="cuda")
+    all_ = prunedctc.lse_select(H, W, u)
+    for m in (1, 40, 300, 1500):
+        few = prunedctc.lse_select(H[:m], W, u)
+        assert torch.equal(few["lam"], all_["lam"][:m]) and torch.equal(few["S"], all_["S"][:m]), m
+
+
 @pytest.mark.parametrize("M,V", [(1, 700), (150, 50_000), (257, 2500)])
 def test_greedy_few_frames(M, V):
     from paper_2609_33645_amd import prunedctc
