@@ -270,7 +270,17 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
   const int wl = threadIdx.x & 63;                        // lane of the wavefront
   const int wv = MULTI ? static_cast<int>(threadIdx.x >> 6) : 0;
   const int lane = MULTI ? static_cast<int>(threadIdx.x) : wl;  // lane of the unit
-  if (status[n] != 0) return;
+  // The forward unit of this launch sets status[n] = 2 where the total is not finite, perhaps before
+  // this unit has begun: one read decides for all wavefronts of a unit, which meet at barriers below
+  // (tables of such an utterance are not used, so either value will do).
+  if constexpr (MULTI) {
+    __shared__ int excluded;
+    if (threadIdx.x == 0) excluded = status[n];
+    __syncthreads();
+    if (excluded != 0) return;
+  } else if (status[n] != 0) {
+    return;
+  }
   const int t0 = toff[n], T = toff[n + 1] - t0;
   const int y0 = yoff[n], U = yoff[n + 1] - y0;
   const int Sp = 2 * U + 1;

@@ -173,6 +173,35 @@ def test_lattice_wavefront_edges(U, beam):
             base += int(T[n]) * Sp
 
 
+@pytest.mark.parametrize("beam", [math.inf, 6.5])
+def test_lattice_wavefronts_with_excluded_utterances(beam):
+    """Four-wavefront lattices whose total is not finite (status 2, set by the forward pass while
+    backward passes of the same launch are still to begin: more workgroups than fit at once) among
+    others: statuses, zero rows, and the others as they are alone."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    N, U, K = 400, 130, 40
+    rng = np.random.default_rng(9)
+    y = rng.integers(1, K, size=N * U).astype(np.int32)
+    T = np.full(N, 3 * U, np.int32)
+    S = workloads.random_scores(9, int(T.sum()), K, integer=True).reshape(N, 3 * U, K)
+    bad = np.arange(N) % 3 != 0
+    S[bad, -1] = -np.inf  # no alignment has a finite score ..
+    S[bad & (np.arange(N) % 2 == 0), -2, 0] = np.nan  # .. or is a number
+    dev = lambda n: (torch.from_numpy(S[n].reshape(-1, K)).cuda(),  # noqa: E731
+                     torch.from_numpy(y.reshape(N, U)[n].reshape(-1)).cuda())
+    say(f"excluded utterances beam={beam}")
+    out = prunedctc.ctc_dp(*dev(np.arange(N)), T, np.full(N, U), beam=beam)
+    np.testing.assert_array_equal(out["status"].cpu().numpy(), np.where(bad, 2, 0))
+    G = out["G"].cpu().numpy().reshape(N, 3 * U, K)
+    assert not G[bad].any()
+    for n in (0, 3, 198, 399):
+        alone = prunedctc.ctc_dp(*dev(np.array([n])), T[:1], [U], beam=beam)
+        np.testing.assert_array_equal(G[n], alone["G"].cpu().numpy())
+        assert float(alone["loss_per_utt"][0]) == float(out["loss_per_utt"][n])
+
+
 @pytest.mark.parametrize("U", [63, 64, 127, 128, 300, 520, 800])
 def test_discarded_mass_wavefront_edges(U):
     import torch
