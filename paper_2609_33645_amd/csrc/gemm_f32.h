@@ -175,6 +175,16 @@ __device__ __forceinline__ f32x4 frag4(const char* lds, int rb, int lane) {
   }
 }
 
+// Value k of row r from a stage.
+template <LL L>
+__device__ __forceinline__ float value(const char* lds, int r, int k) {
+  if constexpr (L == LL::KC) {
+    return *reinterpret_cast<const float*>(lds + r * 64 + (((k >> 2) ^ ((r >> 2) & 3)) << 4) + ((k & 3) << 2));
+  } else {
+    return *reinterpret_cast<const float*>(lds + k * 1024 + ((r * 4) ^ ((k >> 3) << 7)));
+  }
+}
+
 // BUF false: A's rows through its gather table.
 template <LL LA, LL LB, bool BUF = true>
 struct Gemm {
@@ -254,15 +264,77 @@ struct Gemm {
     phase_barrier();
   }
 
-  // Accumulates k in [kbeg, kend) (kbeg a multiple of 16) into acc, which holds starting values.
-  // All 512 threads must call; contains barriers.  On return every copy has landed and every
-  // wave is past its last LDS read.
+  // acc = the sum over k in [kbeg, kend) (kbeg a multiple of 16).  All 512 threads must call;
+  // contains barriers.  On return every copy has landed and every wave is past its last LDS read.
   __device__ static __forceinline__ void run(const GOp& A, const GOp& B, int row0, int col0, int kbeg, int kend,
                                              char* const (&st)[kNS], f32x16 (&acc)[FR][FC]) {
+    zero(acc);
+    if (kend <= kbeg) return;
+    run_split(A, B, row0, col0, kbeg, kend, st, acc);
+    // An operand that is infinite, or too large to round to bf16, has NaN remainders: its whole row
+    // (or column) of the tile is NaN, so one column and one row of each block show it.  Such tiles
+    // are taken again on the fp32 instructions, which give what fp32 arithmetic gives.
+    bool nan = false;
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nan |= acc[i][0][r] != acc[i][0][r];
+#pragma unroll
+    for (int j = 1; j < FC; ++j) nan |= acc[0][j][0] != acc[0][j][0];
+    __shared__ __attribute__((aligned(16))) uint32_t wave_nan[NW];
+    wave_nan[threadIdx.x >> 6] = __ballot(nan) != 0;  // the same value in every lane
+    __syncthreads();  // also: before anyone reuses the stages
+    uint32_t any = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any |= wave_nan[w];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any) != 0u, 0)) {
+      zero(acc);
+      run_plain(A, B, row0, col0, kbeg, kend, st, acc);
+    }
+  }
+
+  // The same on v_mfma_f32_32x32x2_f32 (one k-tile at a time, no overlap: for few tiles only).
+  __device__ static __forceinline__ void run_plain(const GOp& A, const GOp& B, int row0, int col0, int kbeg, int kend,
+                                                   char* const (&st)[kNS], f32x16 (&acc)[FR][FC]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr0 = (wave / WC) * (kT / WR), wc0 = (wave % WC) * (kT / WC);
+    const int klimA = min(A.kmax, kend), klimB = min(B.kmax, kend);
+    CA ca;
+    CB cb;
+    ca.init(A, row0, wave, lane, kbeg, klimA);
+    cb.init(B, col0, wave, lane, kbeg, klimB);
+#pragma unroll 1
+    for (int k0 = kbeg; k0 < kend; k0 += kBK) {
+      ca.issue(A, k0, klimA, st[0], wave);
+      cb.issue(B, k0, klimB, st[0] + kABytes, wave);
+      bf::wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+#pragma unroll 1
+      for (int kk = 0; kk < kBK; kk += 2) {
+        const int k = kk + (lane >> 5);
+        float a[FR], b[FC];
+#pragma unroll
+        for (int i = 0; i < FR; ++i) a[i] = value<LA>(st[0], wr0 + 32 * i + (lane & 31), k);
+#pragma unroll
+        for (int j = 0; j < FC; ++j) b[j] = value<LB>(st[0] + kABytes, wc0 + 32 * j + (lane & 31), k);
+#pragma unroll
+        for (int i = 0; i < FR; ++i)
+#pragma unroll
+          for (int j = 0; j < FC; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      __builtin_amdgcn_s_barrier();  // before the stage is filled again
+    }
+  }
+
+  // Accumulates the split products into acc.  On return this wave's copies have landed; a barrier is
+  // left to the caller.
+  __device__ static __forceinline__ void run_split(const GOp& A, const GOp& B, int row0, int col0, int kbeg, int kend,
+                                                   char* const (&st)[kNS], f32x16 (&acc)[FR][FC]) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = (kend - kbeg + kBK - 1) / kBK;
-    if (nk <= 0) return;
     const int klimA = min(A.kmax, kend), klimB = min(B.kmax, kend);
     CA ca;
     CB cb;
@@ -294,8 +366,6 @@ struct Gemm {
     if (t + 2 < nk) pp_tile<2>(st, wave, lane, acc, f, issue);
     if (!lag) phase_barrier();  // the barrier group 1 took at the start
     bf::wait_vmcnt<0>();  // the copies past the end (zeros) have landed
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_s_barrier();  // before anyone reuses the stages
   }
 };
 

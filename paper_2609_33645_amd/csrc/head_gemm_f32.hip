@@ -50,7 +50,6 @@ __device__ __forceinline__ void vocab_tiles(const float* H, int M, int D, const 
   f32x16 acc[GZ::FR][GZ::FC];
   for (int i = 0; i < ntiles; ++i) {
     const int v0 = vbeg + i * kTile;
-    GZ::zero(acc);
     GZ::run(A, B, v0, m0, 0, D, st, acc);
     // an opaque lane: what the epilogue derives from it is not kept in registers through the next
     // tile's products (it would spill there)
@@ -145,7 +144,6 @@ gather_s_f32(const float* __restrict__ H, int M, int D, const float* __restrict_
   const GOp A{W, D, K, D, u_ids};
   const GOp B{H, D, M, D, nullptr};
   f32x16 acc[G::FR][G::FC];
-  G::zero(acc);
   G::run(A, B, j0, m0, 0, D, st, acc);
   WaveBlock blk = wave_block(st, wave, lane);
   const int jw = j0 + (wave / G::WC) * (kTile / G::WR);  // the wave's first selected class
@@ -202,7 +200,6 @@ recompute_dz_f32(const float* __restrict__ H, int M, int D, const float* __restr
   const GOp A{W + static_cast<int64_t>(c0) * D, D, cw, D, nullptr};
   const GOp B{H, D, M, D, nullptr};
   f32x16 acc[GZ::FR][GZ::FC];
-  GZ::zero(acc);
   GZ::run(A, B, vl0, m0, 0, D, st, acc);
   if (BIAS) bias_add<GZ::FR, GZ::FC, GZ>(acc, bl, wave, lane);
   const bool ragged = vl0 + kTile > cw;
@@ -305,7 +302,6 @@ __global__ void __launch_bounds__(512, 1) products_f32(ProductsF32 P) {
     float* const dst = P.part + static_cast<int64_t>(s) * P.M * P.D;
     // zero starting values, the earlier chunks' sums added at the end: a chain of additions onto
     // a sum that the union columns made large loses more (1.4e-5 against 1.4e-6 at V = 180,000)
-    GH::zero(acc);
     const GOp A{P.dZ, P.chunk, P.M, P.cw, nullptr};
     const GOp B{P.W, P.D, P.D, P.cw, nullptr};
     GH::run(A, B, m0, d0, kb, ke, st, acc);
@@ -330,7 +326,6 @@ __global__ void __launch_bounds__(512, 1) products_f32(ProductsF32 P) {
     const int dt = work % nDt, vt = (work / nDt) % nVt, z = work / (nDt * nVt);
     const int v0 = vt * kTile, d0 = dt * kTile;
     const int kb = z * P.mslice, ke = min(P.M, kb + P.mslice);
-    GW::zero(acc);
     const GOp A{P.dZ, P.chunk, P.cw, P.M, nullptr};
     const GOp B{P.Hs, P.D, P.D, P.M, nullptr};
     GW::run(A, B, v0, d0, kb, ke, st, acc);

@@ -63,6 +63,44 @@ def test_f32_split_keeps_the_range(e):
     assert np.abs(c - ref).max() <= 3.4 * 2.0 ** -8
 
 
+@pytest.mark.parametrize("V", [300, 513])
+def test_f32_infinite_operands(V):
+    """An infinite weight (a class masked or forced by its weights) acts as in fp32 arithmetic: a
+    logit of -inf has probability 0, one of +inf wins the argmax, and everything else is as it is
+    without it."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("f32", [70], 40, V, 21)
+    wl.H[:, 3] = np.abs(wl.H[:, 3]) + 0.1
+    masked = V - 2
+    assert masked not in wl.targets
+    wl.W[masked, 3] = -np.inf
+    H, W, y = to_dev(wl)
+    Z = wl.H.astype(np.float64) @ np.delete(wl.W, masked, 0).astype(np.float64).T
+    lam = Z.max(1) + np.log(np.exp(Z - Z.max(1, keepdims=True)).sum(1))
+    out = prunedctc.lse_select(H, W, torch.tensor([0, masked], dtype=torch.int32, device="cuda"))
+    assert np.abs(out["lam"].cpu().numpy() - lam).max() <= 1e-5
+    assert torch.isneginf(out["S"][:, 1]).all()
+    assert np.abs(out["S"][:, 0].cpu().numpy() - (Z[:, 0] - lam)).max() <= 1e-5
+    # the loss and the weights' gradients, as without the masked class (its own row is zero); dH is
+    # compared where the infinite weight does not meet the class's zero probability
+    res = run_gpu(wl)
+    y2 = np.where(wl.targets > masked, wl.targets - 1, wl.targets)
+    ref = oracle.fwd_bwd(wl.H, np.delete(wl.W, masked, 0), y2, wl.input_lengths, wl.target_lengths, 0, wl.beam)
+    assert loss_rel(res["loss"], ref["loss"]) <= 1e-5
+    assert rel_err(np.delete(res["dW"], masked, 0), ref["dW"]) <= 1e-5 and not res["dW"][masked].any()
+    assert rel_err(np.delete(res["dH"], 3, 1), np.delete(ref["dH"], 3, 1)) <= 1e-5
+    # +inf where the frame's value is positive, -inf where it is negative
+    W[masked, 3] = 0.0
+    W[1, 7] = np.inf
+    ids = prunedctc.greedy_decode(H, W, [70])["ids"].cpu().numpy()
+    Z = wl.H.astype(np.float64) @ W.cpu().numpy().astype(np.float64).T
+    assert np.all(ids[wl.H[:, 7] > 0] == 1)
+    rest = Z[wl.H[:, 7] < 0]
+    np.testing.assert_array_equal(ids[wl.H[:, 7] < 0], rest.argmax(1))
+
+
 # ---- discarded mass of several beams in one launch ----------------------------------------------
 
 @pytest.mark.parametrize("nbeams", [1, 2, 9, 10, 20])
