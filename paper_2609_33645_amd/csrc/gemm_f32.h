@@ -1,13 +1,18 @@
 // fp32 tile engine for gfx950: C[i][j] = sum_k A[i][k] B[j][k] over a 256 x 256 tile with fp32
 // operands, on the bf16 matrix instructions.
 //
-// Every operand value is split exactly into three bf16 parts, x = x0 + x1 + x2 (8 + 8 + 8
-// significand bits; the parts keep fp32's exponent range, so no scaling is needed), and the
+// Every operand value is split into three bf16 parts, x = x0 + x1 + x2, each the rounding to nearest
+// of what the earlier ones leave (exact for |x| of 2^-110 and more: below that the last part's low
+// bits fall under bf16's least, 2^-133, and at 2^-126 eight significand bits are left), and the
 // product is taken as the six part products of weight 2^-16 and more,
-//   a b = a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0) + O(2^-25 |a b|),
-// each a v_mfma_f32_32x32x16_bf16 accumulated in fp32, smallest first.  The dropped terms are
-// below the rounding of one fp32 product; the sums are rounded once per 16 products instead of
-// once per 2 (v_mfma_f32_32x32x2_f32), so the result is as close to 64 bits or closer.
+//   a b = a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0) + dropped,
+// each a v_mfma_f32_32x32x16_bf16 accumulated in fp32, a k-tile's smallest first.  What is dropped is
+// at most 2^-24.2 |a b| and 2^-27.5 |a b| root mean square (one rounding of an fp32 product: at most
+// 2^-24; with x0 cut to 8 bits instead of rounded, 2^-22.3 and 2^-25.5).  A sum is rounded six times
+// per 16 products, on v_mfma_f32_32x32x2_f32 eight times.  At M = 16,000, D = 512, V = 180,000 the
+// gradients are 1.5e-6 off 64 bits (on the fp32 instructions 2.4e-6, with x0 cut 1.7e-6).
+// A value that is infinite, or rounds to infinity in bf16 (from 3.39e38), has no such parts: tiles
+// that hold one are taken on the fp32 instructions (Gemm::run).
 //
 // What bounds it: six bf16 instructions of 32 cycles do the work of eight fp32 ones of 64, so the
 // ceiling is 2500 / 6 = 417 TFLOP/s (fp32 units: 157).
@@ -19,7 +24,7 @@
 // groups, one a phase behind the other, so that on every SIMD one wave issues its 48 products
 // (1536 cycles, registers only) while the other copies, reads and splits its next k-tile.
 // Measured (normaliser pass over M = 16,000, D = 512, V = 16,384; the fp32 units took 2390 us):
-// 1260 us, 1135 with the splitting left out; with the splits interleaved with the products in
+// 1250 us; with x0 cut 1260, and then 1135 with the splitting left out; with the splits interleaved with the products in
 // each wave instead of the phases 1540; with the remainders from v_dot2_f32_bf16 (7 instructions
 // per pair instead of 11) 1430: that instruction keeps the matrix pipe from issuing.
 //
@@ -139,9 +144,9 @@ struct TileCopy {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// The three bf16 parts of a matrix-core fragment (8 values).  x0 is x cut to 8 significand bits
-// (a cut never overflows, unlike a rounding), x1 the rest rounded to 8, x2 what is left (at most
-// 8 bits: exact).
+// The three bf16 parts of a matrix-core fragment (8 values).  x0 and x1 are roundings to nearest of
+// x and of x - x0, x2 what is left (at most 8 bits: exact).  A value whose x0 rounds to infinity has
+// NaN remainders (see Gemm::run).
 struct Tri {
   uint32_t d[3][4];
 };
@@ -150,10 +155,9 @@ template <int HALF>
 __device__ __forceinline__ void split4(const f32x4& x, Tri& t) {
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const uint32_t u0 = __float_as_uint(x[2 * q]), u1 = __float_as_uint(x[2 * q + 1]);
-    t.d[0][2 * HALF + q] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the two high halves
-    const float r0 = x[2 * q] - __uint_as_float(u0 & 0xffff0000u);
-    const float r1 = x[2 * q + 1] - __uint_as_float(u1 & 0xffff0000u);
+    const uint32_t a = pack_bf16x2(x[2 * q], x[2 * q + 1]);
+    t.d[0][2 * HALF + q] = a;
+    const float r0 = x[2 * q] - __uint_as_float(a << 16), r1 = x[2 * q + 1] - __uint_as_float(a & 0xffff0000u);
     const uint32_t m = pack_bf16x2(r0, r1);
     t.d[1][2 * HALF + q] = m;
     t.d[2][2 * HALF + q] = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));

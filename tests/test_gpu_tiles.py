@@ -44,9 +44,10 @@ def test_f32_tile_edges(T, D, V, chunk):
 
 @pytest.mark.parametrize("e", [100, -90])
 def test_f32_split_keeps_the_range(e):
-    """The three bf16 parts of a value keep fp32's exponent range: H 2^e and W 2^-e give the very
-    same logits as H and W (powers of two move through the splits and the sums exactly; every
-    part stays a normal number), and a value too large to round to bf16 stays finite."""
+    """H 2^e and W 2^-e give the very same logits as H and W (powers of two move through the splits
+    and the sums exactly while every part stays a normal number), and values at the top of fp32's
+    range give finite logits: split (3.3e38) and, where they round to infinity in bf16 (3.4e38), on
+    the fp32 instructions."""
     import torch
 
     from paper_2609_33645_amd import prunedctc
@@ -55,12 +56,53 @@ def test_f32_split_keeps_the_range(e):
     a = prunedctc.lse_select(H, W)["lam"]
     b = prunedctc.lse_select(H * 2.0 ** e, W * 2.0 ** -e)["lam"]
     assert torch.equal(a, b)
-    H[:, 0] = 3.4e38  # rounds to infinity in bf16
     W[:, 0] = 1e-38
-    c = prunedctc.lse_select(H, W)["lam"].cpu().numpy()
-    ref = oracle.log_normalizer(H.cpu().numpy().astype(np.float64), W.cpu().numpy().astype(np.float64))
-    # 1e-38 splits into parts down to 2^-142, below bf16's smallest: its product is good to 2^-8
-    assert np.abs(c - ref).max() <= 3.4 * 2.0 ** -8
+    # 1e-38 splits into parts down to 2^-142, below bf16's smallest: its product is good to 2^-8; on
+    # the fp32 instructions it is rounded like any other
+    for top, bar in ((3.3e38, 3.4 * 2.0 ** -8), (3.4e38, 1e-5)):
+        H[:, 0] = top
+        c = prunedctc.lse_select(H, W)["lam"].cpu().numpy()
+        ref = oracle.log_normalizer(H.cpu().numpy().astype(np.float64), W.cpu().numpy().astype(np.float64))
+        assert np.abs(c - ref).max() <= bar
+
+
+def test_f32_split_drops_less_than_a_rounding():
+    """Logits that are one product, of values chosen so that a first part cut to bf16 instead of
+    rounded would drop the most (2^-22.4 of the product): the mean error, in which roundings cancel,
+    shows what is dropped (below 2^-24.2 for any product with parts rounded to nearest)."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+
+    def rest(x, nearest):
+        """x minus its first part, that minus its own, of float32 values as float64."""
+        out = []
+        for near in (nearest, True):
+            u = x.astype(np.float32).view(np.uint32).astype(np.uint64)
+            u = u + 0x7fff + ((u >> 16) & 1) if near else u
+            x = x - (u & 0xffff0000).astype(np.uint32).view(np.float32)
+            out.append(x)
+        return out
+
+    def dropped(a, b, nearest):
+        (a1, a2), (b1, b2) = rest(a, nearest), rest(b, nearest)
+        return ((a1 - a2) * b2 + a2 * (b1 - b2) + a2 * b2) / (a * b)
+
+    rng = np.random.default_rng(3)
+    a, b = ((1.0 + rng.random(300_000) * 0.0625).astype(np.float32).astype(np.float64) for _ in range(2))
+    err = []
+    for x in b[np.argsort(-dropped(a, b, False))[:20]]:
+        top = a[np.argsort(-dropped(a, np.full_like(a, x), False))[:1000]]
+        assert dropped(top, x * np.ones(1000), False).min() > 2.0 ** -23
+        assert np.abs(dropped(top, x * np.ones(1000), True)).max() < 2.0 ** -24.2
+        H, W = torch.zeros(1000, 8), torch.zeros(2, 8)
+        H[:, 0] = torch.from_numpy(top * 64).float()
+        W[0, 0] = float(x)  # logits (a x, 0): lambda = a x + log(1 + exp(-a x)), within 2^-92 of a x
+        lam = prunedctc.lse_select(H.cuda(), W.cuda())["lam"].cpu().numpy()
+        err.append(lam / (top * 64 * x) - 1.0)
+    say(f"mean error {np.mean(err):.3g}, largest {np.abs(err).max():.3g}")
+    assert abs(np.mean(err)) <= 2.0 ** -24.2
+    assert np.abs(err).max() <= 3 * 2.0 ** -24  # dropped, the sum's rounding, the exponent's in lambda
 
 
 @pytest.mark.parametrize("V", [300, 513])
