@@ -60,7 +60,7 @@ typedef enum {
 enum { PCTC_UTT_OK = 0, PCTC_UTT_NOT_ALIGNABLE = 1, PCTC_UTT_NONFINITE = 2 };
 
 /* Limits of this implementation. */
-#define PCTC_MAX_TARGET 1023    /* U_n (2U_n+1 lattice states per frame held in one wavefront) */
+#define PCTC_MAX_TARGET 1023    /* U_n (2U_n+1 lattice states per frame held by up to four wavefronts) */
 #define PCTC_MAX_VOCAB 524288   /* V (the largest vocabulary the parity tests cover) */
 #define PCTC_MAX_DIM 1048576    /* D (the products address 256-row tiles with 32-bit byte offsets) */
 
@@ -145,7 +145,7 @@ int32_t pruned_ctc_fwd_bwd(pctc_dtype dtype, const void* H, int32_t D, const voi
  * utt_weight  device float [N] or NULL (all 1): loss = sum_n w_n L_n over the included
  *             utterances, and dH, dW, db are the gradients of that sum.  loss_per_utt
  *             still receives the unweighted L_n.  A zero weight excludes the utterance
- *             from the gradients.
+ *             from the gradients.  fp32 heads: |w_n| below 2^103 (dL/dZ is kept times 2^24).
  * db          device float [V] or NULL: dL/db, the column sums of dL/dZ (bf16 path:
  *             the sums of the bf16-rounded dL/dZ that the dH and dW products also use).
  * Every other argument is as for pruned_ctc_fwd_bwd, which equals this call with three

@@ -26,6 +26,10 @@ using GZGather = f3::Gemm<LL::KC, LL::KC, false>;  // the same over gathered W r
 using GH = f3::Gemm<LL::KC, LL::MC>;               // dH = dZ W
 using GW = f3::Gemm<LL::MC, LL::MC>;               // dW = dZ^T H
 constexpr int kTile = f3::kT;
+// dZ is kept times 2^24 (exact, and taken off where its products and sums are written), so that
+// probabilities down to fp32's least split into parts without loss (see gemm_f32.h); loss weights up
+// to 2^103 stay finite.
+constexpr float kDzScale = 16777216.f, kDzUnscale = 1.f / kDzScale;
 
 #define PCTC_F3_STAGES                                                          \
   __shared__ __attribute__((aligned(1024))) char st0_[GZ::kStageBytes];         \
@@ -175,7 +179,7 @@ gather_s_f32(const float* __restrict__ H, int M, int D, const float* __restrict_
 }
 
 // dZ chunk [M][chunk] (row pitch `chunk`): columns v_local in [0, cw) hold scatter_U(G) - g p of
-// class c0 + v_local, columns in [cw, tile end) zeros; rows of excluded frames (g = 0) zeros.
+// class c0 + v_local, times kDzScale, columns in [cw, tile end) zeros; rows of excluded frames (g = 0) zeros.
 template <bool BIAS>
 __global__ void __launch_bounds__(512, 1)
 recompute_dz_f32(const float* __restrict__ H, int M, int D, const float* __restrict__ W,
@@ -208,7 +212,7 @@ recompute_dz_f32(const float* __restrict__ H, int M, int D, const float* __restr
 #pragma unroll
   for (int j = 0; j < GZ::FC; ++j) {
     const int m = min(m0 + GZ::col_of(wave, lane, j), M - 1);  // frames past M are not stored
-    const float gm = g[m];
+    const float gm = g[m] * kDzScale;
     const float2 l2 = lam2[m];
     const bool inc = gm != 0.f;
 #pragma unroll
@@ -250,7 +254,7 @@ recompute_dz_f32(const float* __restrict__ H, int M, int D, const float* __restr
         const float4 zz = blk.get(f, lane & 31);
         f3::f32x4 z = {zz.x, zz.y, zz.z, zz.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) z[e] += (inc && sj[e] >= 0) ? gv[e] : 0.f;
+        for (int e = 0; e < 4; ++e) z[e] += (inc && sj[e] >= 0) ? gv[e] * kDzScale : 0.f;
         if (mw + f < M) __builtin_nontemporal_store(z, reinterpret_cast<f3::f32x4*>(dw + static_cast<int64_t>(f) * chunk));
       }
     } else {
@@ -316,7 +320,8 @@ __global__ void __launch_bounds__(512, 1) products_f32(ProductsF32 P) {
           const int m = m0 + GH::row_of(wave, lane, i, r);
           if (m < P.M) {
             float* const o = dst + static_cast<int64_t>(m) * P.D + d;
-            *o = P.first ? acc[i][j][r] : *o + acc[i][j][r];
+            const float x = acc[i][j][r] * kDzUnscale;
+            *o = P.first ? x : *o + x;
           }
         }
       }
@@ -339,7 +344,7 @@ __global__ void __launch_bounds__(512, 1) products_f32(ProductsF32 P) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int v = v0 + GW::row_of(wave, lane, i, r);
-          if (v < P.cw) dst[static_cast<int64_t>(v) * P.D + d] = acc[i][j][r];
+          if (v < P.cw) dst[static_cast<int64_t>(v) * P.D + d] = acc[i][j][r] * kDzUnscale;
         }
       }
   }
@@ -411,7 +416,7 @@ db_reduce_f32(const float* __restrict__ dbpart, int slices, int chunk, int cw, f
   if (v >= cw) return;
   float s = 0.f;
   for (int z = 0; z < slices; ++z) s += dbpart[static_cast<int64_t>(z) * chunk + v];
-  db[v] = s;
+  db[v] = s * kDzUnscale;
 }
 
 // ---------------------------------------------------------------------------------------

@@ -66,6 +66,29 @@ def test_f32_split_keeps_the_range(e):
         assert np.abs(c - ref).max() <= bar
 
 
+@pytest.mark.parametrize("chunk", [0, 256])
+def test_f32_gradients_of_the_least_probabilities(chunk):
+    """Classes whose probabilities come near fp32's least (7e-34 to 7e-38) have gradient rows and bias
+    gradients with an error of the exponent's rounding: 2^-18 at 124 binary places."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("f32", [90, 41], 40, 700, 8, u_frac=0.1, w_std=0.02)
+    b = np.zeros(700, np.float32)
+    rare = np.setdiff1d(np.arange(1, 700, 9), wl.targets)
+    b[rare] = -np.linspace(70, 79, rare.size)  # the logits themselves are within 1 of each other
+    H, W, y = to_dev(wl)
+    out = prunedctc.pruned_ctc_fwd_bwd(H, W, y, wl.input_lengths, wl.target_lengths, 0, wl.beam, chunk=chunk,
+                                       bias=torch.from_numpy(b).cuda(), want_db=True)
+    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, 0, wl.beam, bias=b)
+    dW, db = out["dW"].cpu().numpy()[rare], out["db"].cpu().numpy()[rare]
+    scale = np.abs(ref["dW"][rare]).max(1, keepdims=True)
+    say(f"least probabilities: largest dW row {scale.max():.2g}, least {scale.min():.2g}")
+    assert scale.min() < 5e-36
+    assert (np.abs(dW - ref["dW"][rare]) / scale).max() <= 3 * 2.0 ** -18
+    assert np.abs(db / ref["db"][rare] - 1).max() <= 3 * 2.0 ** -18
+
+
 def test_f32_split_drops_less_than_a_rounding():
     """Logits that are one product, of values chosen so that a first part cut to bf16 instead of
     rounded would drop the most (2^-22.4 of the product): the mean error, in which roundings cancel,
