@@ -39,27 +39,27 @@ constexpr float kDzScale = 16777216.f, kDzUnscale = 1.f / kDzScale;
   char* const st[4] = {st0_, st1_, st2_, st3_};
 
 // Workgroup of a partitioned vocabulary pass: `run` vocabulary tiles of partition p for frame
-// tile mt; epi(v0, lane, acc) after each tile, the bias added.
+// tile mt; epi(v0, lane, acc) after each tile, the bias added.  A tile's bias waits in LDS (two
+// tiles' room, in turn: no wavefront is two tiles ahead of another), so a partition may be any
+// number of tiles.
 template <bool BIAS, class Epi>
 __device__ __forceinline__ void vocab_tiles(const float* H, int M, int D, const float* W, const float* bias, int m0,
-                                            int vbeg, int vend, float* bsh, char* const (&st)[4], Epi&& epi) {
+                                            int vbeg, int vend, char* const (&st)[4], Epi&& epi) {
+  __shared__ __attribute__((aligned(16))) float bsh[2][BIAS ? kTile : 4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ntiles = (vend - vbeg + kTile - 1) / kTile;
-  if (BIAS) {
-    for (int r = tid; r < ntiles * kTile; r += GZ::kThreads) bsh[r] = (vbeg + r < vend) ? bias[vbeg + r] : 0.f;
-    __syncthreads();
-  }
   const GOp A{W, D, vend, D, nullptr};
   const GOp B{H, D, M, D, nullptr};
   f32x16 acc[GZ::FR][GZ::FC];
   for (int i = 0; i < ntiles; ++i) {
     const int v0 = vbeg + i * kTile;
+    if (BIAS && tid < kTile) bsh[i & 1][tid] = (v0 + tid < vend) ? bias[v0 + tid] : 0.f;
     GZ::run(A, B, v0, m0, 0, D, st, acc);
     // an opaque lane: what the epilogue derives from it is not kept in registers through the next
     // tile's products (it would spill there)
     int el = lane;
     asm volatile("" : "+v"(el));
-    if (BIAS) bias_add<GZ::FR, GZ::FC, GZ>(acc, bsh + i * kTile, wave, el);
+    if (BIAS) bias_add<GZ::FR, GZ::FC, GZ>(acc, bsh[i & 1], wave, el);
     if (v0 + kTile > vend) mask_rows_inf<GZ::FR, GZ::FC, GZ>(acc, v0, vend, wave, el);
     epi(v0, el, acc);
   }
@@ -93,7 +93,6 @@ template <bool BIAS>
 __global__ void __launch_bounds__(512, 1)
 lse_partial_f32(const float* __restrict__ H, int M, int D, const float* __restrict__ W, const float* __restrict__ bias,
                 int V, int P, int vper, float2* __restrict__ partials) {
-  extern __shared__ float bsh[];  // BIAS: b over this partition's rows
   PCTC_F3_STAGES
   int mt, p;
   if (!grouped_tile(xcd_swz(blockIdx.x, gridDim.x), (M + kTile - 1) / kTile, P, mt, p)) return;
@@ -105,7 +104,7 @@ lse_partial_f32(const float* __restrict__ H, int M, int D, const float* __restri
     run_max[j] = -INFINITY;
     run_sum[j] = 0.f;
   }
-  vocab_tiles<BIAS>(H, M, D, W, bias, m0, vbeg, vend, bsh, st, [&](int, int, f32x16 (&a)[GZ::FR][GZ::FC]) {
+  vocab_tiles<BIAS>(H, M, D, W, bias, m0, vbeg, vend, st, [&](int, int, f32x16 (&a)[GZ::FR][GZ::FC]) {
     lse_tile_update<GZ::FR, GZ::FC, GZ>(a, run_max, run_sum);
   });
   lse_store_partials<GZ>(run_max, run_sum, st0_, wave, lane, m0, M, partials + static_cast<int64_t>(p) * M);
@@ -115,7 +114,6 @@ template <bool BIAS>
 __global__ void __launch_bounds__(512, 1)
 amax_partial_f32(const float* __restrict__ H, int M, int D, const float* __restrict__ W,
                  const float* __restrict__ bias, int V, int P, int vper, float2* __restrict__ partials) {
-  extern __shared__ float bsh[];
   PCTC_F3_STAGES
   int mt, p;
   if (!grouped_tile(xcd_swz(blockIdx.x, gridDim.x), (M + kTile - 1) / kTile, P, mt, p)) return;
@@ -128,7 +126,7 @@ amax_partial_f32(const float* __restrict__ H, int M, int D, const float* __restr
     bv[j] = -INFINITY;
     bi[j] = 0x7fffffff;
   }
-  vocab_tiles<BIAS>(H, M, D, W, bias, m0, vbeg, vend, bsh, st, [&](int v0, int el, f32x16 (&a)[GZ::FR][GZ::FC]) {
+  vocab_tiles<BIAS>(H, M, D, W, bias, m0, vbeg, vend, st, [&](int v0, int el, f32x16 (&a)[GZ::FR][GZ::FC]) {
     amax_tile_update<GZ::FR, GZ::FC, GZ>(a, v0, wave, el, bv, bi);
   });
   amax_store_partials<GZ>(bv, bi, st0_, wave, lane, m0, M, partials + static_cast<int64_t>(p) * M);
@@ -440,7 +438,7 @@ hipError_t launch_lse_partial_f32(const float* H, int M, int D, const float* W, 
   const dim3 grid(grouped_grid((M + kTile - 1) / kTile, P));
   Prof pr("lse_partial", stream);
   if (bias)
-    hipLaunchKernelGGL(lse_partial_f32<true>, grid, dim3(512), vper * sizeof(float), stream, H, M, D, W, bias, V, P,
+    hipLaunchKernelGGL(lse_partial_f32<true>, grid, dim3(512), 0, stream, H, M, D, W, bias, V, P,
                        vper, partials);
   else
     hipLaunchKernelGGL(lse_partial_f32<false>, grid, dim3(512), 0, stream, H, M, D, W, bias, V, P, vper, partials);
@@ -455,7 +453,7 @@ hipError_t launch_amax_partial_f32(const float* H, int M, int D, const float* W,
   const dim3 grid(grouped_grid((M + kTile - 1) / kTile, P));
   Prof pr("amax_partial", stream);
   if (bias)
-    hipLaunchKernelGGL(amax_partial_f32<true>, grid, dim3(512), vper * sizeof(float), stream, H, M, D, W, bias, V, P,
+    hipLaunchKernelGGL(amax_partial_f32<true>, grid, dim3(512), 0, stream, H, M, D, W, bias, V, P,
                        vper, partials);
   else
     hipLaunchKernelGGL(amax_partial_f32<false>, grid, dim3(512), 0, stream, H, M, D, W, bias, V, P, vper, partials);

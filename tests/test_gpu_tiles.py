@@ -383,3 +383,21 @@ def test_grouped_bias_normaliser(M, D, V):
     ref = oracle.grouped_logprobs(wl.H, wl.W, u, bias=b.cpu().numpy())
     assert np.abs(f["lam"].cpu().numpy() - ref["lam"]).max() < 2e-5
     assert np.abs(f["logp"].cpu().numpy() - ref["logp"]).max() < 5e-5
+
+
+def test_grouped_fp32_many_classes():
+    """An fp32 export of more classes than 32 tiles a partition: partitions of any length."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    M, D, V = 3, 8, 2_200_000
+    g = np.random.default_rng(4)
+    H = g.standard_normal((M, D)).astype(np.float32)
+    W = (g.standard_normal((V, D)) * 0.3).astype(np.float32)
+    b = g.standard_normal(V).astype(np.float32)
+    u = np.array([7, 1, 1_100_000, V - 1], np.int32)
+    say(f"grouped fp32 V={V}")
+    f = prunedctc.grouped_logprobs(*(torch.from_numpy(x).cuda() for x in (H, W, u, b)))
+    ref = oracle.grouped_logprobs(H, W, u, bias=b)
+    assert np.abs(f["lam"].cpu().numpy() - ref["lam"]).max() < 2e-5
+    assert np.abs(f["logp"].cpu().numpy() - ref["logp"]).max() < 5e-5
