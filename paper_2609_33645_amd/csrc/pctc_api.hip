@@ -856,19 +856,41 @@ int32_t pctc_ctc_dp(const float* S, int32_t ldS, int32_t K_max, const int32_t* y
   return PCTC_OK;
 }
 
-// Greedy decode workspace: argmax partials, frame offsets, the ids when not returned, H transposed.
-static size_t greedy_layout(int32_t N, int32_t M, int32_t D, size_t* o_toff, size_t* o_ids, size_t* o_ht) {
+// Greedy decode workspace: argmax partials, frame offsets, the ids when not returned.  Returns its size.
+static size_t greedy_layout(int32_t N, int32_t M, int32_t D, size_t* o_toff, size_t* o_ids) {
   const size_t part = lse_partial_bytes(M > 0 ? M : 1, D);
   *o_toff = part;
   *o_ids = part + align_up(static_cast<size_t>(N + 1) * sizeof(int32_t), 256);
-  *o_ht = *o_ids + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(int32_t), 256);
-  return *o_ht + (amax_reads_ht_bf16(M, D) ? lse_ht_bytes_bf16(M, D) : 0);
+  return *o_ids + align_up(static_cast<size_t>(M > 0 ? M : 1) * sizeof(int32_t), 256);
+}
+
+// Where a bf16 argmax that reads H transposed keeps it (0: it does not read it): in what the
+// partitions of this V leave of the partials (V = 180,000: up to D = 640), else past the end of the
+// layout, where a caller may bring room for it.  end: the workspace that this needs.
+static size_t greedy_ht(int dt, int32_t M, int32_t D, int32_t V, size_t base, size_t* end) {
+  *end = base;
+  if (dt != 1 || !amax_reads_ht_bf16(M, D)) return 0;
+  const size_t ht = lse_ht_bytes_bf16(M, D);
+  const size_t used = align_up(static_cast<size_t>(lse_parts_bf16(M, D, V, false)) * M * sizeof(float2), 256);
+  if (used + ht <= lse_partial_bytes(M, D)) return used;
+  *end = base + ht;
+  return base;
 }
 
 size_t pctc_greedy_workspace_size(int32_t N, int32_t M, int32_t D) {
   if (N < 0 || M < 0 || D <= 0 || D > PCTC_MAX_DIM) return 0;
-  size_t a, b, c;
-  return greedy_layout(N, M, D, &a, &b, &c);
+  size_t a, b;
+  return greedy_layout(N, M, D, &a, &b);
+}
+
+size_t pctc_greedy_workspace_size_ex(pctc_dtype dtype, int32_t N, int32_t M, int32_t D, int32_t V) {
+  if ((dtype != PCTC_F32 && dtype != PCTC_BF16) || N < 0 || M < 0 || D <= 0 || D > PCTC_MAX_DIM || V <= 1 ||
+      V > PCTC_MAX_VOCAB)
+    return 0;
+  size_t a, b, end;
+  const size_t base = greedy_layout(N, M, D, &a, &b);
+  greedy_ht(dtype == PCTC_BF16 ? 1 : 0, M, D, V, base, &end);
+  return end;
 }
 
 int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const void* W, const float* bias, int32_t V,
@@ -886,8 +908,8 @@ int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const voi
   if (M64 > INT32_MAX) return PCTC_EINVAL;
   const int M = static_cast<int>(M64);
   if (M > 0 && (!H || !tokens || !token_lengths)) return PCTC_EINVAL;
-  size_t o_toff, o_ids, o_ht;
-  const size_t need = greedy_layout(N, M, D, &o_toff, &o_ids, &o_ht);
+  size_t o_toff, o_ids, ht_end;
+  const size_t need = greedy_layout(N, M, D, &o_toff, &o_ids);
   if (!workspace || workspace_bytes < need) return PCTC_EWORKSPACE;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return PCTC_EINVAL;
   if (N == 0) return PCTC_OK;
@@ -898,10 +920,11 @@ int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const voi
   int32_t* dtoff = reinterpret_cast<int32_t*>(ws + o_toff);
   PCTC_HIP(hipMemcpyAsync(dtoff, toff.data(), (N + 1) * sizeof(int32_t), hipMemcpyHostToDevice, stream));
   int32_t* idv = ids ? ids : reinterpret_cast<int32_t*>(ws + o_ids);
-  PCTC_HIP(launch_greedy(dtype == PCTC_BF16 ? 1 : 0, H, M, D, W, bias, V, dtoff, N, blank,
-                         reinterpret_cast<float2*>(ws), idv, tokens, token_lengths, stream,
-                         dtype == PCTC_BF16 && amax_reads_ht_bf16(M, D) ? reinterpret_cast<uint16_t*>(ws + o_ht)
-                                                                        : nullptr));
+  const int dt = dtype == PCTC_BF16 ? 1 : 0;
+  const size_t o_ht = greedy_ht(dt, M, D, V, need, &ht_end);
+  uint16_t* Ht = o_ht && workspace_bytes >= ht_end ? reinterpret_cast<uint16_t*>(ws + o_ht) : nullptr;
+  PCTC_HIP(launch_greedy(dt, H, M, D, W, bias, V, dtoff, N, blank, reinterpret_cast<float2*>(ws), idv, tokens,
+                         token_lengths, stream, Ht));
   PCTC_HIP(hipStreamSynchronize(stream));  // the host offsets must outlive the copy
   prof_flush();
   return PCTC_OK;

@@ -69,7 +69,7 @@ hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W
                            hipStream_t stream, float* Gz = nullptr);
 
 // ---- greedy emission head -----------------------------------------------------------------
-// Ht: scratch of lse_ht_bytes_bf16(M, D) where amax_reads_ht_bf16 (bf16), else null.
+// Ht (null: none): scratch of lse_ht_bytes_bf16(M, D) for H transposed, where amax_reads_ht_bf16.
 // partials: lse_partial_bytes(M, D); ids [M]; tokens [M] (utterance n at toff[n]); lengths [N].
 hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
                          const int32_t* toff, int N, int blank, float2* partials, int32_t* ids, int32_t* tokens,

@@ -81,6 +81,8 @@ def lib() -> ctypes.CDLL:
     L.pctc_ctc_dp.restype = c_i32
     L.pctc_greedy_workspace_size.argtypes = [c_i32, c_i32, c_i32]
     L.pctc_greedy_workspace_size.restype = c_sz
+    L.pctc_greedy_workspace_size_ex.argtypes = [c_i32, c_i32, c_i32, c_i32, c_i32]
+    L.pctc_greedy_workspace_size_ex.restype = c_sz
     L.pctc_greedy_decode.argtypes = [c_i32, c_p, c_i32, c_p, c_p, c_i32, i32p, c_i32, c_i32, c_p, c_p, c_p, c_p, c_sz,
                                      c_p]
     L.pctc_greedy_decode.restype = c_i32
@@ -405,7 +407,7 @@ def greedy_decode(H: torch.Tensor, W: torch.Tensor, input_lengths, blank: int = 
     ids = torch.empty(max(M, 1), dtype=torch.int32, device=dev)
     tokens = torch.empty(max(M, 1), dtype=torch.int32, device=dev)
     lengths = torch.empty(max(N, 1), dtype=torch.int32, device=dev)
-    ws = _workspace(int(L.pctc_greedy_workspace_size(N, M, D)), dev)
+    ws = _workspace(int(L.pctc_greedy_workspace_size_ex(dt, N, M, D, V)), dev)
     code = L.pctc_greedy_decode(dt, _ptr(H), D, _ptr(W), _ptr(bias), V, _i32p(T), N, int(blank), _ptr(ids),
                                 _ptr(tokens), _ptr(lengths), ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel()),
                                 _stream(stream))

@@ -71,6 +71,8 @@ def test_host_side_sizing_rules():
     lib.pctc_lse_scratch_bytes.argtypes = [i32, i32]
     lib.pctc_greedy_workspace_size.restype = sz
     lib.pctc_greedy_workspace_size.argtypes = [i32, i32, i32]
+    lib.pctc_greedy_workspace_size_ex.restype = sz
+    lib.pctc_greedy_workspace_size_ex.argtypes = [i32, i32, i32, i32, i32]
     lib.pctc_bwd_chunk.restype = i32
     lib.pctc_bwd_chunk.argtypes = [i32, i32, i32, i32, i32]
     lib.pctc_bwd_scratch_bytes.restype = sz
@@ -84,6 +86,18 @@ def test_host_side_sizing_rules():
     assert lib.pctc_lse_scratch_bytes(-1, 512) == 0 and lib.pctc_lse_scratch_bytes(10, 0) == 0
     assert lib.pctc_greedy_workspace_size(16, 4215, 4096) > lib.pctc_greedy_workspace_size(16, 4215, 512) > 0
     assert lib.pctc_greedy_workspace_size(16, 4215, 0) == 0
+    # argmax partials, frame offsets, ids: nothing that only a bf16 head would read
+    for M, D in ((4215, 512), (4215, 1024), (300, 512), (4215, 4096)):
+        parts = 1024 if D >= 2048 else 256
+        base = up(parts * M * 8) + up(17 * 4) + up(M * 4)
+        assert lib.pctc_greedy_workspace_size(16, M, D) == base
+        assert lib.pctc_greedy_workspace_size_ex(0, 16, M, D, 180_000) == base
+        # a bf16 argmax of many frames of a narrow head has H transposed, past the layout where the
+        # partials leave no room (V = 180,000: 88 partitions written of 256)
+        ht = up(2 * D * ((M + 63) // 64 * 64)) if (M, D) == (4215, 1024) else 0
+        assert lib.pctc_greedy_workspace_size_ex(1, 16, M, D, 180_000) == base + ht
+    assert lib.pctc_greedy_workspace_size_ex(2, 16, 4215, 512, 180_000) == 0
+    assert lib.pctc_greedy_workspace_size_ex(1, 16, 4215, 512, 1) == 0
     # default chunk: the fewest equal chunks (multiples of 256) whose bf16 gradient fits ~512 MiB;
     # narrow bf16 heads (D < 2048) round to whole normaliser partitions (2048 columns), so that
     # the normaliser can write the first chunk's gradient rows

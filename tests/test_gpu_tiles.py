@@ -366,6 +366,35 @@ def test_greedy_transposed_frames(M, V, bias):
     assert np.all(Z[np.arange(M), ids] >= top - 1e-5 * np.abs(top))
 
 
+@pytest.mark.parametrize("D", [256, 1024])
+def test_greedy_workspace_sizes(D):
+    """The same ids and tokens with the smallest workspace (D = 256: H transposed in what the
+    partials leave; D = 1024: none) and with room for H transposed."""
+    import ctypes
+
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    L, N, V = prunedctc.lib(), 2, 3000
+    wl = _fixed("bf16", [400, 301], D, V, D, u_frac=0.0, w_std=0.1)
+    H, W, _ = to_dev(wl)
+    T, M = wl.input_lengths, wl.M
+    least, most = L.pctc_greedy_workspace_size(N, M, D), L.pctc_greedy_workspace_size_ex(1, N, M, D, V)
+    assert (most > least) == (D == 1024)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    got = []
+    for size in (least, most):
+        ws = prunedctc._workspace(size, H.device)
+        ids, tok, n = (torch.full((k,), -7, dtype=torch.int32, device="cuda") for k in (M, M, N))
+        assert L.pctc_greedy_decode(1, p(H), D, p(W), None, V, prunedctc._i32p(T), N, 0, p(ids), p(tok), p(n), p(ws),
+                                    ctypes.c_size_t(size), prunedctc._stream(None)) == 0
+        got.append((ids, tok, n))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    ws = prunedctc._workspace(least, H.device)
+    assert L.pctc_greedy_decode(1, p(H), D, p(W), None, V, prunedctc._i32p(T), N, 0, None, p(tok), p(n), p(ws),
+                                ctypes.c_size_t(least - 1), prunedctc._stream(None)) == -4
+
+
 @pytest.mark.parametrize("M,D,V", [(70, 128, 700), (300, 256, 2049), (33, 72, 300), (260, 2048, 513)])
 def test_grouped_bias_normaliser(M, D, V):
     """The complement's normaliser with its -inf bias (frames from H transposed where D is a multiple
