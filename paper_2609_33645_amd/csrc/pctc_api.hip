@@ -709,6 +709,45 @@ static hipError_t noalloc_scratch(char** out) {
   return hipSuccess;
 }
 
+// Layout of a call of the allocation-free entry (its total is more than the scratch where the batch does
+// not fit).
+static Layout noalloc_layout(pctc_dtype dtype, int32_t N, const int32_t* T, const int32_t* U, int32_t D, int32_t V,
+                             float beam, int32_t chunk, bool want_dW) {
+  auto layout = [&](int c, bool lean) { return make_layout(dtype, N, T, U, D, V, beam, c, want_dW, false, lean); };
+  const Layout L = layout(chunk, false);
+  if (L.total <= kNoAllocScratchBytes) return L;
+  // The widest backward chunk (a multiple of 256 columns; or the caller's) whose layout fits the
+  // scratch; the layout is not monotone in the chunk (the products' slice counts change with
+  // it), so widths are tried one by one, down from the widest whose gradient buffer fits beside
+  // what every width needs.  The lean plan, whose products have few slices (and which leaves out
+  // what only the two-stream schedule needs), is taken where the other fits at no width or at
+  // less than half of the lean one's, so its widths are tried above twice the other's only.
+  auto widest = [&](bool lean, int above, Layout* out) {
+    int c = chunk;
+    if (!chunk) {
+      const Layout s = layout(256, lean);
+      // needed at any width: all but the gradient buffer, the slices, and what may be lodged there
+      const size_t lodged = align_up(static_cast<size_t>(s.M) * s.ldS * sizeof(double), 256) +
+                            align_up(lse_partial_bytes(s.M, D), 256);
+      const size_t any = s.bwd.ht_bytes + s.bwd.lam2_bytes + s.bwd.hst_bytes + s.total -
+                         std::min(s.total, align_up(s.bwd.total, 256) + lodged);
+      const size_t room = kNoAllocScratchBytes - std::min(kNoAllocScratchBytes, any);
+      const size_t cols = room / (static_cast<size_t>(std::max(s.M, 1)) * (dtype == PCTC_BF16 ? 2 : 4));
+      c = static_cast<int>(std::min<size_t>(L.bwd.chunk, cols)) / 256 * 256;
+    }
+    for (; c > above; c -= 256) {
+      *out = layout(c, lean);
+      if (out->total <= kNoAllocScratchBytes) return c;
+      if (chunk) break;
+    }
+    return 0;
+  };
+  Layout full, lean;
+  const int cf = widest(false, 0, &full);
+  const int cl = (chunk && cf) ? 0 : widest(true, 2 * cf, &lean);
+  return cl > 0 ? lean : (cf > 0 ? full : L);
+}
+
 extern "C" {
 
 int32_t pruned_ctc_fwd_bwd_ex(pctc_dtype dtype, const void* H, int32_t D, const void* W, const float* bias, int32_t V,
@@ -739,26 +778,7 @@ int32_t pruned_ctc_fwd_bwd_noalloc(pctc_dtype dtype, const void* H, int32_t D, c
   int32_t st = check_args(dtype, N, input_lengths, target_lengths, D, V, beam, chunk);
   if (st != PCTC_OK) return st;
   if (blank < 0 || blank >= V || !loss || !W || misaligned16(W) || misaligned16(H)) return PCTC_EINVAL;
-  Layout L = make_layout(dtype, N, input_lengths, target_lengths, D, V, beam, chunk, dW != nullptr, false);
-  if (L.total > kNoAllocScratchBytes) {
-    // the widest backward chunk (a multiple of 256 columns; or the caller's) whose layout fits the
-    // scratch; the layout is not monotone in the chunk (the products' slice counts change with
-    // it), so every width is tried from the default down.  The lean plan, whose products have
-    // few slices (and which leaves out what only the two-stream schedule needs), is taken where the other fits at no width or at less than half of its width
-    auto widest = [&](bool lean, Layout* out) {
-      int c = chunk ? chunk : L.bwd.chunk / 256 * 256;
-      for (; c >= 1; c -= 256) {
-        *out = make_layout(dtype, N, input_lengths, target_lengths, D, V, beam, c, dW != nullptr, false, lean);
-        if (out->total <= kNoAllocScratchBytes) return c;
-        if (chunk) break;
-      }
-      return 0;
-    };
-    Layout full, lean;
-    const int cf = widest(false, &full), cl = widest(true, &lean);
-    if (cl > 0 && 2 * cf < cl) L = lean;
-    else if (cf > 0) L = full;
-  }
+  const Layout L = noalloc_layout(dtype, N, input_lengths, target_lengths, D, V, beam, chunk, dW != nullptr);
   if (L.total > kNoAllocScratchBytes) {
     snprintf(g_last_error, sizeof(g_last_error),
              "the batch needs %zu bytes of scratch; the allocation-free entry point holds %zu", L.total,
