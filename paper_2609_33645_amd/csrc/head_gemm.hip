@@ -322,7 +322,7 @@ BwdPlan plan_bwd(int dtype, int M, int D, int V, int chunk, bool lean) {
       }
       if (fill >= 0.9) break;
     }
-    if (!lean && tiles * maxs < 256 && p.chunk > 256 * maxs) {
+    if (!lean && M > 0 && tiles * maxs < 256 && p.chunk > 256 * maxs) {
       // few frames: eight slices leave most of the chip idle (331 frames, D = 512, chunks of
       // 60,000 columns: 16 or 32 workgroups, 160 us a launch).  The count whose launch is
       // shortest by 0.7 us a 32-deep k-tile and 4 us a workgroup, with every slice's partial sums

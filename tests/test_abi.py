@@ -210,3 +210,32 @@ def test_misaligned_head_pointers_rejected_on_host():
         rc = lib.pruned_ctc_fwd_bwd(1, H, 64, W, 100, ok, p(T), p(U), 2, 0, 16.0, 0, ok, None, None, None, None,
                                     ok, 1 << 30, None)
         assert rc == -1, (hex(H), hex(W), rc)
+
+
+def test_plans_without_undefined_conversions(tmp_path):
+    """The backward's plan of every kind of batch, the empty one among them, compiled (host code)
+    with the compiler's check of float-to-int conversions."""
+    import subprocess
+
+    from paper_2609_33645_amd import build
+    objs = [os.path.join(build.BUILD, os.path.splitext(x)[0] + ".o") for x in build.SOURCES if x != "head_gemm.hip"]
+    if not all(os.path.exists(o) for o in objs):
+        pytest.skip("library not built")
+    src = tmp_path / "plans.hip"
+    src.write_text("""#include "head_gemm.hip"
+int main() {
+  for (int dt = 0; dt < 2; ++dt)
+    for (int M : {0, 1, 331, 20000})
+      for (int D : {8, 512, 4096})
+        for (int V : {2, 5000, 180000})
+          for (int chunk : {0, 256, 16384})
+            for (bool lean : {false, true}) pctc::plan_bwd(dt, M, D, V, chunk, lean);
+}
+""")
+    check = ["-Xarch_host", "-fsanitize=float-cast-overflow"]
+    exe, obj = str(tmp_path / "plans"), str(tmp_path / "plans.o")
+    subprocess.run([build.hipcc(), *build.COMMON, "-w", "-O1", "-I", build.CSRC, *check, "-Xarch_host",
+                    "-fno-sanitize-recover=float-cast-overflow", "-c", str(src), "-o", obj], check=True)
+    subprocess.run([build.hipcc(), "--offload-arch=gfx950", *check, obj, *objs, "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
