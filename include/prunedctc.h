@@ -97,6 +97,13 @@ int32_t pctc_normaliser_chunk_columns(pctc_dtype dtype, int32_t N, const int32_t
                                       const int32_t* target_lengths, int32_t D, int32_t V, float beam,
                                       int32_t chunk, int32_t flags);
 
+/* 1 when a fused bf16 call of this shape (with gradients) takes the lattice for more than half as
+ * long as the dense part of the backward beside it and runs it ungated on the second stream, 0 when
+ * it gates the lattice's kernels to run beside that part's recomputes (same results either way).
+ * 0 also for fp32, which has one stream, and on invalid arguments.  Host only; no device work. */
+int32_t pctc_lattice_leads(pctc_dtype dtype, int32_t N, const int32_t* input_lengths,
+                           const int32_t* target_lengths, int32_t D, int32_t V, float beam);
+
 /* Forward and backward pass of Pruned CTC (Algorithm 1).
  *
  * H        [M, D] row-major, dtype; M = sum input_lengths.  D must be a multiple of 8 and at

@@ -390,6 +390,13 @@ int32_t pctc_normaliser_chunk_columns(pctc_dtype dtype, int32_t N, const int32_t
   return L.eparts > 0 ? std::min(L.bwd.chunk, V) : 0;
 }
 
+int32_t pctc_lattice_leads(pctc_dtype dtype, int32_t N, const int32_t* input_lengths, const int32_t* target_lengths,
+                           int32_t D, int32_t V, float beam) {
+  if (check_args(dtype, N, input_lengths, target_lengths, D, V, beam, 0) != PCTC_OK) return 0;
+  if (dtype != PCTC_BF16 || N == 0) return 0;
+  return lattice_leads(plan_dp(N, input_lengths, target_lengths, beam), t_max_of(N, input_lengths), D, V) ? 1 : 0;
+}
+
 const char* pctc_status_string(int32_t status) {
   switch (status) {
     case PCTC_OK: return "ok";

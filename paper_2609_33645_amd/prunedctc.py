@@ -58,6 +58,8 @@ def lib() -> ctypes.CDLL:
     L.pruned_ctc_fwd_bwd_ex.argtypes = [c_i32, c_p, c_i32, c_p, c_p, c_i32, c_p, i32p, i32p, c_i32, c_i32, c_f, c_i32,
                                         c_p, c_p, c_p, c_p, c_p, c_p, c_p, c_p, c_sz, c_p]
     L.pruned_ctc_fwd_bwd_ex.restype = c_i32
+    L.pctc_lattice_leads.argtypes = [c_i32, c_i32, i32p, i32p, c_i32, c_i32, c_f]
+    L.pctc_lattice_leads.restype = c_i32
     L.pctc_noalloc_scratch_bytes.argtypes = []
     L.pctc_noalloc_scratch_bytes.restype = c_sz
     L.pruned_ctc_fwd_bwd_noalloc.argtypes = [c_i32, c_p, c_i32, c_p, c_p, c_i32, c_p, i32p, i32p, c_i32, c_i32, c_f,
@@ -182,6 +184,14 @@ def normaliser_chunk_columns(dtype: int, input_lengths, target_lengths, D: int, 
     U = _host_i32(target_lengths)
     return int(lib().pctc_normaliser_chunk_columns(dtype, T.size, _i32p(T), _i32p(U), D, V, float(beam), chunk,
                                                    0 if want_dW else WS_NO_DW))
+
+
+def lattice_leads(dtype: int, input_lengths, target_lengths, D: int, V: int, beam: float) -> bool:
+    """Whether a fused call of this shape runs its lattice ungated beside the dense part of the
+    backward (see pctc_lattice_leads)."""
+    T = _host_i32(input_lengths)
+    U = _host_i32(target_lengths)
+    return bool(lib().pctc_lattice_leads(dtype, T.size, _i32p(T), _i32p(U), D, V, float(beam)))
 
 
 def bwd_chunk(dtype: int, M: int, D: int, V: int, chunk: int = 0) -> int:

@@ -212,6 +212,34 @@ def test_misaligned_head_pointers_rejected_on_host():
         assert rc == -1, (hex(H), hex(W), rc)
 
 
+@pytest.mark.skipif(not os.path.exists(LIB), reason="library not built")
+def test_lattice_schedule_rule():
+    """Where the lattice runs ungated: few frames of work beside many sequential ones."""
+    import numpy as np
+    import torch  # noqa: F401
+    lib = ctypes.CDLL(LIB)
+    i32, i32p = ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)
+    lib.pctc_lattice_leads.argtypes = [i32, i32, i32p, i32p, i32, i32, ctypes.c_float]
+
+    def leads(T, U, D, V, beam=16.0, dtype=1):
+        T, U = np.array(T, np.int32), np.array(U, np.int32)
+        return lib.pctc_lattice_leads(dtype, T.size, T.ctypes.data_as(i32p), U.ctypes.data_as(i32p), D, V, beam)
+
+    T16 = np.linspace(150, 375, 16).astype(int)
+    assert leads([331], [55], 512, 180_000) == 1          # one utterance
+    assert leads(T16, T16 // 6, 512, 180_000) == 0        # a training batch of them
+    assert leads([1500] * 2, [400] * 2, 5120, 151_936) == 0
+    assert leads([1500] * 2, [400] * 2, 512, 151_936) == 1
+    assert leads([331], [55], 512, 180_000, dtype=0) == 0  # fp32: one stream
+    assert leads([331], [55], 500, 180_000) == 0           # invalid arguments
+    assert leads([], [], 512, 180_000) == 0
+    # more classes can only end it, longer targets only bring it on
+    edge = [leads([40] * 40, [6] * 40, 512, V) for V in range(1000, 80_000, 1000)]
+    assert edge == sorted(edge, reverse=True) and edge[0] == 1 and edge[-1] == 0
+    edge = [leads([300] * 3, [u] * 3, 512, 300_000) for u in range(1, 290, 8)]
+    assert edge == sorted(edge)
+
+
 def test_plans_without_undefined_conversions(tmp_path):
     """The backward's plan of every kind of batch, the empty one among them, compiled (host code)
     with the compiler's check of float-to-int conversions."""

@@ -6,6 +6,7 @@ loss relative error <= 2e-3 and gradient cosine >= 0.999 (plus tighter checks th
 document the achieved accuracy).
 """
 import dataclasses
+import functools
 import math
 
 import numpy as np
@@ -432,20 +433,72 @@ def test_e2e_tight_alignment(beam):
     _check_e2e(wl, res, ref, fp32=False)
 
 
-@pytest.mark.parametrize("t_max", [512, 513])
-def test_e2e_lattice_front_schedules(t_max):
-    """The two-stream schedule starts the lattice's Viterbi front beside the first chunk's dW
-    product when no utterance is longer than 512 frames, and as soon as S is formed otherwise;
-    both orders give the oracle's loss and gradients (three backward chunks, so the gated
-    log-sum passes, the union part and the final reduction all run on the second stream)."""
-    rng = np.random.default_rng(512)
-    T = np.array([t_max, 301, 447], np.int32)
-    U = (T // 4).astype(np.int32)
-    wl = workloads.synthesize(name=f"front{t_max}", dtype="bf16", T=T, U=U, D=128, V=3001, rng=rng, beam=16.0)
-    say(f"e2e lattice front schedule T={T.tolist()} U={U.tolist()} V={wl.V} chunk=1024")
-    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam)
-    res = run_gpu(wl, chunk=1024)
-    _check_e2e(wl, res, ref, fp32=False)
+# Both schedules of the second stream (pctc_lattice_leads): the least vocabulary that 64 utterances
+# of 20 frames have their lattice gated at, and one class fewer, where it runs ungated.
+_SCHED_T = np.full(64, 20, np.int32)
+_SCHED_U = np.full(64, 4, np.int32)
+_SCHED_D, _SCHED_BEAM = 512, 16.0
+
+
+@functools.lru_cache(maxsize=None)
+def _gated_from():
+    from paper_2609_33645_amd import prunedctc
+    lo, hi = 2, 400_000  # leads at lo, gated at hi
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lead = prunedctc.lattice_leads(prunedctc.PCTC_BF16, _SCHED_T, _SCHED_U, _SCHED_D, mid, _SCHED_BEAM)
+        lo, hi = (mid, hi) if lead else (lo, mid)
+    return hi
+
+
+@functools.lru_cache(maxsize=None)
+def _schedule_case(gated, bias):
+    """(workload, bias, oracle's result).  "miss": one target's bias is -inf, "nan": a frame is not a
+    number; the forecast of that utterance is wrong and the backward done again in the plain order."""
+    V = _gated_from() - (0 if gated else 1)
+    wl = workloads.synthesize(name="sched", dtype="bf16", T=_SCHED_T, U=_SCHED_U, D=_SCHED_D, V=V, beam=_SCHED_BEAM,
+                              rng=np.random.default_rng(20))
+    b = None
+    if bias == "nan":
+        wl.H[25, 3] = np.nan  # a frame of the second utterance
+    elif bias:
+        b = np.random.default_rng(21).standard_normal(V).astype(np.float32) * 0.5
+        if bias == "miss":
+            b[int(wl.targets[5])] = -np.inf
+    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam, bias=b)
+    return wl, b, ref
+
+
+@pytest.mark.parametrize("gated", [True, False])
+@pytest.mark.parametrize("chunk,outputs,bias", [
+    (0, "dH dW", None), (65_536, "dH dW", None),   # one chunk
+    (32_768, "dH dW", None), (32_768, "dH", None), (32_768, "dW", None),
+    (16_384, "dH dW", None), (16_384, "dH", None), (16_384, "dW", None),
+    (256, "dH dW", None), (256, "dH", None),       # dH in one slice: summed in place
+    (16_384, "dH dW db", "plain"), (65_536, "dH dW db", "plain"), (16_384, "db", "plain"),
+    (16_384, "dH dW db", "miss"), (256, "dH dW db", "miss"), (0, "dH dW", "nan"), (256, "dH dW", "nan"),
+])
+def test_e2e_lattice_schedules(gated, chunk, outputs, bias):
+    """Gated and ungated lattice beside the dense part, on both sides of the rule's edge: one, two and
+    more chunks, dH in slices and in place, a frozen head, dW or db alone, and a wrong forecast."""
+    import torch
+    from paper_2609_33645_amd import prunedctc
+    wl, b, ref = _schedule_case(gated, bias)
+    assert prunedctc.lattice_leads(prunedctc.PCTC_BF16, wl.input_lengths, wl.target_lengths, wl.D, wl.V,
+                                   wl.beam) == (not gated)
+    assert prunedctc.bwd_chunk(prunedctc.PCTC_BF16, wl.M, wl.D, wl.V, 65_536) >= wl.V
+    say(f"lattice schedules gated={gated} V={wl.V} chunk={chunk} {outputs} bias={bias}")
+    H, W, y = to_dev(wl)
+    out = prunedctc.pruned_ctc_fwd_bwd(H, W, y, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam, chunk=chunk,
+                                       want_dH="dH" in outputs, want_dW="dW" in outputs, want_db="db" in outputs,
+                                       bias=None if b is None else torch.from_numpy(b).cuda())
+    np.testing.assert_array_equal(out["status"].cpu().numpy(), ref["status"])
+    assert (ref["status"] != 0).any() == (bias in ("miss", "nan"))
+    assert loss_rel(float(out["loss"].item()), ref["loss"]) <= 1e-5
+    for name in outputs.split():
+        got = out[name].cpu().numpy()
+        assert np.isfinite(got).all(), name
+        assert cosine(got, ref[name]) >= 0.99999, name
 
 
 @pytest.mark.parametrize("nthreads", [2, 6])
