@@ -1304,6 +1304,13 @@ size_t lse_ht_bytes_bf16(int M, int D) {
   return align_up(static_cast<size_t>(D) * ((M + 63) / 64 * 64) * sizeof(uint16_t), 256);
 }
 
+// Whether a normaliser with a bias reads its frames from H transposed: many frames of wide enough
+// heads.  Fused call, V = 180,000: D = 512, 4,215 frames 3,462 -> 3,420 us, 2,304 frames 2,152 -> 2,134;
+// D = 1,920, V = 60,000, 4,215 frames 3,999 -> 3,896; but 331 frames 693 -> 731, D = 1,024, V = 60,000,
+// 1,536 frames 964 -> 1,042, D = 256, V = 100,000, 3,072 frames 1,159 -> 1,176: the kernel takes a
+// unit's whole LDS, which the second stream's kernels beside a short normaliser then wait for.
+bool bias_reads_ht_bf16(int M, int D) { return M > 2048 && D >= 512 && lse_ht_bytes_bf16(M, D) > 0; }
+
 hipError_t launch_ht_build_bf16(const uint16_t* H, int M, int D, const float* g, uint16_t* Hs, uint16_t* Ht, int Mp,
                                 hipStream_t stream) {
   if (M <= 0) return hipSuccess;

@@ -510,7 +510,7 @@ static int32_t fwd_bwd_run(pctc_dtype dtype, const void* H, int32_t D, const voi
       PCTC_HIP(launch_lse_partial_e_bf16(static_cast<const uint16_t*>(H), L.M, D, static_cast<const uint16_t*>(W),
                                          nullptr, V, partials, &P, reinterpret_cast<uint16_t*>(bws), L.bwd.chunk,
                                          L.eparts, einv, stream, Ht, L.bwd.Mp));
-    } else if (dt == 1 && L.o_ht && (!bias || D < kWideD)) {
+    } else if (dt == 1 && L.o_ht && (!bias || bias_reads_ht_bf16(L.M, D))) {
       // no E rows (a bias, db or no room): the same kernel with none of its partitions writing
       // them, frames from H^T
       uint16_t* Ht = reinterpret_cast<uint16_t*>(ws + L.o_ht);
@@ -1065,7 +1065,7 @@ static GroupedLayout grouped_layout(int dt, int M, int D, int V, int K, int chun
   L.o_zero = L.o_lam2f + m8;
   L.o_bo = L.o_zero + m8;
   L.o_ht = L.o_bo + align_up(static_cast<size_t>(V) * 4, 256);
-  const size_t fwd_end = L.o_ht + (dt == 1 ? lse_ht_bytes_bf16(M, D) : 0);
+  const size_t fwd_end = L.o_ht + (dt == 1 && bias_reads_ht_bf16(M, D) ? lse_ht_bytes_bf16(M, D) : 0);
   L.o_G = L.o_part;
   L.o_g = L.o_G + align_up(static_cast<size_t>(M) * K * 4, 256);
   L.o_lam2b = L.o_g + align_up(static_cast<size_t>(M > 0 ? M : 1) * 4, 256);
@@ -1119,7 +1119,7 @@ int32_t pctc_grouped_logprobs(pctc_dtype dtype, const void* H, int32_t M, int32_
     PCTC_HIP(launch_grouped_comp_bias(bias, remap, V, bo, stream));
     PCTC_HIP(launch_lse(dt, H, M, D, W, bo, V, reinterpret_cast<float2*>(ws + L.o_part), lse_o,
                         reinterpret_cast<float2*>(ws + L.o_lam2f), stream,
-                        dt == 1 && lse_ht_bytes_bf16(M, D) ? reinterpret_cast<uint16_t*>(ws + L.o_ht) : nullptr));
+                        dt == 1 && bias_reads_ht_bf16(M, D) ? reinterpret_cast<uint16_t*>(ws + L.o_ht) : nullptr));
   } else {
     PCTC_HIP(launch_fill_d(lse_o, M, -INFINITY, stream));
   }

@@ -209,6 +209,7 @@ hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint
                                      float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
                                      hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0, bool any_m = false);
 size_t lse_ht_bytes_bf16(int M, int D);
+bool bias_reads_ht_bf16(int M, int D);
 int lse_parts_bf16(int M, int D, int V, bool any_m);  // partitions that a normaliser launch of this shape writes
 // rowscale/Hp of ChunkE from the finalize's s_m (in rowscale) and its check flag.
 hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t* einv, float* rowscale, uint16_t* Hp,

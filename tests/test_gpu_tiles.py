@@ -395,10 +395,29 @@ def test_greedy_workspace_sizes(D):
                                 ctypes.c_size_t(least - 1), prunedctc._stream(None)) == -4
 
 
-@pytest.mark.parametrize("M,D,V", [(70, 128, 700), (300, 256, 2049), (33, 72, 300), (260, 2048, 513)])
+@pytest.mark.parametrize("T,V", [([256] * 8, 2000), ([250] * 9, 2305)])
+def test_fused_bias_transposed_frames(T, V):
+    """The biased normaliser of the fused call on both sides of its rule (2,048 and 2,250 frames)."""
+    wl = _fixed("bf16", T, 512, V, V, u_frac=0.1, w_std=0.05)
+    b = np.random.default_rng(6).standard_normal(V).astype(np.float32)
+    say(f"fused bias M={wl.M} V={V}")
+    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam, bias=b)
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    H, W, y = to_dev(wl)
+    out = prunedctc.pruned_ctc_fwd_bwd(H, W, y, wl.input_lengths, wl.target_lengths, wl.blank, wl.beam,
+                                       bias=torch.from_numpy(b).cuda(), want_db=True)
+    assert loss_rel(float(out["loss"].item()), ref["loss"]) <= 1e-5
+    for k in ("dH", "dW", "db"):
+        assert cosine(out[k].cpu().numpy(), ref[k]) >= 0.99999, k
+
+
+@pytest.mark.parametrize("M,D,V", [(70, 128, 700), (300, 256, 2049), (33, 72, 300), (260, 2048, 513),
+                                   (2048, 512, 700), (2049, 512, 2305), (2100, 640, 300)])
 def test_grouped_bias_normaliser(M, D, V):
-    """The complement's normaliser with its -inf bias (frames from H transposed where D is a multiple
-    of 128 and below the wide heads)."""
+    """The complement's normaliser with its -inf bias (frames from H transposed for more than 2,048
+    frames where D is a multiple of 128, from 512 on, and below the wide heads)."""
     import torch
 
     from paper_2609_33645_amd import prunedctc
