@@ -273,9 +273,12 @@ int32_t pctc_greedy_decode(pctc_dtype dtype, const void* H, int32_t D, const voi
  * in lockstep in double precision with one shared per-frame scale; the per-frame emission
  * factors are formed once in float and used by both, so their rounding cancels in the
  * ratio.  Estimates carry the rounding of both sums (they are not certified bounds) and
- * can be slightly negative.  Utterances that are not alignable get NaN.
+ * can be slightly negative.  An arc whose margin lies within S's rounding of the beam may be
+ * decided either way, which moves delta by the mass of its alignments.  Utterances that are not
+ * alignable get NaN.
  * beams: HOST float [nbeams], each finite and >= 0.  delta: device double [nbeams * N].
- * dp_scratch: pctc_discarded_mass_scratch_bytes() bytes.  Synchronises the stream. */
+ * dp_scratch: pctc_discarded_mass_scratch_bytes() bytes.  Scores below -745 nats count as
+ * impossible (an utterance that needs one gets NaN).  Synchronises the stream. */
 size_t pctc_discarded_mass_scratch_bytes(int32_t N, const int32_t* input_lengths,
                                          const int32_t* target_lengths);
 int32_t pctc_discarded_mass(const float* S, int32_t ldS, int32_t K_max, const int32_t* y_rel,

@@ -214,7 +214,7 @@ __device__ __forceinline__ Acc comb3(Acc a, Acc b, Acc c) {
 // bounded by the wave's memory counter (63 instructions: per frame Q emission loads (and two of
 // the next wavefront's states), Q table stores and the offset store, and with a mask up to
 // (Q + 5) / 4 + 1 flag-word loads) and by registers.
-template <int Q, bool MASK>
+template <int Q>
 constexpr int prefetch_depth() {
   return Q <= 2 ? 8 : (Q <= 4 ? 6 : (Q <= 6 ? 4 : 3));
 }
@@ -259,7 +259,7 @@ dp_pass_kernel(const float* __restrict__ S, int ldS, const int32_t* __restrict__
                float* __restrict__ tab_b, double* __restrict__ sc_f, double* __restrict__ sc_b,
                double* __restrict__ total_out, double* __restrict__ loss_n, int N, float* __restrict__ dummy) {
   using Acc = typename std::conditional<VIT, float, double>::type;
-  constexpr int PF = prefetch_depth<Q, MASK>();
+  constexpr int PF = prefetch_depth<Q>();
   constexpr bool MULTI = NWV > 1;
   static_assert(NWV == 1 || NWV == kPassWaves, "a unit is one wavefront or the workgroup");
   __shared__ Exchange<MULTI ? NWV : 1, Acc, 2> xch;
@@ -918,15 +918,16 @@ hipError_t launch_ctc_dp(const DpPlan& plan, const int32_t* T, const int32_t* U,
 
 // ---------------------------------------------------------------------------------------
 // Discarded posterior mass (App. B.3): delta_n = 1 - (sum over retained alignments) /
-// (sum over all valid alignments), both of prod_t p_{pi_t}(t) on the same scores.  One
-// wavefront per utterance and beam runs the two forward recursions in lockstep in linear space
-// and double precision, with one shared scale per frame (a power of two near the full
+// (sum over all valid alignments), both of prod_t p_{pi_t}(t) on the same scores.  One wavefront
+// (four above 128 states) per utterance and beam runs the two forward recursions in lockstep in
+// linear space and double precision, with one shared scale per frame (a power of two near the full
 // recursion's maximum), so the per-frame scaling is exact and cancels in the ratio.  Bound by
 // the latency of its T sequential frames, so all beams run at once (the full recursion again
 // for each of them): nine beams, 16 utterances of up to 375 frames, 9 x 180 us one after
-// another, 104 us together.  The emission factor exp(S - m_t) (m_t the
-// frame's largest selected score) is formed once in float and used by both recursions.
-// Utterances that are not alignable get NaN.
+// another, 104 us together.  The emission factor exp(S), the same for both recursions, is a float
+// significand with its own power of two in double: it loses precision for S below -708 and is zero
+// below -745, so an utterance with a frame whose every reachable state scores less gets NaN, as
+// those that are not alignable do.
 // ---------------------------------------------------------------------------------------
 
 // Linear-space neighbour move: lane l receives lane l-1, lane 0 receives 0 (no state).

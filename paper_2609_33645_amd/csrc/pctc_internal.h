@@ -133,8 +133,8 @@ struct BwdSide {
   SideWork front;
   hipEvent_t front_gate = nullptr;
   int nwork = 0;
-  // the lattice is longer than the dense part: no gates, work[0] enqueued before the first chunk and
-  // the rest right after it
+  // the lattice is more than half as long as the dense part (it is then on the critical path): no
+  // gates, work[0] enqueued before the first chunk and the rest right after it
   bool eager = false;
   const float* dH_extra = nullptr;
   bool hs_built = false;
