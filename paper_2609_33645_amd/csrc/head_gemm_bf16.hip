@@ -1075,15 +1075,46 @@ hipError_t launch_union_merge_bf16(const int32_t* Kdev, int K_max, const int32_t
 // run length also sets the L2 reuse of the tile order), unless those make less than one round
 // of workgroups (few frames or a small vocabulary); then the run whose rounds are shortest by a
 // tile's time (0.5 us a 32-deep k-tile, 4 us the epilogue) and 4 us a workgroup: 331 frames,
-// D = 512, V = 180,000, 176 workgroups of 8 tiles 125 us, 236 of 6 101 us; 150 frames (argmax),
-// 88 of 8 tiles 94 us, 235 of 3 46 us.  any_m: the runs of many frames whatever M, so that a
-// frame's lambda does not depend, to the last bit, on how many frames are beside it.
+// D = 512, V = 180,000, 176 workgroups of 8 tiles 125 us, 236 of 6 101 us.  The argmax's epilogue is
+// shorter, and its tile order is padded to whole groups, so that some XCDs get more of the tiles
+// than others: its rounds are the fullest XCD's (8,192 frames, D = 512, V = 9,000: 192 workgroups of 6
+// tiles 150 us, 41 of them on one XCD's 32 units, 160 of 8 92 us).  150 frames, D =
+// 512, V = 180,000: 88 workgroups of 8 tiles 86 us, 235 of 3 46 us; 6,722 frames, D = 64, V = 8,931: 135 of
+// 8 30 us, 243 of 4 36, 189 of 5 25.
+// kAnyM: the runs of many frames whatever M, so that a frame's lambda does not depend, to the last
+// bit, on how many frames are beside it.
+enum class SplitFor { kLse, kAnyM, kAmax };
 struct LseSplit {
   bool wide;  // D >= kWideD: one vocabulary tile per partition (argmax: GWide tiles)
   int vper, P, nM;
 };
 
-static LseSplit lse_split_bf16(int M, int D, int V, bool any_m = false) {
+// Rounds of one workgroup per CU (32 an XCD) that the fullest XCD gets of nA x nB tiles in
+// grouped_tile's order.
+static int grouped_rounds(int nA, int nB) {
+  int ga, gb;
+  group_shape(nA, ga, gb);
+  const int gA = (nA + ga - 1) / ga, per = std::max(grouped_grid(nA, nB) / 8, 1);
+  int most = 0, here = 0, left = per;  // tiles of the XCD at hand, its ids left
+  for (int blk = 0; blk * ga * gb < 8 * per; ++blk) {
+    const int ra = std::min(ga, nA - blk % gA * ga), rb = std::min(gb, nB - blk / gA * gb);
+    auto before = [&](int in) { return std::min(in / ga, rb) * ra + (in / ga < rb ? std::min(in % ga, ra) : 0); };
+    for (int in = 0; in < ga * gb;) {
+      const int to = std::min(ga * gb, in + left);
+      here += before(to) - before(in);
+      left -= to - in;
+      in = to;
+      if (left == 0) {
+        most = std::max(most, here);
+        here = 0;
+        left = per;
+      }
+    }
+  }
+  return (most + 31) / 32;
+}
+
+static LseSplit lse_split_bf16(int M, int D, int V, SplitFor what) {
   LseSplit s;
   s.wide = D >= kWideD;
   constexpr int TR = 256, TC = 256;
@@ -1095,13 +1126,15 @@ static LseSplit lse_split_bf16(int M, int D, int V, bool any_m = false) {
   if (!s.wide && run < kMidRun) {
     const int least = run > 1 ? run : 1;
     run = kMidRun;
-    if (!any_m && s.nM * ((vtiles + kMidRun - 1) / kMidRun) < 256) {
+    if (what != SplitFor::kAnyM && s.nM * ((vtiles + kMidRun - 1) / kMidRun) < 256) {
+      const bool amax = what == SplitFor::kAmax;
+      const double tile = amax ? D / 32 * 0.53 + 1.4 : D / 32 * 0.5 + 4;
       double best = -1;
       for (int r = kMidRun; r >= least; --r) {
-        const int wgs = s.nM * ((vtiles + r - 1) / r);
-        const double t = ((wgs + 255) / 256) * (r * (D / 32 * 0.5 + 4) + 4);
+        const int P = (vtiles + r - 1) / r;
+        const double t = (amax ? grouped_rounds(s.nM, P) : (s.nM * P + 255) / 256) * (r * tile + 4);
         if (best < 0 || t < best) {
-          best = t;
+          best = (amax && best < 0) ? 0.9 * t : t;  // the argmax leaves runs of kMidRun for a tenth only
           run = r;
         }
       }
@@ -1112,12 +1145,13 @@ static LseSplit lse_split_bf16(int M, int D, int V, bool any_m = false) {
   return s;
 }
 
-int lse_part_columns_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V).vper; }
-int lse_parts_bf16(int M, int D, int V, bool any_m) { return lse_split_bf16(M, D, V, any_m).P; }
+int lse_part_columns_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V, SplitFor::kLse).vper; }
+int lse_parts_any_m_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V, SplitFor::kAnyM).P; }
+int amax_parts_bf16(int M, int D, int V) { return lse_split_bf16(M, D, V, SplitFor::kAmax).P; }
 
 hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                    float2* partials, int* P_out, hipStream_t stream, bool any_m) {
-  const LseSplit sp = lse_split_bf16(M, D, V, any_m);
+  const LseSplit sp = lse_split_bf16(M, D, V, any_m ? SplitFor::kAnyM : SplitFor::kLse);
   const int vper = sp.vper, Peff = sp.P;
   *P_out = Peff;
   Prof pr("lse_partial", stream);
@@ -1142,7 +1176,7 @@ bool amax_reads_ht_bf16(int M, int D) { return M > 512 && lse_ht_bytes_bf16(M, D
 
 hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                     float2* partials, int* P_out, hipStream_t stream, const uint16_t* Ht, int Mp) {
-  const LseSplit sp = lse_split_bf16(M, D, V);
+  const LseSplit sp = lse_split_bf16(M, D, V, SplitFor::kAmax);
   const int vper = sp.vper, Peff = sp.P;
   *P_out = Peff;
   Prof pr("amax_partial", stream);
@@ -1267,7 +1301,7 @@ hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t*
 
 int lse_e_parts_bf16(int M, int D, int V, int chunk) {
   if (M <= 0 || D % (GMid::kNS * GMid::KK * 16) != 0 || chunk <= 0) return 0;
-  const LseSplit sp = lse_split_bf16(M, D, V);
+  const LseSplit sp = lse_split_bf16(M, D, V, SplitFor::kLse);
   if (chunk % sp.vper != 0) return 0;
   const int ep = chunk / sp.vper;
   return ep < sp.P ? ep : sp.P;
@@ -1276,7 +1310,7 @@ int lse_e_parts_bf16(int M, int D, int V, int chunk) {
 hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                      float2* partials, int* P_out, uint16_t* E, int epitch, int eparts, int32_t* einv,
                                      hipStream_t stream, const uint16_t* Ht, int Mp, bool any_m) {
-  const LseSplit sp = lse_split_bf16(M, D, V, any_m);
+  const LseSplit sp = lse_split_bf16(M, D, V, any_m ? SplitFor::kAnyM : SplitFor::kLse);
   *P_out = sp.P;
   const dim3 grid(sp.nM * sp.P), block(GMid::kThreads);
   Prof pr("lse_partial", stream);

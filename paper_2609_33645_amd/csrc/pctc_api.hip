@@ -835,16 +835,15 @@ int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, c
   // less moves a discarded mass by far more than S's last bit (with partitions chosen by M one
   // batch's masses moved by 5e-4; the shorter runs of few frames save 24 us at 331 frames, V =
   // 180,000)
-  constexpr bool any_m = true;
   uint16_t* Ht = nullptr;
   if (dt == 1 && !misaligned16(partials)) {
     const size_t ht = lse_ht_bytes_bf16(M, D);
-    const size_t used = ht ? align_up(static_cast<size_t>(lse_parts_bf16(M, D, V, any_m)) * M * sizeof(float2), 256) : 0;
+    const size_t used = ht ? align_up(static_cast<size_t>(lse_parts_any_m_bf16(M, D, V)) * M * sizeof(float2), 256) : 0;
     if (ht && used + ht <= lse_partial_bytes(M, D))
       Ht = reinterpret_cast<uint16_t*>(static_cast<char*>(partials) + used);
   }
   PCTC_HIP(launch_lse(dt, H, M, D, W, nullptr, V, static_cast<float2*>(partials), lam, lam2, stream, Ht,
-                      any_m));
+                      /*any_m=*/true));
   if (S && u_ids && K) PCTC_HIP(launch_gather_s(dt, H, M, D, W, nullptr, u_ids, K, K_max, lam, S, ldS, stream));
   PCTC_HIP(hipStreamSynchronize(stream));
   prof_flush();
@@ -898,7 +897,7 @@ static size_t greedy_ht(int dt, int32_t M, int32_t D, int32_t V, size_t base, si
   *end = base;
   if (dt != 1 || !amax_reads_ht_bf16(M, D)) return 0;
   const size_t ht = lse_ht_bytes_bf16(M, D);
-  const size_t used = align_up(static_cast<size_t>(lse_parts_bf16(M, D, V, false)) * M * sizeof(float2), 256);
+  const size_t used = align_up(static_cast<size_t>(amax_parts_bf16(M, D, V)) * M * sizeof(float2), 256);
   if (used + ht <= lse_partial_bytes(M, D)) return used;
   *end = base + ht;
   return base;

@@ -210,7 +210,9 @@ hipError_t launch_lse_partial_e_bf16(const uint16_t* H, int M, int D, const uint
                                      hipStream_t stream, const uint16_t* Ht = nullptr, int Mp = 0, bool any_m = false);
 size_t lse_ht_bytes_bf16(int M, int D);
 bool bias_reads_ht_bf16(int M, int D);
-int lse_parts_bf16(int M, int D, int V, bool any_m);  // partitions that a normaliser launch of this shape writes
+// Partitions that a normaliser launch with any_m, and an argmax launch, of this shape write.
+int lse_parts_any_m_bf16(int M, int D, int V);
+int amax_parts_bf16(int M, int D, int V);
 // rowscale/Hp of ChunkE from the finalize's s_m (in rowscale) and its check flag.
 hipError_t launch_hs_scale_bf16(const uint16_t* Hs, int M, int D, const int32_t* einv, float* rowscale, uint16_t* Hp,
                                 hipStream_t stream);

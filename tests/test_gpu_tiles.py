@@ -221,7 +221,7 @@ def test_lse_select_does_not_depend_on_the_batch(D, V):
         assert torch.equal(few["lam"], all_["lam"][:m]) and torch.equal(few["S"], all_["S"][:m]), m
 
 
-@pytest.mark.parametrize("M,V", [(1, 700), (150, 50_000), (257, 2500)])
+@pytest.mark.parametrize("M,V", [(1, 700), (150, 50_000), (257, 2500), (6700, 8931), (8192, 9000), (4000, 2300)])
 def test_greedy_few_frames(M, V):
     from paper_2609_33645_amd import prunedctc
     wl = _fixed("bf16", [M], 128, V, M, u_frac=0.0)
