@@ -255,7 +255,7 @@ int32_t pctc_ctc_dp(const float* S, int32_t ldS, int32_t K_max, const int32_t* y
  * workspace: at least pctc_greedy_workspace_size(N, M, D) bytes, 256-byte aligned (independent of
  * V).  With pctc_greedy_workspace_size_ex(dtype, N, M, D, V) bytes, which is more for some bf16
  * heads (at most 2 (M + 63) D bytes more), the argmax reads its frames from a transposed copy of H,
- * about 5% faster with the same result; it also does where that copy fits in the smaller size.
+ * about 5% faster, with the same result; it also does where that copy fits in the smaller size.
  * Both return 0 for invalid arguments.  NaN logits give an unspecified id for their frame.  Synchronises
  * the stream. */
 size_t pctc_greedy_workspace_size(int32_t N, int32_t M, int32_t D);

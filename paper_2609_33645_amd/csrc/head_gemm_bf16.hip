@@ -1169,10 +1169,13 @@ hipError_t launch_lse_partial_bf16(const uint16_t* H, int M, int D, const uint16
   return hipGetLastError();
 }
 
-// The argmax's frames come from H transposed (Ht, lse_ht_bytes_bf16) for narrow heads of more than two
-// frame tiles: below that the transpose's launch costs what its whole lines save (150 frames 46 us
-// either way; 4,347 frames, D = 512, V = 180,000: 767 -> 727 us).
-bool amax_reads_ht_bf16(int M, int D) { return M > 512 && lse_ht_bytes_bf16(M, D) > 0; }
+// Whether an argmax, or the stage entry's normaliser, reads its frames from H transposed (Ht,
+// lse_ht_bytes_bf16): it saves 7% of the product and costs a launch of 7 to 12 us, so from products of
+// about 150 us on.  4,215 frames, D = 512, V = 180,000: 770 -> 730 us; 4,096 frames, V = 36,000 197 -> 184 + 12;
+// D = 128, V = 8,931, 6,722 frames 38 -> 39 + 7.
+bool frames_from_ht_bf16(int M, int D, int V) {
+  return static_cast<double>(M) * V * D >= 8e10 && lse_ht_bytes_bf16(M, D) > 0;
+}
 
 hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                     float2* partials, int* P_out, hipStream_t stream, const uint16_t* Ht, int Mp) {

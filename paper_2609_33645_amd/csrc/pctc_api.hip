@@ -836,7 +836,7 @@ int32_t pctc_lse_select(pctc_dtype dtype, const void* H, int32_t M, int32_t D, c
   // batch's masses moved by 5e-4; the shorter runs of few frames save 24 us at 331 frames, V =
   // 180,000)
   uint16_t* Ht = nullptr;
-  if (dt == 1 && !misaligned16(partials)) {
+  if (dt == 1 && !misaligned16(partials) && frames_from_ht_bf16(M, D, V)) {
     const size_t ht = lse_ht_bytes_bf16(M, D);
     const size_t used = ht ? align_up(static_cast<size_t>(lse_parts_any_m_bf16(M, D, V)) * M * sizeof(float2), 256) : 0;
     if (ht && used + ht <= lse_partial_bytes(M, D))
@@ -895,7 +895,7 @@ static size_t greedy_layout(int32_t N, int32_t M, int32_t D, size_t* o_toff, siz
 // layout, where a caller may bring room for it.  end: the workspace that this needs.
 static size_t greedy_ht(int dt, int32_t M, int32_t D, int32_t V, size_t base, size_t* end) {
   *end = base;
-  if (dt != 1 || !amax_reads_ht_bf16(M, D)) return 0;
+  if (dt != 1 || !frames_from_ht_bf16(M, D, V)) return 0;
   const size_t ht = lse_ht_bytes_bf16(M, D);
   const size_t used = align_up(static_cast<size_t>(amax_parts_bf16(M, D, V)) * M * sizeof(float2), 256);
   if (used + ht <= lse_partial_bytes(M, D)) return used;

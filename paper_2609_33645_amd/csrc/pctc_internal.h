@@ -69,12 +69,12 @@ hipError_t launch_gather_s(int dtype, const void* H, int M, int D, const void* W
                            hipStream_t stream, float* Gz = nullptr);
 
 // ---- greedy emission head -----------------------------------------------------------------
-// Ht (null: none): scratch of lse_ht_bytes_bf16(M, D) for H transposed, where amax_reads_ht_bf16.
+// Ht (null: none): scratch of lse_ht_bytes_bf16(M, D) for H transposed, where frames_from_ht_bf16.
 // partials: lse_partial_bytes(M, D); ids [M]; tokens [M] (utterance n at toff[n]); lengths [N].
 hipError_t launch_greedy(int dtype, const void* H, int M, int D, const void* W, const float* bias, int V,
                          const int32_t* toff, int N, int blank, float2* partials, int32_t* ids, int32_t* tokens,
                          int32_t* lengths, hipStream_t stream, uint16_t* Ht);
-bool amax_reads_ht_bf16(int M, int D);
+bool frames_from_ht_bf16(int M, int D, int V);
 hipError_t launch_amax_partial_bf16(const uint16_t* H, int M, int D, const uint16_t* W, const float* bias, int V,
                                     float2* partials, int* P_out, hipStream_t stream, const uint16_t* Ht, int Mp);
 

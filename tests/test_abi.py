@@ -92,7 +92,7 @@ def test_host_side_sizing_rules():
         base = up(parts * M * 8) + up(17 * 4) + up(M * 4)
         assert lib.pctc_greedy_workspace_size(16, M, D) == base
         assert lib.pctc_greedy_workspace_size_ex(0, 16, M, D, 180_000) == base
-        # a bf16 argmax of many frames of a narrow head has H transposed, past the layout where the
+        # a large bf16 argmax of a narrow head has H transposed, past the layout where the
         # partials leave no room (V = 180,000: 88 partitions written of 256)
         ht = up(2 * D * ((M + 63) // 64 * 64)) if (M, D) == (4215, 1024) else 0
         assert lib.pctc_greedy_workspace_size_ex(1, 16, M, D, 180_000) == base + ht

@@ -205,7 +205,7 @@ def test_few_frames_slices(T, D, V):
     assert cosine(res["dW"], ref["dW"]) >= 0.99999
 
 
-@pytest.mark.parametrize("D,V", [(256, 20_001), (72, 20_001), (2048, 700)])
+@pytest.mark.parametrize("D,V", [(256, 20_001), (256, 60_001), (72, 20_001), (2048, 700)])
 def test_lse_select_does_not_depend_on_the_batch(D, V):
     """A frame's lambda and S are the same, to the last bit, alone and in a batch: S decides the
     arcs at a beam's edge, where its last bit moves the discarded mass."""
@@ -351,7 +351,8 @@ def test_union_block_edges(V):
 
 # ---- frames from H transposed: argmax and normaliser with bias -------------------------------------
 
-@pytest.mark.parametrize("M,V,bias", [(513, 2000, False), (700, 2305, True), (512, 300, True)])
+@pytest.mark.parametrize("M,V,bias", [(513, 2000, False), (700, 2305, True), (512, 300, True),
+                                      (5210, 59_990, False), (5201, 60_100, True)])  # the last two transposed
 def test_greedy_transposed_frames(M, V, bias):
     import torch
 
@@ -369,18 +370,20 @@ def test_greedy_transposed_frames(M, V, bias):
 @pytest.mark.parametrize("D", [256, 1024])
 def test_greedy_workspace_sizes(D):
     """The same ids and tokens with the smallest workspace (D = 256: H transposed in what the
-    partials leave; D = 1024: none) and with room for H transposed."""
+    partials leave; D = 1024: none) and with room for H transposed (from M V D = 8e10 on)."""
     import ctypes
 
     import torch
 
     from paper_2609_33645_amd import prunedctc
-    L, N, V = prunedctc.lib(), 2, 3000
-    wl = _fixed("bf16", [400, 301], D, V, D, u_frac=0.0, w_std=0.1)
+    L, N = prunedctc.lib(), 2
+    V = int(8e10 / D / 3701) + 1
+    wl = _fixed("bf16", [400, 3301], D, V, D, u_frac=0.0, w_std=0.1)
     H, W, _ = to_dev(wl)
     T, M = wl.input_lengths, wl.M
     least, most = L.pctc_greedy_workspace_size(N, M, D), L.pctc_greedy_workspace_size_ex(1, N, M, D, V)
     assert (most > least) == (D == 1024)
+    assert L.pctc_greedy_workspace_size_ex(1, N, M, D, V - 1) == least
     p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
     got = []
     for size in (least, most):
