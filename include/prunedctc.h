@@ -152,7 +152,8 @@ int32_t pruned_ctc_fwd_bwd(pctc_dtype dtype, const void* H, int32_t D, const voi
  * utt_weight  device float [N] or NULL (all 1): loss = sum_n w_n L_n over the included
  *             utterances, and dH, dW, db are the gradients of that sum.  loss_per_utt
  *             still receives the unweighted L_n.  A zero weight excludes the utterance
- *             from the gradients.  fp32 heads: |w_n| below 2^103 (dL/dZ is kept times 2^24).
+ *             from the gradients.  fp32 heads: weights and gradients below 2^103 in magnitude
+ *             (dL/dZ is kept times 2^24; larger ones become infinite).
  * db          device float [V] or NULL: dL/db, the column sums of dL/dZ (bf16 path:
  *             the sums of the bf16-rounded dL/dZ that the dH and dW products also use).
  * Every other argument is as for pruned_ctc_fwd_bwd, which equals this call with three

@@ -797,6 +797,16 @@ hipError_t launch_dp_tail(int N, const double* loss_n, const int32_t* status, co
 
 // ---------------------------------------------------------------------------------------
 
+// LDS that keeps a workgroup off a compute unit where a dW product's runs (128 of 160 KB).  Beside it
+// a pass of up to 96 registers would fit, and both run slower than on units of their own, which
+// dW's launches of narrow heads leave free: 30 x 200 frames, D = 256, V = 150,000 (152 workgroups),
+// the Viterbi pass 167 us and dW 179, apart 61 and 141.  For the passes whose registers do not see
+// to it themselves (one wavefront of one state a lane has always run beside dW).
+constexpr size_t kOffDw = 32768 + 512;
+constexpr bool reserve_lds(int Q, int nwv, bool vit, bool mask) {
+  return nwv == 1 ? Q == 2 && vit : Q == 1 && (vit || !mask);
+}
+
 template <bool VIT>
 static hipError_t launch_pass(int Q, int nwv, int N, hipStream_t stream, const float* S, int ldS, const int32_t* toff,
                               const int32_t* yoff, const int64_t* soff, const int32_t* y_rel, int32_t* status,
@@ -805,11 +815,12 @@ static hipError_t launch_pass(int Q, int nwv, int N, hipStream_t stream, const f
 #define PCTC_PASS(QQ, NWV)                                                                                        \
   if (Q == QQ && nwv == NWV) {                                                                                    \
     const dim3 grid(NWV > 1 ? 2 * N : (2 * N + kPassWaves - 1) / kPassWaves);                                     \
+    const size_t lds = reserve_lds(QQ, NWV, VIT, mask != nullptr) ? kOffDw : 0;                                   \
     if (mask)                                                                                                     \
-      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, !VIT, NWV>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS,     \
+      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, !VIT, NWV>), grid, dim3(64 * kPassWaves), lds, stream, S, ldS,   \
                          toff, yoff, soff, y_rel, status, mask, tf, tb, sf, sb, total, loss_n, N, dummy);         \
     else                                                                                                          \
-      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, false, NWV>), grid, dim3(64 * kPassWaves), 0, stream, S, ldS,    \
+      hipLaunchKernelGGL((dp_pass_kernel<QQ, VIT, false, NWV>), grid, dim3(64 * kPassWaves), lds, stream, S, ldS,  \
                          toff, yoff, soff, y_rel, status, nullptr, tf, tb, sf, sb, total, loss_n, N, dummy);      \
     return hipGetLastError();                                                                                     \
   }

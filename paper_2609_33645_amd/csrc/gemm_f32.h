@@ -24,9 +24,10 @@
 // groups, one a phase behind the other, so that on every SIMD one wave issues its 48 products
 // (1536 cycles, registers only) while the other copies, reads and splits its next k-tile.
 // Measured (normaliser pass over M = 16,000, D = 512, V = 16,384; the fp32 units took 2390 us):
-// 1250 us; with x0 cut 1260, and then 1135 with the splitting left out; with the splits interleaved with the products in
-// each wave instead of the phases 1540; with the remainders from v_dot2_f32_bf16 (7 instructions
-// per pair instead of 11) 1430: that instruction keeps the matrix pipe from issuing.
+// 1250 us (with x0 cut 1260, and then 1135 with the splitting left out); with the splits
+// interleaved with the products in each wave instead of the phases 1540; with the remainders from
+// v_dot2_f32_bf16 (7 instructions per pair instead of 11) 1430: that instruction keeps the matrix
+// pipe from issuing.
 //
 // LDS layouts: KC [row][k] (k contiguous in memory; 64-byte rows, 16-byte slots XORed with
 // (row >> 2) mod 4, as KC<32> of gemm_bf16.h) and MC [k][row] (rows contiguous; 1 KB k-lines,

@@ -27,8 +27,8 @@ using GH = f3::Gemm<LL::KC, LL::MC>;               // dH = dZ W
 using GW = f3::Gemm<LL::MC, LL::MC>;               // dW = dZ^T H
 constexpr int kTile = f3::kT;
 // dZ is kept times 2^24 (exact, and taken off where its products and sums are written), so that
-// probabilities down to fp32's least split into parts without loss (see gemm_f32.h); loss weights up
-// to 2^103 stay finite.
+// probabilities down to fp32's least split into parts without loss (see gemm_f32.h); loss weights and
+// gradients up to 2^103 stay finite.
 constexpr float kDzScale = 16777216.f, kDzUnscale = 1.f / kDzScale;
 
 #define PCTC_F3_STAGES                                                          \

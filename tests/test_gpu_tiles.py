@@ -166,6 +166,27 @@ def test_f32_infinite_operands(V):
     np.testing.assert_array_equal(ids[wl.H[:, 7] < 0], rest.argmax(1))
 
 
+def test_f32_largest_frame_values():
+    """Values that round to infinity in bf16 in the weights' product too (frames of 3.4e38 where the
+    weights are zero, a loss weight of 1e-20): on the fp32 instructions, and as the oracle has it."""
+    import torch
+
+    from paper_2609_33645_amd import prunedctc
+    wl = _fixed("f32", [300, 41], 40, 300, 23, w_std=0.2)
+    wl.W[:, 5] = 0.0
+    wl.H[::3, 5] = 3.4e38
+    w = np.full(2, 1e-20, np.float32)
+    H, W, y = to_dev(wl)
+    out = prunedctc.pruned_ctc_fwd_bwd(H, W, y, wl.input_lengths, wl.target_lengths, 0, wl.beam,
+                                       utt_weight=torch.from_numpy(w).cuda())
+    ref = oracle.fwd_bwd(wl.H, wl.W, wl.targets, wl.input_lengths, wl.target_lengths, 0, wl.beam, weights=w)
+    assert loss_rel(float(out["loss"].item()), ref["loss"]) <= 1e-5
+    dW, dH = out["dW"].cpu().numpy(), out["dH"].cpu().numpy()
+    assert rel_err(dW[:, 5], ref["dW"][:, 5]) <= 1e-5 and np.abs(ref["dW"][:, 5]).max() > 1e17
+    assert rel_err(np.delete(dW, 5, 1), np.delete(ref["dW"], 5, 1)) <= 1e-5
+    assert rel_err(dH, ref["dH"]) <= 1e-5
+
+
 # ---- discarded mass of several beams in one launch ----------------------------------------------
 
 @pytest.mark.parametrize("nbeams", [1, 2, 9, 10, 20])
