@@ -349,12 +349,13 @@ static int t_max_of(int N, const int32_t* T) {
   return t;
 }
 
-// Whether the lattice (T sequential frames a pass, whatever the batch) is more than half as long as
-// the dense part of the backward beside it, by 1 PFLOP/s and by what a frame takes: 0.45 us a
-// total-score pass on one wavefront (up to 128 states), 0.3 + 0.12 per state a lane on four,
-// about two thirds of that for the Viterbi pass, and 100 us of small launches around them.
-// 331 frames, D = 512, V = 180,000 (dense part 180 us, lattice 350): 661 us ungated against
-// 686; 16 utterances of up to 375 frames there (2400 us, 380): gated.
+// Whether the lattice (T sequential frames a pass, whatever the batch) is taken for more than half as
+// long as the dense part of the backward beside it, by 1 PFLOP/s for the latter and, a frame,
+// 0.45 us of a total-score pass on one wavefront (up to 128 states; 0.42 measured), 0.3 + 0.12 per
+// state a lane on four, two thirds more for the Viterbi pass (0.18 us measured), and 100 us of small
+// launches around them.  331 frames, D = 512, V = 180,000 (taken for 180 us of products and 345 of
+// lattice; short launches are far from that rate: 460 and 220 measured, beside each other): 661 us
+// ungated against 686; 16 utterances of up to 375 frames there (2400 us, 380): gated.
 static bool lattice_leads(const DpPlan& dp, int t_max, int D, int V) {
   const double dense = 6.0 * dp.M * static_cast<double>(V) * D / 1e9;
   const double frame = dp.Smax <= 128 ? 0.45 : 0.3 + 0.12 * ((dp.Smax + 255) / 256);
